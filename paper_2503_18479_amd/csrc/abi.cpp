@@ -81,9 +81,9 @@ void dfree(T *&p) {
 }
 
 void plan_free_workspace(cosim_plan *p) {
-    dfree(p->bWt);
+    dfree(p->bX);
     dfree(p->bZmax);
-    dfree(p->bTinv);
+    dfree(p->bD);
     dfree(p->bA32);
     dfree(p->I_ws);
     dfree(p->rpart);
@@ -123,8 +123,8 @@ BigFactor big_factor_args(const cosim_plan *p) {
     bf.ldl = p->ldl_ok;
     bf.fmt = p->fac.fmt;
     bf.zmax = p->bZmax;
-    bf.wt = p->bWt;
-    bf.tinv = p->bTinv;
+    bf.x = p->bX;
+    bf.d = p->bD;
     return bf;
 }
 
@@ -190,12 +190,12 @@ int ensure_workspace(cosim_plan *p, size_t systems, int chunks, size_t parts = 0
     const size_t n = (size_t)p->n, NP = (size_t)p->NP;
     const bool big = big_plan(p->NP);
     if (big && p->ldl_ok &&
-        (hipMalloc((void **)&p->bWt, ns * 64 * NP * sizeof(double2)) != hipSuccess ||
+        (hipMalloc((void **)&p->bX, ns * 64 * NP * sizeof(double2)) != hipSuccess ||
          hipMalloc((void **)&p->bZmax, ns * sizeof(double)) != hipSuccess ||
-         hipMalloc((void **)&p->bTinv, ns * 64 * 64 * sizeof(double2)) != hipSuccess)) {
+         hipMalloc((void **)&p->bD, ns * 2 * NP * sizeof(double2)) != hipSuccess)) {
         plan_free_workspace(p);
         (void)hipGetLastError();
-        return fail(COSIM_ENOMEM, "LDL^T panel workspace for %zu systems failed", ns);
+        return fail(COSIM_ENOMEM, "LDL^T workspace for %zu systems failed", ns);
     }
     if (need32 && hipMalloc(&p->bA32, ns * NP * NP * sizeof(float2)) != hipSuccess) {
         plan_free_workspace(p);
@@ -352,10 +352,10 @@ struct StreamPool {
     hipEvent_t ws_free = nullptr;
     bool ws_used = false;
     // factor records of grouped instances, sized for the largest call so far
-    double2 *gA = nullptr, *gWt = nullptr, *gTinv = nullptr;
+    double2 *gA = nullptr, *gX = nullptr, *gD = nullptr;
     int *gPiv = nullptr, *gFmt = nullptr;
     double *gZmax = nullptr;
-    size_t capA = 0, capWt = 0, capTinv = 0, capPiv = 0, capSys = 0;
+    size_t capA = 0, capX = 0, capD = 0, capPiv = 0, capSys = 0;
 };
 constexpr int kPoolStreams = 16;
 
@@ -374,27 +374,27 @@ int pool_events(StreamPool *pool, size_t count) {
 
 // Group workspace of at least the given sizes (elements).  Growing it waits
 // for the device first: earlier calls may still be using the old buffers.
-int pool_group_ws(StreamPool *pool, size_t nA, size_t nWt, size_t nTinv, size_t nPiv, size_t nSys) {
-    if (nA <= pool->capA && nWt <= pool->capWt && nTinv <= pool->capTinv && nPiv <= pool->capPiv &&
+int pool_group_ws(StreamPool *pool, size_t nA, size_t nX, size_t nD, size_t nPiv, size_t nSys) {
+    if (nA <= pool->capA && nX <= pool->capX && nD <= pool->capD && nPiv <= pool->capPiv &&
         nSys <= pool->capSys)
         return COSIM_OK;
     HIP_TRY(hipDeviceSynchronize());
     dfree(pool->gA);
-    dfree(pool->gWt);
-    dfree(pool->gTinv);
+    dfree(pool->gX);
+    dfree(pool->gD);
     dfree(pool->gPiv);
     dfree(pool->gFmt);
     dfree(pool->gZmax);
-    pool->capA = pool->capWt = pool->capTinv = pool->capPiv = pool->capSys = 0;
+    pool->capA = pool->capX = pool->capD = pool->capPiv = pool->capSys = 0;
     if (hipMalloc((void **)&pool->gA, nA * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&pool->gWt, nWt * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&pool->gTinv, nTinv * sizeof(double2)) != hipSuccess ||
+        hipMalloc((void **)&pool->gX, nX * sizeof(double2)) != hipSuccess ||
+        hipMalloc((void **)&pool->gD, nD * sizeof(double2)) != hipSuccess ||
         hipMalloc((void **)&pool->gPiv, nPiv * sizeof(int)) != hipSuccess ||
         hipMalloc((void **)&pool->gFmt, nSys * sizeof(int)) != hipSuccess ||
         hipMalloc((void **)&pool->gZmax, nSys * sizeof(double)) != hipSuccess) {
         dfree(pool->gA);
-        dfree(pool->gWt);
-        dfree(pool->gTinv);
+        dfree(pool->gX);
+        dfree(pool->gD);
         dfree(pool->gPiv);
         dfree(pool->gFmt);
         dfree(pool->gZmax);
@@ -402,8 +402,8 @@ int pool_group_ws(StreamPool *pool, size_t nA, size_t nWt, size_t nTinv, size_t 
         return fail(COSIM_ENOMEM, "group workspace allocation failed");
     }
     pool->capA = nA;
-    pool->capWt = nWt;
-    pool->capTinv = nTinv;
+    pool->capX = nX;
+    pool->capD = nD;
     pool->capPiv = nPiv;
     pool->capSys = nSys;
     return COSIM_OK;
@@ -823,7 +823,7 @@ int cosim_solve(cosim_plan_t p, int B, int F, const double *C_d, const double *o
     if (big_plan(p->NP)) {
         const BigFactor bf = big_factor_args(p);
         const BigRefine rf = big_refine_args(p, COSIM_FP64);
-        HIP_TRY(big_factor(bf, rf, p->NP, p->n, S, F, p->M_d, p->R_d, C_d, omega_d, p->fac.L,
+        HIP_TRY(big_factor(bf, rf, p->NP, p->n, S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d, p->fac.L,
                            p->fac.piv_row, status_d, st));
         HIP_TRY(big_solve(bf, rf, p->NP, p->n, S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                           p->fac.L, p->fac.piv_row, I, kRhsExcitation, nullptr, 0, 0.0, nullptr,
@@ -918,7 +918,7 @@ int cosim_field_backward(cosim_plan_t p, int B, int F, const double *C_d, const 
     } else if (big_plan(p->NP)) {
         const BigFactor bf = big_factor_args(p);
         const BigRefine rf = big_refine_args(p, COSIM_FP64);
-        HIP_TRY(big_factor(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, C_d, omega_d,
+        HIP_TRY(big_factor(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                            p->fac.L, p->fac.piv_row, status_d, st));
         HIP_TRY(big_solve(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                           p->fac.L, p->fac.piv_row, I, kRhsPairs, p->rpart, sh.nchunk, 0.5,
@@ -1057,7 +1057,7 @@ static int loss_and_grad_impl(cosim_plan_t p, int B, int F, const double *C_d, c
         // factor, GEMM contractions with the loss epilogue between, solves
         const BigFactor bf = big_factor_args(p);
         const BigRefine rf = big_refine_args(p, precision);
-        HIP_TRY(big_factor(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, C_d, omega_d,
+        HIP_TRY(big_factor(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                            p->fac.L, p->fac.piv_row, status_d, st));
         HIP_TRY(big_solve(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                           p->fac.L, p->fac.piv_row, p->I_ws, kRhsExcitation, nullptr, 0, 0.0,
@@ -1408,18 +1408,18 @@ static int enqueue_big_group(const ManyCall &mc, const std::vector<int> &g, int 
     bf.ldl = true;
     bf.fmt = pool->gFmt + off[4];
     bf.zmax = pool->gZmax + off[4];
-    bf.wt = pool->gWt + off[1];
-    bf.tinv = pool->gTinv + off[2];
+    bf.x = pool->gX + off[1];
+    bf.d = pool->gD + off[2];
     double2 *A = pool->gA + off[0];
     int *piv = pool->gPiv + off[3];
     off[0] += (size_t)Sg * NP * NP;
     off[1] += (size_t)Sg * 64 * NP;
-    off[2] += (size_t)Sg * 64 * 64;
+    off[2] += (size_t)Sg * 2 * NP;
     off[3] += (size_t)Sg * NP;
     off[4] += (size_t)Sg;
     hipEvent_t ev_fwd = pool->extra[group];
     if (big_group_factor(bf, ga, NP, Sg, A, piv, gs) != hipSuccess ||
-        big_group_solve(ga, NP, Sg, A, piv, kRhsExcitation, gs) != hipSuccess ||
+        big_group_solve(bf, ga, NP, Sg, A, piv, kRhsExcitation, gs) != hipSuccess ||
         hipEventRecord(ev_fwd, gs) != hipSuccess) {
         return fail(COSIM_EDEVICE, "grouped solve launch failed");
     }
@@ -1472,7 +1472,7 @@ static int enqueue_big_group(const ManyCall &mc, const std::vector<int> &g, int 
         first_rc = fail(COSIM_EDEVICE, "grouped contraction launch failed");
     if (first_rc != COSIM_OK) return first_rc;
     if (grad &&
-        big_group_solve(ga, NP, Sg, A, piv, kRhsPairs, gs) != hipSuccess) {
+        big_group_solve(bf, ga, NP, Sg, A, piv, kRhsPairs, gs) != hipSuccess) {
         return fail(COSIM_EDEVICE, "grouped adjoint launch failed");
     }
     ReduceGroup rg{};
@@ -1580,7 +1580,7 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
         }
     }
     // workspaces first (allocation, when growing, happens before anything is enqueued)
-    size_t nA = 0, nWt = 0, nTinv = 0, nPiv = 0, nSys = 0;
+    size_t nA = 0, nX = 0, nD = 0, nPiv = 0, nSys = 0;
     std::vector<int> chunks(count, 0), tpcs(count, 1);
     bool big_groups = false;
     for (const std::vector<int> &g : groups)
@@ -1595,12 +1595,12 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
             if (!big_plan((int)NP)) continue;  // its own factor record
             big_groups = true;
             nA += S * NP * NP;
-            nWt += S * 64 * NP;
-            nTinv += S * 64 * 64;
+            nX += S * 64 * NP;
+            nD += S * 2 * NP;
             nPiv += S * NP;
             nSys += S;
         }
-    if (big_groups && (rc = pool_group_ws(pool, nA, nWt, nTinv, nPiv, nSys))) return rc;
+    if (big_groups && (rc = pool_group_ws(pool, nA, nX, nD, nPiv, nSys))) return rc;
     if (!groups.empty() && (rc = pool_events(pool, groups.size() + count))) return rc;
     HIP_TRY(hipEventRecord(pool->start, st));
     for (int k = 0; k < ns; ++k) {

@@ -161,25 +161,21 @@ struct FusedGroup {
 hipError_t launch_fused_group(Prec prec, int NP, int loss_mode, bool grad, const FusedGroup &g,
                               int blocks, hipStream_t st);
 
-// ---- more than 64 loops: blocked LU with partial pivoting (solve_big.hip)
-// and GEMM-based contractions (contract_big.hip).
-// Right-hand side of launch_lu_solve.
+// ---- more than 64 loops: blocked LDL^T, or LU with partial pivoting
+// (solve_big.hip).
+// Right-hand side of big_solve.
 enum BigRhs {
     kRhsExcitation = 0,  // E - j w Phi (loop_voltage), writes I
-    kRhsPairs = 1,       // rpart[c][s][k] (rr, ri) FP64 pairs, writes gsys
-    kRhsPlanarF32 = 2,   // R[c] NP x 2S FP32 planes, writes gsys
-    kRhsPlanarF64 = 3    // R[c] NP x 2S FP64 planes, writes gsys
+    kRhsPairs = 1        // rpart[c][s][k] (rr, ri) FP64 pairs, writes gsys
 };
-hipError_t launch_lu_big(int NP, int n, int S, int F, const double *M_d, const double *R_d,
-                         const double *C_d, const double *omega_d, double2 *A_d, int *piv_d,
-                         int32_t *status_d, hipStream_t st);
 // Workspace of the blocked LDL^T above 64 loops (ldl: every R_k > 0).
 struct BigFactor {
     bool ldl = false;
     int *fmt = nullptr;       // [S] kFmtLDL / kFmtNeedsPivot
     double *zmax = nullptr;   // [S] largest |re| + |im| of a diagonal entry of Z
-    double2 *wt = nullptr;    // [S][64][NP] L21 of the current panel, column-major
-    double2 *tinv = nullptr;  // [S][64][64] L11^-T of the current panel
+    double2 *x = nullptr;     // [S][NP/64][64][64] L_bb^-T of the diagonal blocks (complex64
+                              // in half the space for the FP32 factor)
+    double2 *d = nullptr;     // [S][2][NP] D^-1, then L^-1 (E - j w Phi) (FP64 factor only)
 };
 // FP32 factorisation with FP64 iterative refinement (above 64 loops, every
 // R_k > 0): the blocked LDL^T runs on a complex64 record A32 [S][NP][NP].
@@ -193,12 +189,13 @@ struct BigRefine {
 // pivoted FP64 LU into A_d for the marked systems when bf.ldl, else pivoted
 // LU throughout.
 hipError_t big_factor(const BigFactor &bf, const BigRefine &rf, int NP, int n, int S, int F,
-                      const double *M_d, const double *R_d, const double *C_d,
-                      const double *omega_d, double2 *A_d, int *piv_d, int32_t *status_d,
-                      hipStream_t st);
-// Solves with the records big_factor left (arguments as launch_lu_solve): the
-// FP64 records directly; with refinement, the FP32 records refined in FP64
-// and FP64 fallbacks for the systems that do not converge.
+                      const double *M_d, const double *R_d, const double *phi_d,
+                      const double *C_d, const double *omega_d, double2 *A_d, int *piv_d,
+                      int32_t *status_d, hipStream_t st);
+// Solves with the records big_factor left (rhs_kind, rhs_d [nchunk][S][NP],
+// outputs I_d or gsys_d and mu_d): the FP64 records directly (the forward solve
+// with the excitation of the factorisation); with refinement, the FP32 records
+// refined in FP64 and FP64 fallbacks for the systems that do not converge.
 hipError_t big_solve(const BigFactor &bf, const BigRefine &rf, int NP, int n, int S, int F,
                      const double *M_d, const double *R_d, const double *phi_d, const double *C_d,
                      const double *omega_d, double2 *A_d, int *piv_d, double2 *I_d, int rhs_kind,
@@ -211,7 +208,7 @@ constexpr int kGroupMax = 32;
 struct GroupInst {
     const double *M, *R, *phi, *C, *omega;
     double2 *I;        // [S][n] currents
-    const void *rhs;   // adjoint sums, as for launch_lu_solve
+    const void *rhs;   // adjoint sums [nchunk][S][NP] (rr, ri)
     double *gsys;      // [S][n] adjoint gradient terms
     double2 *mu;       // [S][n] adjoint solutions or null
     int32_t *status;   // [S]
@@ -264,13 +261,8 @@ hipError_t launch_small_group(int NP, const SmallGroup &g, int S, SmallPhase pha
 hipError_t big_group_factor(const BigFactor &bf, const GroupArgs &g, int NP, int S,
                             double2 *A_d, int *piv_d, hipStream_t st);
 // Forward (kRhsExcitation, writes I) or adjoint solves of the group's systems.
-hipError_t big_group_solve(const GroupArgs &g, int NP, int S, const double2 *A_d,
-                           const int *piv_d, int rhs_kind, hipStream_t st);
-hipError_t launch_lu_solve(int NP, int n, int S, int F, const double2 *A_d, const int *piv_d,
-                           const double *phi_d, const double *C_d, const double *omega_d,
-                           double2 *I_d, int rhs_kind, const void *rhs_d, int nchunk,
-                           double rscale, double *gsys_d, int32_t *status_d, hipStream_t st,
-                           double2 *mu_d = nullptr);
+hipError_t big_group_solve(const BigFactor &bf, const GroupArgs &g, int NP, int S,
+                           const double2 *A_d, const int *piv_d, int rhs_kind, hipStream_t st);
 // ---- matrix-core contractions for any padded loop count (contract_mfma.hip):
 // the loss path above 64 loops, the materialised field and its vector-Jacobian
 // product for every plan.
@@ -482,8 +474,8 @@ struct cosim_plan {
     std::vector<hipEvent_t> events;
     int timing_cap = 0, timing_used = 0;
     // more than 64 loops: the blocked LDL^T and refinement workspace
-    double2 *bWt = nullptr;   // blocked LDL^T panel copy ([S][64][NP], see BigFactor)
-    double2 *bTinv = nullptr; // blocked LDL^T L11^-T ([S][64][64])
+    double2 *bX = nullptr;    // blocked LDL^T: L_bb^-T of the diagonal blocks ([S][64][NP], see BigFactor)
+    double2 *bD = nullptr;    // blocked LDL^T: D^-1 and the forward-substituted excitation ([S][2][NP])
     double *bZmax = nullptr;  // [S] largest diagonal |Z_kk| (blocked LDL^T)
     void *bA32 = nullptr;     // [S][NP][NP] complex64 records of the refined solves
     bool refine = false;      // FP32 factorisation + FP64 refinement (cosim_plan_set_refinement)

@@ -17,25 +17,23 @@
 //
 // When every R_k > 0 the impedance is complex symmetric with a positive
 // definite real part, and Z = L D L^T needs no row exchanges (as for the
-// smaller systems).  big_factor then runs a blocked LDL^T in panels of 64
-// columns, the matrix in HBM and only its lower triangle maintained:
-//   1. k_ldl_big_diag: the 64x64 diagonal block factored in LDS (one
-//      workgroup per system), written back as L11, D and U11 = D L11^T, with
-//      T = L11^-T for step 2;
-//   2.-3. k_ldl_big_panel: V21 = A21 T on FP64 matrix cores, then
-//      L21 = V21 D^-1 to the lower part, U12 = V21^T to the upper part, a
-//      copy of L21 for step 4;
-//   4. k_ldl_big_update: A22 -= L21 V21^T (= L21 D L21^T) on the tiles on and
-//      below the diagonal, FP64 matrix cores.
-// The upper triangle then holds U = D L^T, so with identity swaps the record
-// is an LU factor and k_lu_solve serves both.  Systems whose smallest pivot is
-// below 1e-5 of the largest |Z_kk| (or not finite), or whose input is invalid,
-// are marked and re-factored by k_lu_big with pivoting.
+// smaller systems).  big_factor then runs a blocked LDL^T in block rows of 64,
+// U = D L^T in the upper triangle of the slot:
+//   k_ldl_start: input flags and diagonal block 0;
+//   k_ldl_step, one launch per block row b: U_b,i = X_b (Z_b,i - the rows
+//   above) on matrix cores, X_b = L_bb^-1, and diagonal block b + 1;
+//   k_ldl_trail, after every kSuper block rows: their update of the trailing
+//   matrix.
+// The forward substitution rides along with the diagonal blocks, so that the
+// forward solve is one backward sweep (k_big_solve), the adjoint both sweeps.
+// Systems whose smallest pivot is below 1e-5 of the largest |Z_kk| (or not
+// finite), or whose input is invalid, are marked and re-factored by k_lu_big
+// with pivoting.
 //
-// With refinement on, steps 1-4 run on a complex64 copy of Z (diagonal block
-// still eliminated in FP64 in LDS; panel and trailing update on FP32 matrix
-// cores, half the bytes and twice the peak of FP64), and k_solve_refined
-// turns the FP32 factor F into FP64 solutions by iterative refinement:
+// With refinement on, the same kernels run on a complex64 record (diagonal
+// blocks in FP64; the tiles on FP32 matrix cores, half the bytes and twice the
+// peak of FP64), and k_solve_refined turns the FP32 factor F into FP64
+// solutions by iterative refinement:
 // x = F^-1 b, then r = b - Z x in FP64 (Z formed on the fly from M, R, C and
 // w; it is never stored in FP64) and x += F^-1 r until the next correction is
 // predicted below tol |x|.  A system that does not converge is re-factored in
@@ -317,439 +315,715 @@ __global__ __launch_bounds__(kTB) void k_lu_big(int NP, int S, Src src,
     if (tid == 0) r.status[r.s] = sFlag;
 }
 
-// Lower triangle of Z = diag(R) + j w M + diag(1/(j w C)) (identity padding),
-// grid (S, NP/16): workgroup y writes rows 16y .. 16y + 15; the one with
-// y = 0 also sets the input flags, fmt = kFmtLDL (kFmtNeedsPivot for invalid
-// input) and the largest |re| + |im| of a diagonal entry.
-template <typename T2, class Src>
-__global__ __launch_bounds__(kTB) void k_big_assemble(int NP, int S, Src src,
-                                                      T2 *__restrict__ Aall,
-                                                      int *__restrict__ fmt,
-                                                      double *__restrict__ zmax) {
-    __shared__ double sm[kTB / 64];
-    __shared__ int si[kTB / 64];
-    __shared__ int sFlag;
-    const int s = blockIdx.x;
-    if (s >= S) return;  // whole workgroup
-    const int tid = threadIdx.x;
-    T2 *A = Aall + (size_t)s * NP * NP;
-    const SysRef r = src.ref(s);
-    const int n = r.n;
-    const double w = r.w;
-    const double *__restrict__ M = r.M;
-    const double *__restrict__ Rv = r.R;
-    const double *__restrict__ Cb = r.Cb;
-    if (tid == 0) sFlag = 0;
-    __syncthreads();
-    double zm = 0.0;
-    const bool first = blockIdx.y == 0;
-    for (int k = tid; first && k < n; k += kTB) {
-        const double c = Cb[k];
-        if (isnan(c) || c == 0.0 || !isfinite(w) || w == 0.0) atomicOr(&sFlag, COSIM_SYS_BAD_INPUT);
-        else if (c < 0.0) atomicOr(&sFlag, COSIM_SYS_NEGATIVE_C);
-        zm = fmax(zm, fabs(Rv[k]) + fabs(w * M[(size_t)k * n + k] - 1.0 / (w * c)));
-    }
-    // row i, columns j <= i: lanes along j (coalesced), waves over rows
-    for (int i = 16 * blockIdx.y + (tid >> 6); i < 16 * blockIdx.y + 16; i += kTB / 64) {
-        for (int j = tid & 63; j <= i; j += 64) {
-            double zr = 0.0, zi = 0.0;
-            if (i < n && j < n) {
-                zi = w * M[(size_t)i * n + j];
-                if (i == j) {
-                    zr = Rv[i];
-                    zi -= 1.0 / (w * Cb[i]);
-                }
-            } else if (i == j) {
-                zr = 1.0;
-            }
-            A[(size_t)i * NP + j] = st2<T2>(make_double2(zr, zi));
+// Entry (i, j) of Z = diag(R) + j w M + diag(1/(j w C)), identity padding.
+__device__ inline double2 z_entry(const SysRef &r, int i, int j) {
+    if (i < r.n && j < r.n) {
+        double2 z = make_double2(0.0, r.w * r.M[(size_t)i * r.n + j]);
+        if (i == j) {
+            z.x = r.R[i];
+            z.y -= 1.0 / (r.w * r.Cb[i]);
         }
+        return z;
     }
-    if (!first) return;  // whole workgroup
-    int dummy = 0;
-    block_amax(zm, dummy, sm, si);  // max over the workgroup (index unused)
-    if (tid == 0) {
-        r.status[r.s] = sFlag;
-        fmt[s] = (sFlag & COSIM_SYS_BAD_INPUT) ? kFmtNeedsPivot : kFmtLDL;
-        zmax[s] = zm;
+    return make_double2(i == j ? 1.0 : 0.0, 0.0);
+}
+
+// 1/a of a pivot that is checked afterwards: hardware reciprocal and two
+// Newton steps (error at the rounding of the result, no division sequence).
+__device__ inline double2 zinv_nr(double2 a) {
+    const double q = fma(a.x, a.x, a.y * a.y);
+    double r = __builtin_amdgcn_rcp(q);
+    r = fma(r, fma(-q, r, 1.0), r);
+    r = fma(r, fma(-q, r, 1.0), r);
+    return make_double2(a.x * r, -a.y * r);
+}
+
+// ---- blocked LDL^T --------------------------------------------------------
+// Blocks of 64 rows, U = D L^T kept in the upper triangle of the system's
+// slot (row-major, row stride NP).  Per system beside it: X^T = L_bb^-T of
+// each diagonal block b ([NP/64][64][64]) and D^-1, y = L^-1 (E - j w Phi)
+// ([2][NP]).
+//
+// Block row b is U_b,i = X_b (Z_b,i - sum_j U_j,b^T D_j^-1 U_j,i).  The sum
+// runs over the rows of the current super-panel of kSuper blocks only; what
+// the super-panels before it contribute has been subtracted from the tile in
+// HBM by k_ldl_trail (a tile of the first super-panel is formed from M, R, C
+// and w and never stored).  Against an update of the whole trailing matrix
+// after every 64 columns this reads and writes it once per kSuper blocks.
+constexpr int kSuper = 4;
+
+// Entry k of the right-hand side less what the super-panels before block js
+// contribute: E - j w Phi, later the running value that k_ldl_trail keeps in
+// the place of y.
+__device__ inline double2 rhs_base(const SysRef &r, int k, int js, const double2 *y) {
+    if (js > 0) return y[k];
+    return k < r.n ? loop_voltage(r.phi, r.n, k, r.w) : make_double2(0.0, 0.0);
+}
+
+// Accumulates sum over rows j0 <= j < j1 (a multiple of 64 apart) of
+// u_ja d_j u_jb, d = D^-1, for NR pairs of 16-column blocks: pair q takes the
+// rows' entries at column ca[q] as the A operand and those at cb[q] (cb[0]
+// when NB == 1) times d_j as the B operand.  Lane l supplies row j + l / 16
+// of each step of 4 rows and column l % 16 of the block (in ca, cb), so both
+// operands are runs of 256 bytes.  The operands of two steps are loaded one
+// pair ahead into the other of two register sets.  sd[j - j0] = d_j; with Y
+// the lane also forms its share of sum_j (d_j u_jb) y_j for cb[0].
+template <typename T2, typename T, int NR, int NB, bool Y>
+__device__ __forceinline__ void acc_utu(const T2 *__restrict__ A, int NP, int j0, int j1,
+                                        const int (&ca)[NR], const int (&cb)[NB],
+                                        const double2 *sd, const double2 *sy, int g,
+                                        typename Acc4<T>::type (&Cr)[NR],
+                                        typename Acc4<T>::type (&Ci)[NR], double2 &yacc) {
+    T2 a0[2][NR], b0[2][NB], a1[2][NR], b1[2][NB];
+    auto load = [&](int j, T2 (&a)[2][NR], T2 (&b)[2][NB]) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const T2 *row = A + (size_t)(j + 4 * u + g) * NP;
+#pragma unroll
+            for (int q = 0; q < NR; ++q) a[u][q] = row[ca[q]];
+#pragma unroll
+            for (int t = 0; t < NB; ++t) b[u][t] = row[cb[t]];
+        }
+    };
+    auto mul = [&](int j, const T2 (&a)[2][NR], const T2 (&b)[2][NB]) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const double2 d = sd[j - j0 + 4 * u + g];
+            T br[NB], bi[NB];
+#pragma unroll
+            for (int t = 0; t < NB; ++t) {
+                const double2 v = zmul(ld2(b[u][t]), d);
+                if (Y && t == 0) yacc = zfma(yacc, v, sy[j - j0 + 4 * u + g]);
+                br[t] = (T)v.x;
+                bi[t] = (T)v.y;
+            }
+#pragma unroll
+            for (int q = 0; q < NR; ++q) {
+                const int t = NB == 1 ? 0 : q;
+                const T ar = (T)a[u][q].x, ai = (T)a[u][q].y;
+                Cr[q] = mfma4(ar, br[t], Cr[q]);
+                Ci[q] = mfma4(ar, bi[t], Ci[q]);
+                Cr[q] = mfma4(ai, -bi[t], Cr[q]);
+                Ci[q] = mfma4(ai, br[t], Ci[q]);
+            }
+        }
+    };
+    if (j0 >= j1) return;
+    load(j0, a0, b0);
+    for (int j = j0; j < j1; j += 16) {
+        load(j + 8, a1, b1);
+        mul(j, a0, b0);
+        load(min(j + 16, j1 - 8), a0, b0);  // the last pass loads rows again (unused)
+        mul(j + 8, a1, b1);
     }
 }
 
-// Step 1 of the blocked LDL^T: the diagonal block at k0 (lower triangle in
-// HBM) factored in LDS, V (= L D, unscaled) kept in place,
-//   a_rc2 -= v_r v_c2 / d_c  for c < c2 <= r,
-// in four sub-panels of 16 columns: column by column inside the sub-panel
-// (each step touches at most 15 columns), then the rest of the block at once,
-// 16 terms per entry with the thread's own row of the sub-panel in registers.
-// Then X = L11^-1 of the unit lower L = V D^-1 in 16x16 blocks: the diagonal
-// blocks column by column (64 independent substitutions of length 16), then
-// X_ij = -X_ii sum_(j <= k < i) L_ik X_kj block by block, for i - j = 1, 2, 3
-// (whole blocks at once, one entry per thread).
-// Written back: L_rc = v_rc / d_c below the diagonal, d_c on it, U_cr = v_rc
-// above it, identity swaps, and T = X^T = L11^-T ([64][64] per system) for
-// step 2; a pivot below 1e-5 zmax marks the system.  The arithmetic is FP64
-// for either storage type.
-template <typename T2>
-__global__ __launch_bounds__(kTB) void k_ldl_big_diag(int NP, int k0, int S,
-                                                      T2 *__restrict__ Aall,
-                                                      int *__restrict__ pivall,
-                                                      int *__restrict__ fmt,
-                                                      const double *__restrict__ zmax,
-                                                      T2 *__restrict__ tinv) {
-    __shared__ double2 sa[64][65];
-    __shared__ double2 sx[64][65];
-    const int s = blockIdx.x;
-    if (s >= S) return;  // whole workgroup
-    if (fmt[s] != kFmtLDL) return;  // invalid input: left to the pivoted LU
-    const int tid = threadIdx.x;
-    T2 *A = Aall + (size_t)s * NP * NP + (size_t)k0 * NP + k0;
-    for (int e = tid; e < 64 * 64; e += kTB) {
-        const int r = e >> 6, c = e & 63;
-        sa[r][c] = c <= r ? ld2(A[(size_t)r * NP + c]) : make_double2(0.0, 0.0);
-        sx[r][c] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+// LDS of one workgroup of k_ldl_step.
+struct LdlLds {
+    double2 sd[64 * kSuper];  // D^-1 of the super-panel's rows
+    double2 sy[64 * kSuper];  // y of the same rows
+    double2 sp[64][17];       // 16 columns of the diagonal block
+    double2 sx[16][17];       // inverse of their unit lower triangle
+    double2 sdv[16], sdi[16]; // their pivots and 1/pivots
+    double2 st[64];           // right-hand side of the block
+    double sm[kTB / 64];
+    int si[kTB / 64];
+    int flag;
+    double zm;
+};
+
+// L D L^T of the 16 x 16 symmetric block in rows p0 .. p0 + 15 of sp by one
+// wave, and X = L^-1.  Lane l holds columns 4 (l / 16) + u, u < 4, of row
+// l % 16, the whole symmetric block.  Step c subtracts l_r = a_rc / d_c times
+// row c from the rows below it; a column that has been eliminated holds the
+// matching column of X from then on (it starts as e_c), so each step costs
+// four complex multiply-adds per lane, with row c reaching the lanes as DPP
+// broadcasts inside the 16-lane rows and column c through one exchange.  A
+// serial chain of 16 steps; returns the smallest |re| + |im| of a pivot
+// (0 if one is NaN).
+template <int C>
+__device__ __forceinline__ double row_bcast(double x) {
+    // DPP row_newbcast: lane C of each row of 16
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x150 + C, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, 0x150 + C, 0xF, 0xF, false));
+}
+__device__ inline double lane_value(double x, int src) {  // src uniform over the wave
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
+                            __builtin_amdgcn_readlane(__double2loint(x), src));
+}
+template <int C>
+__device__ __forceinline__ void ldl16_step(double2 (&a)[4], double2 (&v)[4], double2 &dv, double2 &di,
+                                           double &dmin, int r, int q) {
+    constexpr int Q = C >> 2, U = C & 3;
+    const double2 d = make_double2(lane_value(a[U].x, 16 * Q + C), lane_value(a[U].y, 16 * Q + C));
+    const double2 col = make_double2(__shfl(a[U].x, 16 * Q + r), __shfl(a[U].y, 16 * Q + r));
+    const double2 inv = zinv_nr(d);
+    const double ad = fabs(d.x) + fabs(d.y);
+    dmin = ad == ad ? fmin(dmin, ad) : 0.0;
+    if (r == C) {
+        dv = d;
+        di = inv;
     }
-    __syncthreads();
-    const int rr = tid >> 2, q = tid & 3;  // four threads per row
-    __shared__ double2 sdi[64];          // D^-1
-    __shared__ double2 sw[3][16][17];
-    for (int c0 = 0; c0 < 64; c0 += 16) {
-        const int ce = c0 + 15;  // last column of the sub-panel
-        for (int c = c0; c < c0 + 16; ++c) {
-            if (rr > c) {
-                const double2 l = zmul(sa[rr][c], zinv(sa[c][c]));
-                const int hi = min(rr, ce);
-                for (int c2 = c + 1 + q; c2 <= hi; c2 += 4) sa[rr][c2] = zfms(sa[rr][c2], l, sa[c2][c]);
-            }
-            __syncthreads();
-        }
-        if (tid < 16) sdi[c0 + tid] = zinv(sa[c0 + tid][c0 + tid]);
-        __syncthreads();
-        if (c0 + 16 < 64 && rr >= c0 + 16) {
-            double2 w[16];  // row rr of the sub-panel, scaled by D^-1
+    const double2 l = r > C ? zmul(col, inv) : make_double2(0.0, 0.0);
 #pragma unroll
-            for (int m = 0; m < 16; ++m) w[m] = zmul(sa[rr][c0 + m], sdi[c0 + m]);
-            for (int c2 = c0 + 16 + q; c2 <= rr; c2 += 4) {
-                double2 acc = sa[rr][c2];
-#pragma unroll
-                for (int m = 0; m < 16; ++m) acc = zfms(acc, w[m], sa[c2][c0 + m]);
-                sa[rr][c2] = acc;
-            }
+    for (int u = 0; u < 4; ++u) {
+        const double2 row = make_double2(row_bcast<C>(a[u].x), row_bcast<C>(a[u].y));
+        if (u == U && q == Q) {
+            v[u] = a[u];
+            a[u] = make_double2(r == C ? 1.0 : -l.x, -l.y);
+        } else {
+            a[u] = zfms(a[u], l, row);
         }
-        __syncthreads();
     }
-    // X = L^-1, L_rc = v_rc / d_c (sx holds the identity, so the blocks above
-    // the diagonal stay zero)
-    if (tid < 64) {  // diagonal block j, column k
-        const int j = tid >> 4, k = tid & 15, b0 = 16 * j;
-        double2 x[16];
+    if constexpr (C + 1 < 16) ldl16_step<C + 1>(a, v, dv, di, dmin, r, q);
+}
+__device__ __forceinline__ double ldl16(LdlLds &m, int p0, int lane) {
+    const int r = lane & 15, q = lane >> 4;
+    double2 a[4], v[4], dv, di;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            double2 acc = make_double2(i == k ? 1.0 : 0.0, 0.0);
-#pragma unroll
-            for (int m = 0; m < i; ++m)
-                if (m >= k) acc = zfms(acc, zmul(sa[b0 + i][b0 + m], sdi[b0 + m]), x[m]);
-            x[i] = i < k ? make_double2(0.0, 0.0) : acc;
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) sx[b0 + i][b0 + k] = x[i];
-    }
-    __syncthreads();
-    for (int d = 1; d < 4; ++d) {
-        const int npair = 4 - d;  // blocks (j + d, j), j < npair
-        for (int e = tid; e < npair * 256; e += kTB) {  // W = sum_k L_ik X_kj
-            const int j = e >> 8, r = (e >> 4) & 15, c = e & 15, i = j + d;
-            double2 acc = make_double2(0.0, 0.0);
-            for (int kb = j; kb < i; ++kb)
-#pragma unroll 4
-                for (int m = 0; m < 16; ++m)
-                    acc = zfma(acc, zmul(sa[16 * i + r][16 * kb + m], sdi[16 * kb + m]),
-                               sx[16 * kb + m][16 * j + c]);
-            sw[j][r][c] = acc;
-        }
-        __syncthreads();
-        for (int e = tid; e < npair * 256; e += kTB) {  // X_ij = -X_ii W
-            const int j = e >> 8, r = (e >> 4) & 15, c = e & 15, i = j + d;
-            double2 acc = make_double2(0.0, 0.0);
-#pragma unroll 4
-            for (int m = 0; m < 16; ++m) acc = zfms(acc, sx[16 * i + r][16 * i + m], sw[j][m][c]);
-            sx[16 * i + r][16 * j + c] = acc;
-        }
-        __syncthreads();
-    }
-    T2 *T = tinv + (size_t)s * 64 * 64;
-    for (int e = tid; e < 64 * 64; e += kTB) T[e] = st2<T2>(sx[e & 63][e >> 6]);  // T[k][c] = X[c][k]
+    for (int u = 0; u < 4; ++u) a[u] = m.sp[p0 + r][4 * q + u];
     double dmin = __builtin_inf();
-    for (int e = tid; e < 64 * 64; e += kTB) {
-        const int r = e >> 6, c = e & 63;  // lower part and diagonal by rows
-        if (c < r) A[(size_t)r * NP + c] = st2<T2>(zmul(sa[r][c], zinv(sa[c][c])));
-        else if (c == r) {
-            const double2 d = sa[r][r];
-            A[(size_t)r * NP + r] = st2<T2>(d);
-            const double ad = fabs(d.x) + fabs(d.y);
-            dmin = ad == ad ? fmin(dmin, ad) : 0.0;  // a NaN pivot counts as zero
-        }
-        const int c2 = e >> 6, r2 = e & 63;  // upper part by rows: U_c2,r2 = v_r2,c2
-        if (r2 > c2) A[(size_t)c2 * NP + r2] = st2<T2>(sa[r2][c2]);
+    ldl16_step<0>(a, v, dv, di, dmin, r, q);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        m.sp[p0 + r][4 * q + u] = v[u];  // column c as it stood at its own step (rows above c unused)
+        m.sx[r][4 * q + u] = a[u];
     }
-    if (tid < 64) pivall[(size_t)s * NP + k0 + tid] = k0 + tid;
-    int dummy = 0;
-    double neg = -dmin;  // min via the arg-max helper
-    __shared__ double sm[kTB / 64];
-    __shared__ int si[kTB / 64];
-    block_amax(neg, dummy, sm, si);
-    if (tid == 0 && !(-neg >= 1e-5 * zmax[s])) fmt[s] = kFmtNeedsPivot;
+    if (lane < 16) {
+        m.sdv[lane] = dv;
+        m.sdi[lane] = di;
+    }
+    return dmin;
 }
 
-// Steps 2-3 for 64 rows i of the panel below the diagonal block, grid
-// (S, m/64): V21 = A21 T (T = L11^-T from step 1) on FP64 matrix cores, then
-// L21 = V21 D^-1 to the lower part, U12 = V21^T to the upper part and L21
-// again as column-major [64][NP] rows of wt (the A operand of step 4).  The
-// rows of A21 are staged in LDS (rows padded to 65 entries); each wave forms
-// a 32x32 quarter as 2x2 blocks of 16x16 (the layout of k_ldl_big_update,
-// with the contraction index k = 16 g + ks); V goes back through the same
-// LDS tile so that every HBM write is a run of consecutive entries.
-template <typename T2>
-__global__ __launch_bounds__(kTB) void k_ldl_big_panel(int NP, int k0, int S,
-                                                       const int *__restrict__ fmt,
-                                                       T2 *__restrict__ Aall,
-                                                       const T2 *__restrict__ tinv,
-                                                       T2 *__restrict__ wt) {
-    typedef typename Scal<T2>::type T;
-    typedef typename Acc4<T>::type V4;
-    __shared__ T2 sv[64][65];
-    __shared__ double2 dinv[64];
-    const int s = blockIdx.x;
-    if (s >= S) return;  // whole workgroup
-    if (fmt[s] != kFmtLDL) return;
-    const int tid = threadIdx.x;
-    T2 *A = Aall + (size_t)s * NP * NP;
-    const int i0 = k0 + 64 + 64 * blockIdx.y;  // first row of this block
-    if (tid < 64) dinv[tid] = zinv(ld2(A[(size_t)(k0 + tid) * NP + k0 + tid]));
-    for (int e = tid; e < 64 * 64; e += kTB) {
-        const int r = e >> 6, c = e & 63;
-        sv[r][c] = A[(size_t)(i0 + r) * NP + k0 + c];
-    }
-    __syncthreads();
-    const int lane = tid & 63, wv = tid >> 6;
-    const int g = lane >> 4, r16 = lane & 15;
-    const int wr = 32 * (wv >> 1), wc = 32 * (wv & 1);
-    const T2 *Tm = tinv + (size_t)s * 64 * 64 + (size_t)(16 * g) * 64 + wc + r16;
-    V4 Vr[2][2], Vi[2][2];
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            Vr[bi][bj] = V4{0, 0, 0, 0};
-            Vi[bi][bj] = V4{0, 0, 0, 0};
-        }
-    auto step = [&](int ks, const T2 (&t)[2]) {
-        T2 a[2];
-#pragma unroll
-        for (int b2 = 0; b2 < 2; ++b2) a[b2] = sv[wr + 16 * b2 + r16][16 * g + ks];
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 2; ++bj) {
-                Vr[bi][bj] = mfma4(a[bi].x, t[bj].x, Vr[bi][bj]);
-                Vr[bi][bj] = mfma4(-a[bi].y, t[bj].y, Vr[bi][bj]);
-                Vi[bi][bj] = mfma4(a[bi].x, t[bj].y, Vi[bi][bj]);
-                Vi[bi][bj] = mfma4(a[bi].y, t[bj].x, Vi[bi][bj]);
-            }
-    };
-    if constexpr (sizeof(T) == 8) {
-        // FP64: the T operands of two steps loaded one pair ahead into the
-        // other of two register sets (unrolled: the sets alternate in place)
-        T2 t0[2][2], t1[2][2];
-        auto load = [&](int ks, T2 (&t)[2][2]) {
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int b2 = 0; b2 < 2; ++b2) t[u][b2] = Tm[(ks + u) * 64 + 16 * b2];
-        };
-        load(0, t0);
-#pragma unroll
-        for (int ks = 0; ks < 16; ks += 4) {
-            load(ks + 2, t1);
-            step(ks, t0[0]);
-            step(ks + 1, t0[1]);
-            if (ks + 4 < 16) load(ks + 4, t0);
-            step(ks + 2, t1[0]);
-            step(ks + 3, t1[1]);
-        }
-    } else {
-#pragma unroll 4
-        for (int ks = 0; ks < 16; ++ks) {
-            T2 t[2];
-#pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) t[b2] = Tm[ks * 64 + 16 * b2];
-            step(ks, t);
-        }
-    }
-    __syncthreads();  // every wave is done reading A21
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                T2 v;
-                v.x = Vr[bi][bj][m];
-                v.y = Vi[bi][bj][m];
-                sv[wr + 16 * bi + acc_row<T>(g, m)][wc + 16 * bj + r16] = v;
-            }
-    __syncthreads();
-    T2 *W = wt + (size_t)s * 64 * NP;
-    for (int e = tid; e < 64 * 64; e += kTB) {
-        const int r = e >> 6, c = e & 63;
-        A[(size_t)(i0 + r) * NP + k0 + c] = st2<T2>(zmul(ld2(sv[r][c]), dinv[c]));
-        const int c2 = e >> 6, r2 = e & 63;  // transposed: consecutive threads along rows
-        A[(size_t)(k0 + c2) * NP + i0 + r2] = sv[r2][c2];
-        W[(size_t)c2 * NP + (i0 - k0 - 64) + r2] = st2<T2>(zmul(ld2(sv[r2][c2]), dinv[c2]));
-    }
-}
+// The 16-column blocks of a 64 x 64 diagonal block that wave w holds as
+// (row block, column block) accumulators; every pair below or on the diagonal
+// appears once, wave 1's three in transposed form, so that each wave has at
+// most three products and two distinct column blocks.
+__device__ inline int diag_rb(int w, int q) { return w == 3 ? 2 + q : (w == 2 ? 1 + q : q); }
+__device__ inline int diag_cb(int w, int q) { return w == 3 ? 2 + q : (w == 2 ? 1 : (w == 1 ? 3 : 0)); }
 
-// Step 4: A22 -= L21 V21^T on the 64x64 tiles of the trailing matrix on or
-// below the diagonal (a diagonal tile is updated in full; its part above the
-// diagonal is never read), nt(nt+1)/2 = T tiles per system, tile
-// t = ti(ti+1)/2 + tj.  One-dimensional grid of 8 ceil(S/8) T workgroups,
-// mapped so that every tile of a system runs on one XCD and the tiles of a
-// system are consecutive there (workgroups are dealt to the 8 XCDs round
-// robin): workgroup id -> XCD x = id % 8, its k = id / 8-th workgroup on that
-// XCD takes tile k % T of system 8 (k / T) + x.  The L21 and V21 panels of
-// the few systems in flight on an XCD then stay in its L2 across their tiles.
-// Each wave takes a 32x32 quarter as 2x2 FP64 MFMA blocks of 16x16 (real and
-// imaginary accumulators; lane l holds column l%16, rows g + 4m, g = l/16).
-// Panel column c enters as MFMA step ks = c % 16 of lane group g = c / 16 for
-// both operands, so each lane's operand is one 16-byte load and the 16 lanes
-// of a group read 256 consecutive bytes: the A operand from wt (rows of
-// L21^T), the B operand from U12 (rows of V21^T).
-template <typename T2>
-__global__ __launch_bounds__(kTB) void k_ldl_big_update(int NP, int k0, int S,
-                                                        const int *__restrict__ fmt,
-                                                        T2 *__restrict__ Aall,
-                                                        const T2 *__restrict__ wt, int T) {
-    typedef typename Scal<T2>::type Ts;
-    typedef typename Acc4<Ts>::type V4;
-    const int kx = blockIdx.x >> 3;
-    const int s = 8 * (kx / T) + (blockIdx.x & 7);
-    if (s >= S) return;  // whole workgroup
-    if (fmt[s] != kFmtLDL) return;
-    const int t = kx % T;
-    int ti = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-    while ((ti + 1) * (ti + 2) / 2 <= t) ++ti;
-    while (ti * (ti + 1) / 2 > t) --ti;
-    const int tj = t - ti * (ti + 1) / 2;
-    const int base = k0 + 64;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+// Diagonal block ib: Z_ii - sum over the super-panel's rows [64 js, 64 ib) of
+// u d u^T, its L D L^T and X = L^-1, in 16-column sub-panels p:
+//   1. the waves put their accumulators of block column p into sp;
+//   2. wave 0 factors the 16 x 16 block (ldl16);
+//   3. V_rp = A_rp X_pp^T, one row block per wave;
+//   4. A_rc -= V_rp D^-1 V_cp^T on the accumulators still to come, and the
+//      rows below of the inverse, Y_rj -= L_rp X_pj with X_pj = X_pp Y_pj: a
+//      wave owns a block column j of the inverse, whose accumulators are in
+//      the layout of the B operand of both products.
+// Everything but the pivots' chain runs on FP64 matrix cores, also for
+// complex64 storage.  Bounded by the chain of 64 pivots and 16 barriers: the
+// first block of 8 systems takes 37 us with its input checks, where the whole
+// block eliminated in LDS with 80 barriers took 54.
+template <typename T2, class Src>
+__device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, int js, T2 *__restrict__ A,
+                                         T2 *__restrict__ XT, double2 *__restrict__ D,
+                                         int *__restrict__ fmt, double zmax, LdlLds &m) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane >> 4, r16 = lane & 15;
-    const int wi = base + 64 * ti + 32 * (wv >> 1);  // first row of this wave's quarter
-    const int wj = base + 64 * tj + 32 * (wv & 1);   // first column
-    T2 *A = Aall + (size_t)s * NP * NP;
-    // lane's operand streams: L21[wi + 16 bi + r16][16 g + ks] and V21[wj + 16 bj + r16][16 g + ks]
-    const T2 *La = wt + (size_t)s * 64 * NP + (size_t)(16 * g) * NP + (wi - base) + r16;
-    const T2 *Vb = A + (size_t)(k0 + 16 * g) * NP + wj + r16;
-    V4 Cr[2][2], Ci[2][2];
+    const int k0 = 64 * ib, j0 = 64 * js;
+    const SysRef sys = src.ref(s);
+    f64x4 Cr[3], Ci[3], Yr[3], Yi[3];
 #pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            Cr[bi][bj] = V4{0, 0, 0, 0};
-            Ci[bi][bj] = V4{0, 0, 0, 0};
-        }
-    // FP64: operands of two steps at a time, loaded one pair of steps ahead
-    // into the other of two register sets (the loop is unrolled, so the sets
-    // alternate without copies); the tile's current values are loaded before
-    // the last pair of steps, so that the epilogue does not wait for them
-    auto load = [&](int ks, T2 (&l)[2][2], T2 (&v)[2][2]) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                l[u][b2] = La[(size_t)(ks + u) * NP + 16 * b2];
-                v[u][b2] = Vb[(size_t)(ks + u) * NP + 16 * b2];
+    for (int q = 0; q < 3; ++q) Cr[q] = Ci[q] = Yr[q] = Yi[q] = f64x4{0, 0, 0, 0};
+    double2 yacc = make_double2(0.0, 0.0);
+    constexpr bool kY = sizeof(T2) == sizeof(double2);
+    {
+        const int nq = wv < 2 ? 3 : 2;
+        if (wv < 2) {
+            const int ca[3] = {k0 + r16, k0 + 16 + r16, k0 + 32 + r16};
+            const int cb[1] = {k0 + (wv == 1 ? 48 : 0) + r16};
+            acc_utu<T2, double, 3, 1, kY>(A, NP, j0, k0, ca, cb, m.sd, m.sy, g, Cr, Ci, yacc);
+        } else {
+            f64x4 cr[2] = {Cr[0], Cr[0]}, ci[2] = {Cr[0], Cr[0]};
+            if (wv == 2) {
+                const int ca[2] = {k0 + 16 + r16, k0 + 32 + r16};
+                const int cb[1] = {k0 + 16 + r16};
+                acc_utu<T2, double, 2, 1, kY>(A, NP, j0, k0, ca, cb, m.sd, m.sy, g, cr, ci, yacc);
+            } else {
+                const int ca[2] = {k0 + 32 + r16, k0 + 48 + r16};
+                acc_utu<T2, double, 2, 2, kY>(A, NP, j0, k0, ca, ca, m.sd, m.sy, g, cr, ci, yacc);
             }
-    };
-    auto steps = [&](const T2 (&l)[2][2], const T2 (&v)[2][2]) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+            for (int q = 0; q < 2; ++q) {
+                Cr[q] = cr[q];
+                Ci[q] = ci[q];
+            }
+        }
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
+        for (int q = 0; q < 3; ++q) {
+            if (q >= nq) continue;
+            const int row = k0 + 16 * diag_rb(wv, q) + g, col = k0 + 16 * diag_cb(wv, q) + r16;
 #pragma unroll
-                for (int bj = 0; bj < 2; ++bj) {
-                    // (lr + j li)(vr + j vi): re = lr vr - li vi, im = lr vi + li vr
-                    Cr[bi][bj] = mfma4(l[u][bi].x, v[u][bj].x, Cr[bi][bj]);
-                    Cr[bi][bj] = mfma4(-l[u][bi].y, v[u][bj].y, Cr[bi][bj]);
-                    Ci[bi][bj] = mfma4(l[u][bi].x, v[u][bj].y, Ci[bi][bj]);
-                    Ci[bi][bj] = mfma4(l[u][bi].y, v[u][bj].x, Ci[bi][bj]);
+            for (int e = 0; e < 4; ++e) {
+                const double2 z = js == 0 ? z_entry(sys, row + 4 * e, col)
+                                          : ld2(A[(size_t)(row + 4 * e) * NP + col]);
+                Cr[q][e] = z.x - Cr[q][e];
+                Ci[q][e] = z.y - Ci[q][e];
+            }
+        }
+    }
+    if (kY) {  // st = E - j w Phi - L y (the columns of this wave's first B operand)
+        yacc.x += __shfl_xor(yacc.x, 16);
+        yacc.y += __shfl_xor(yacc.y, 16);
+        yacc.x += __shfl_xor(yacc.x, 32);
+        yacc.y += __shfl_xor(yacc.y, 32);
+        if (lane < 16) {
+            const int c = 16 * diag_cb(wv, 0) + r16;
+            const double2 b = rhs_base(sys, k0 + c, js, D + NP);
+            m.st[c] = make_double2(b.x - yacc.x, b.y - yacc.y);
+        }
+    }
+    T2 *X = XT + (size_t)ib * 64 * 64;
+    const int yj = wv == 0 ? 0 : (wv == 2 ? 1 : (wv == 1 ? 2 : 3));  // block column of the inverse
+    double dmin = __builtin_inf();
+    for (int p = 0; p < 4; ++p) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (q >= (wv < 2 ? 3 : 2)) continue;
+            const int rb = diag_rb(wv, q), cb = diag_cb(wv, q);
+            if (min(rb, cb) != p) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double2 v = make_double2(Cr[q][e], Ci[q][e]);
+                if (rb >= cb) m.sp[16 * rb + g + 4 * e][r16] = v;
+                else m.sp[16 * cb + r16][g + 4 * e] = v;
+            }
+        }
+        __syncthreads();
+        if (wv == 0) dmin = fmin(dmin, ldl16(m, 16 * p, lane));
+        __syncthreads();
+        if (wv > p) {  // V of row block wv
+            f64x4 vr = f64x4{0, 0, 0, 0}, vi = vr;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double2 a = m.sp[16 * wv + r16][4 * e + g], b = m.sx[r16][4 * e + g];
+                vr = mfma4(a.x, b.x, vr);
+                vi = mfma4(a.x, b.y, vi);
+                vr = mfma4(a.y, -b.y, vr);
+                vi = mfma4(a.y, b.x, vi);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m.sp[16 * wv + g + 4 * e][r16] = make_double2(vr[e], vi[e]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            if (q >= (wv < 2 ? 3 : 2)) continue;
+            const int rb = diag_rb(wv, q), cb = diag_cb(wv, q);
+            if (min(rb, cb) <= p) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double2 a = m.sp[16 * rb + r16][4 * e + g];
+                const double2 b = zmul(m.sp[16 * cb + r16][4 * e + g], m.sdi[4 * e + g]);
+                Cr[q] = mfma4(a.x, -b.x, Cr[q]);
+                Ci[q] = mfma4(a.x, -b.y, Ci[q]);
+                Cr[q] = mfma4(a.y, b.y, Cr[q]);
+                Ci[q] = mfma4(a.y, -b.x, Ci[q]);
+            }
+        }
+        if (yj <= p) {
+            f64x4 xr = f64x4{0, 0, 0, 0}, xi = xr;
+            if (yj == p) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double2 v = m.sx[g + 4 * e][r16];
+                    xr[e] = v.x;
+                    xi[e] = v.y;
                 }
-    };
-    auto cell = [&](int bi, int bj, int m) {
-        return A + (size_t)(wi + 16 * bi + acc_row<Ts>(g, m)) * NP + wj + 16 * bj + r16;
-    };
-    if constexpr (sizeof(Ts) == 8) {
-        T2 l0[2][2], v0[2][2], l1[2][2], v1[2][2], c[2][2][4];
-        load(0, l0, v0);
-#pragma unroll
-        for (int ks = 0; ks < 16; ks += 4) {
-            load(ks + 2, l1, v1);
-            steps(l0, v0);
-            if (ks + 4 < 16) {
-                load(ks + 4, l0, v0);
             } else {
 #pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
+                for (int t = 0; t < 3; ++t) {
+                    if (t + 1 != p) continue;
 #pragma unroll
-                    for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) c[bi][bj][m] = *cell(bi, bj, m);
-            }
-            steps(l1, v1);
-        }
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    T2 a = c[bi][bj][m];
-                    a.x -= Cr[bi][bj][m];
-                    a.y -= Ci[bi][bj][m];
-                    *cell(bi, bj, m) = a;
+                    for (int e = 0; e < 4; ++e) {
+                        const double2 a = m.sx[r16][4 * e + g];
+                        xr = mfma4(a.x, Yr[t][e], xr);
+                        xi = mfma4(a.x, Yi[t][e], xi);
+                        xr = mfma4(a.y, -Yi[t][e], xr);
+                        xi = mfma4(a.y, Yr[t][e], xi);
+                    }
                 }
-    } else {
-        // FP32: the operands of four steps loaded as they come, the tile read
-        // in the epilogue (more resident waves do the hiding: the prefetching
-        // form holds five instead of six and runs 3% slower)
-#pragma unroll 4
-        for (int ks = 0; ks < 16; ++ks) {
-            T2 l[2], v[2];
-#pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                l[b2] = La[(size_t)ks * NP + 16 * b2];
-                v[b2] = Vb[(size_t)ks * NP + 16 * b2];
             }
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
+            for (int t = 0; t < 3; ++t) {  // row block t + 1
+                if (t + 1 <= p) continue;
 #pragma unroll
-                for (int bj = 0; bj < 2; ++bj) {
-                    Cr[bi][bj] = mfma4(l[bi].x, v[bj].x, Cr[bi][bj]);
-                    Cr[bi][bj] = mfma4(-l[bi].y, v[bj].y, Cr[bi][bj]);
-                    Ci[bi][bj] = mfma4(l[bi].x, v[bj].y, Ci[bi][bj]);
-                    Ci[bi][bj] = mfma4(l[bi].y, v[bj].x, Ci[bi][bj]);
+                for (int e = 0; e < 4; ++e) {
+                    const double2 a = zmul(m.sp[16 * (t + 1) + r16][4 * e + g], m.sdi[4 * e + g]);
+                    Yr[t] = mfma4(a.x, -xr[e], Yr[t]);
+                    Yi[t] = mfma4(a.x, -xi[e], Yi[t]);
+                    Yr[t] = mfma4(a.y, xi[e], Yr[t]);
+                    Yi[t] = mfma4(a.y, -xr[e], Yi[t]);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                X[(16 * yj + r16) * 64 + 16 * p + g + 4 * e] = st2<T2>(make_double2(xr[e], xi[e]));
+        }
+        {  // rows 16 p .. 16 p + 15 of U in this block, and D^-1
+            const int c = tid >> 4;
+            for (int rr = 16 * p + (tid & 15); rr < 64; rr += 16) {
+                if (rr < 16 * p + c) continue;
+                const double2 v = rr == 16 * p + c ? m.sdv[c] : m.sp[rr][c];
+                A[(size_t)(k0 + 16 * p + c) * NP + k0 + rr] = st2<T2>(v);
+            }
+            if (tid < 16) D[k0 + 16 * p + tid] = m.sdi[tid];
+        }
+        __syncthreads();
+    }
+    if (kY) {  // y = X st (X^T rows just written by this workgroup)
+        double2 *red = &m.sp[0][0];
+        const int rr = tid & 63, part = tid >> 6;
+        double2 acc = make_double2(0.0, 0.0);
+        if (part <= (rr >> 4))
+            for (int c = 16 * part; c < 16 * part + 16; ++c) acc = zfma(acc, ld2(X[c * 64 + rr]), m.st[c]);
+        red[part * 64 + rr] = acc;
+        __syncthreads();
+        if (tid < 64) {
+            double2 y = red[tid];
+            for (int e = 1; e < 4; ++e) {
+                y.x += red[64 * e + tid].x;
+                y.y += red[64 * e + tid].y;
+            }
+            D[NP + k0 + tid] = y;
+        }
+    }
+    if (tid == 0 && !(dmin >= 1e-5 * zmax)) fmt[s] = kFmtNeedsPivot;
+}
+
+// Workgroups of a system consecutive on one XCD (workgroups are dealt to the
+// 8 XCDs round robin): id -> system 8 (k / T) + id % 8, item k % T, k = id / 8.
+// The rows of U that a system's tiles share then stay in that XCD's L2.
+__device__ inline int xcd_system(int id, int T, int *item) {
+    const int k = id >> 3;
+    *item = k % T;
+    return 8 * (k / T) + (id & 7);
+}
+
+// The first step: input flags, the largest diagonal |Z_kk|, diagonal block 0.
+template <typename T2, class Src>
+__global__ __launch_bounds__(kTB, 2) void k_ldl_start(int NP, int S, Src src, T2 *__restrict__ Aall,
+                                                      T2 *__restrict__ Xall, double2 *__restrict__ Dall,
+                                                      int *__restrict__ fmt, double *__restrict__ zmax) {
+    __shared__ LdlLds m;
+    const int s = blockIdx.x, tid = threadIdx.x;
+    if (s >= S) return;  // whole workgroup
+    const SysRef r = src.ref(s);
+    if (tid == 0) m.flag = 0;
+    __syncthreads();
+    double zm = 0.0;
+    for (int k = tid; k < r.n; k += kTB) {
+        const double c = r.Cb[k];
+        if (isnan(c) || c == 0.0 || !isfinite(r.w) || r.w == 0.0) atomicOr(&m.flag, COSIM_SYS_BAD_INPUT);
+        else if (c < 0.0) atomicOr(&m.flag, COSIM_SYS_NEGATIVE_C);
+        zm = fmax(zm, fabs(r.R[k]) + fabs(r.w * r.M[(size_t)k * r.n + k] - 1.0 / (r.w * c)));
+    }
+    int dummy = 0;
+    block_amax(zm, dummy, m.sm, m.si);  // max over the workgroup (index unused)
+    const int flag = m.flag;
+    const bool bad = (flag & COSIM_SYS_BAD_INPUT) != 0;
+    if (tid == 0) {
+        r.status[r.s] = flag;
+        fmt[s] = bad ? kFmtNeedsPivot : kFmtLDL;
+        zmax[s] = zm;
+    }
+    if (bad) return;  // whole workgroup: left to the pivoted LU
+    ldl_diag(NP, s, src, 0, 0, Aall + (size_t)s * NP * NP, Xall + (size_t)s * 64 * NP,
+             Dall + (size_t)s * 2 * NP, fmt, zm, m);
+}
+
+// A 64 x 64 tile of the trailing matrix as accumulators: each wave holds 64
+// rows of its 16 columns, so that block row b's product with X_b takes them
+// as the B operand where they are.  base + rows (and yacc) as in acc_utu.
+template <typename T2, bool Y>
+__device__ __forceinline__ void ldl_tile(int NP, const SysRef &sys, int rb, int cbk, int js, int j1,
+                                         const T2 *__restrict__ A, const double2 *sd,
+                                         const double2 *sy, double2 &yacc, int g, int r16, int wv, typename Acc4<typename Scal<T2>::type>::type (&Cr)[4],
+                                         typename Acc4<typename Scal<T2>::type>::type (&Ci)[4]) {
+    typedef typename Scal<T2>::type T;
+    typedef typename Acc4<T>::type V4;
+    const int col = 64 * cbk + 16 * wv + r16;
+    int ca[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        ca[q] = 64 * rb + 16 * q + r16;
+        Cr[q] = Ci[q] = V4{0, 0, 0, 0};
+    }
+    const int cb[1] = {col};
+    acc_utu<T2, T, 4, 1, Y>(A, NP, 64 * js, j1, ca, cb, sd, sy, g, Cr, Ci, yacc);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int row = 64 * rb + 16 * q + acc_row<T>(g, e);
+            const double2 z = js == 0 ? z_entry(sys, row, col) : ld2(A[(size_t)row * NP + col]);
+            Cr[q][e] = (T)z.x - Cr[q][e];
+            Ci[q][e] = (T)z.y - Ci[q][e];
+        }
+}
+
+// Block row kb: workgroup t of a system forms U_kb,i of block column
+// i = kb + 1 + t; the one with t = 0 goes on to diagonal block kb + 1 (its
+// last operand), whose X the next launch needs, so that a step is one launch
+// and the factorisation of the diagonal block runs beside the other tiles.
+// FP64 matrix-core issue bounds it for many systems, the chain of the t = 0
+// workgroup for few.  Factorisation of 256 systems of 1,024 loops (all steps):
+// 8.2 ms where separate assembly, diagonal, panel and update launches after
+// every 64 columns took 11.6; of 160 of 256 loops 0.30 ms, 0.43 before.
+template <typename T2, class Src>
+__global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int kb, int js, int T,
+                                                     T2 *__restrict__ Aall, T2 *__restrict__ Xall,
+                                                     double2 *__restrict__ Dall, int *__restrict__ fmt,
+                                                     const double *__restrict__ zmax) {
+    typedef typename Scal<T2>::type Ts;
+    typedef typename Acc4<Ts>::type V4;
+    __shared__ LdlLds m;
+    int t;
+    const int s = xcd_system(blockIdx.x, T, &t);
+    if (s >= S) return;  // whole workgroup
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int g = lane >> 4, r16 = lane & 15;
+    if (tid == 0) m.flag = fmt[s];  // one read: the t = 0 workgroup may be marking the system
+    __syncthreads();
+    if (m.flag != kFmtLDL) return;  // whole workgroup
+    const int ib = kb + 1 + t;
+    T2 *A = Aall + (size_t)s * NP * NP;
+    T2 *XT = Xall + (size_t)s * 64 * NP;
+    double2 *D = Dall + (size_t)s * 2 * NP;
+    for (int j = tid; j < 64 * (kb + 1 - js); j += kTB) {
+        m.sd[j] = D[64 * js + j];
+        if (t == 0) m.sy[j] = D[NP + 64 * js + j];
+    }
+    __syncthreads();
+    {
+        const SysRef sys = src.ref(s);
+        V4 Cr[4], Ci[4], Ur[4], Ui[4];
+        double2 none = make_double2(0.0, 0.0);
+        ldl_tile<T2, false>(NP, sys, kb, ib, js, 64 * kb, A, m.sd, nullptr, none, g, r16, wv, Cr, Ci);
+        const T2 *X = XT + (size_t)kb * 64 * 64;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) {
+            Ur[rb] = Ui[rb] = V4{0, 0, 0, 0};
+#pragma unroll
+            for (int cb = 0; cb <= rb; ++cb)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const T2 x = X[(16 * cb + acc_row<Ts>(g, e)) * 64 + 16 * rb + r16];
+                    Ur[rb] = mfma4(x.x, Cr[cb][e], Ur[rb]);
+                    Ui[rb] = mfma4(x.x, Ci[cb][e], Ui[rb]);
+                    Ur[rb] = mfma4(-x.y, Ci[cb][e], Ur[rb]);
+                    Ui[rb] = mfma4(x.y, Cr[cb][e], Ui[rb]);
                 }
         }
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+        for (int rb = 0; rb < 4; ++rb)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
+            for (int e = 0; e < 4; ++e) {
+                T2 u;
+                u.x = Ur[rb][e];
+                u.y = Ui[rb][e];
+                A[(size_t)(64 * kb + 16 * rb + acc_row<Ts>(g, e)) * NP + 64 * ib + 16 * wv + r16] = u;
+            }
+    }
+    if (t != 0) return;  // whole workgroup
+    __syncthreads();     // the rows of block kb are operands of the diagonal block
+    ldl_diag(NP, s, src, ib, js, A, XT, D, fmt, zmax[s], m);
+}
+
+// After the super-panel of blocks js .. ns - 1: its rows subtracted from the
+// tiles (r, c), ns <= r <= c, of the trailing matrix (all but the first
+// diagonal tile, which the last step has taken care of), and from the
+// right-hand side of the rows of the diagonal tiles.
+template <typename T2, class Src>
+__global__ __launch_bounds__(kTB, 2) void k_ldl_trail(int NP, int S, Src src, int js, int ns, int T,
+                                                      T2 *__restrict__ Aall,
+                                                      double2 *__restrict__ Dall,
+                                                      const int *__restrict__ fmt) {
+    typedef typename Scal<T2>::type Ts;
+    typedef typename Acc4<Ts>::type V4;
+    constexpr bool kY = sizeof(T2) == sizeof(double2);
+    __shared__ double2 sd[64 * kSuper], sy[64 * kSuper];
+    int t;
+    const int s = xcd_system(blockIdx.x, T, &t);
+    if (s >= S) return;  // whole workgroup
+    if (fmt[s] != kFmtLDL) return;
+    ++t;
+    int tc = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+    while ((tc + 1) * (tc + 2) / 2 <= t) ++tc;
+    while (tc * (tc + 1) / 2 > t) --tc;
+    const int rb = ns + t - tc * (tc + 1) / 2, cb = ns + tc;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int g = lane >> 4, r16 = lane & 15;
+    T2 *A = Aall + (size_t)s * NP * NP;
+    double2 *D = Dall + (size_t)s * 2 * NP;
+    for (int j = tid; j < 64 * (ns - js); j += kTB) {
+        sd[j] = D[64 * js + j];
+        if (kY) sy[j] = D[NP + 64 * js + j];
+    }
+    __syncthreads();
+    const SysRef sys = src.ref(s);
+    V4 Cr[4], Ci[4];
+    double2 yacc = make_double2(0.0, 0.0);
+    ldl_tile<T2, kY>(NP, sys, rb, cb, js, 64 * ns, A, sd, sy, yacc, g, r16, wv, Cr, Ci);
+    if (kY && rb == cb) {
+        yacc.x += __shfl_xor(yacc.x, 16);
+        yacc.y += __shfl_xor(yacc.y, 16);
+        yacc.x += __shfl_xor(yacc.x, 32);
+        yacc.y += __shfl_xor(yacc.y, 32);
+        if (lane < 16) {
+            const int k = 64 * cb + 16 * wv + r16;
+            const double2 b = rhs_base(sys, k, js, D + NP);
+            D[NP + k] = make_double2(b.x - yacc.x, b.y - yacc.y);
+        }
+    }
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    T2 *cp = cell(bi, bj, m);
-                    T2 a = *cp;
-                    a.x -= Cr[bi][bj][m];
-                    a.y -= Ci[bi][bj][m];
-                    *cp = a;
-                }
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            T2 u;
+            u.x = Cr[q][e];
+            u.y = Ci[q][e];
+            A[(size_t)(64 * rb + 16 * q + acc_row<Ts>(g, e)) * NP + 64 * cb + 16 * wv + r16] = u;
+        }
+}
+
+// sx <- Z^-1 sx from the U, X, D^-1 record of one system (FWD: the sweep with
+// L = U^T D^-1; BWD: the one with U), the vector in LDS, the kTS threads of the
+// workgroup taking part, in blocks of 64 rows.  Forward: y_b = X_b t_b, then
+// the rows of U_b times D^-1 y_b are taken off the rest of the vector, each
+// wave 64 columns (fewer columns than waves: the 64 rows split over up to 16
+// groups).  Backward: rows 4 w .. 4 w + 3 of the block against the solved
+// entries per wave, x_b = X_b^T D^-1 (y_b - .).  Rows and X are loaded before
+// the value they multiply is ready.  sred: kTS entries, sv: 64 entries of LDS.
+//   Latency of the blocks bounds it for small NP (8 systems of 144 loops: 29
+// us for both sweeps, 12 us for the backward one, where blocks of 16 rows
+// against an explicit LU record took 110 and 79 us), the read of U per sweep
+// for large NP (256 systems of 1,024: 720 and 364 us, 868 and 855 before;
+// 2.1 GB per sweep).
+template <typename T2, bool FWD, bool BWD>
+__device__ __forceinline__ void ldl_apply_inverse(const T2 *__restrict__ U, const T2 *__restrict__ XT,
+                                                  const double2 *__restrict__ dinv, int NP, double2 *sx,
+                                                  double2 *sred, double2 *sv) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int nb = NP / 64;
+    const double2 z = make_double2(0.0, 0.0);
+    for (int b = 0; FWD && b < nb; ++b) {
+        const T2 *X = XT + (size_t)b * 64 * 64;
+        const int mb = nb - 1 - b;  // column blocks right of the diagonal
+        const int kg = mb <= 1 ? 16 : mb == 2 ? 8 : mb <= 4 ? 4 : mb <= 8 ? 2 : 1;
+        const int rows = 64 / kg;
+        const bool act = wv < mb * kg;
+        const int cbk = act ? wv % mb : 0, kgrp = act ? wv / mb : 0;
+        const T2 *ub = U + (size_t)(64 * b + rows * kgrp) * NP + 64 * (b + (act ? 1 + cbk : 0)) + lane;
+        T2 u[16], x[4];
+        if (act) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) u[e] = ub[(size_t)(e < rows ? e : 0) * NP];
+        }
+        double2 acc = z;
+        const bool low = (wv >> 2) <= (lane >> 4);  // X is lower triangular
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = X[(low ? (4 * wv + e) * 64 : 0) + lane];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = zfma(acc, low ? ld2(x[e]) : z, sx[64 * b + 4 * wv + e]);
+        sred[tid] = acc;
+        __syncthreads();
+        if (tid < 64) {
+            double2 y = sred[tid];
+#pragma unroll
+            for (int e = 1; e < 16; ++e) {
+                y.x += sred[64 * e + tid].x;
+                y.y += sred[64 * e + tid].y;
+            }
+            sx[64 * b + tid] = y;
+            sv[tid] = zmul(y, dinv[64 * b + tid]);
+        }
+        __syncthreads();
+        if (mb == 0) break;  // uniform
+        acc = z;
+        if (act) {
+            const double2 *v = sv + rows * kgrp;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (e < rows) acc = zfma(acc, ld2(u[e]), v[e]);
+            for (int r0 = 16; r0 < rows; r0 += 16) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e) u[e] = ub[(size_t)(r0 + e) * NP];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc = zfma(acc, ld2(u[e]), v[r0 + e]);
+            }
+            sred[(kgrp * mb + cbk) * 64 + lane] = acc;
+        }
+        __syncthreads();
+        if (tid < 64 * mb) {
+            double2 t = sx[64 * (b + 1) + tid];
+            for (int e = 0; e < kg; ++e) {
+                t.x -= sred[e * 64 * mb + tid].x;
+                t.y -= sred[e * 64 * mb + tid].y;
+            }
+            sx[64 * (b + 1) + tid] = t;
+        }
+        __syncthreads();
+    }
+    for (int b = nb - 1; BWD && b >= 0; --b) {
+        const T2 *X = XT + (size_t)b * 64 * 64;
+        const int mb = nb - 1 - b;
+        const int c = tid >> 4, r16 = tid & 15;
+        T2 x[4];  // X^T of column c (rows of block e >= c / 16)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = X[c * 64 + r16 + 16 * (e >= (c >> 4) ? e : 3)];
+        const T2 *ub = U + (size_t)(64 * b + 4 * wv) * NP + 64 * (b + 1) + lane;
+        double2 acc[4] = {z, z, z, z};
+        for (int f = 0; f < mb; f += 3) {
+            T2 u[3][4];
+#pragma unroll
+            for (int h = 0; h < 3; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    u[h][e] = ub[(size_t)e * NP + 64 * (f + h < mb ? f + h : f)];
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {
+                const double2 xv = f + h < mb ? sx[64 * (b + 1 + f + h) + lane] : z;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] = zfma(acc[e], ld2(u[h][e]), xv);
+            }
+        }
+        // sums over the lanes: 32-lane halves keep two rows each, 16-lane
+        // quarters one, then the 16 lanes of each row
+        const bool hi = lane & 32, odd = lane & 16;
+        double2 p[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const double2 mine = hi ? acc[2 + e] : acc[e], give = hi ? acc[e] : acc[2 + e];
+            p[e] = make_double2(mine.x + __shfl_xor(give.x, 32), mine.y + __shfl_xor(give.y, 32));
+        }
+        const double2 mine = odd ? p[1] : p[0], give = odd ? p[0] : p[1];
+        double2 t = make_double2(mine.x + __shfl_xor(give.x, 16), mine.y + __shfl_xor(give.y, 16));
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) {
+            t.x += __shfl_xor(t.x, off);
+            t.y += __shfl_xor(t.y, off);
+        }
+        if (r16 == 0) {
+            const int k = 4 * wv + 2 * (hi ? 1 : 0) + (odd ? 1 : 0);
+            const double2 y = sx[64 * b + k];
+            sv[k] = zmul(make_double2(y.x - t.x, y.y - t.y), dinv[64 * b + k]);
+        }
+        __syncthreads();
+        double2 w = z;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            w = zfma(w, e >= (c >> 4) ? ld2(x[e]) : z, sv[r16 + 16 * e]);
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) {
+            w.x += __shfl_xor(w.x, off);
+            w.y += __shfl_xor(w.y, off);
+        }
+        if (r16 == 0) sx[64 * b + c] = w;
+        __syncthreads();
     }
 }
 
@@ -759,17 +1033,17 @@ __global__ __launch_bounds__(kTB) void k_ldl_big_update(int NP, int k0, int S,
 // walk their blocks of rows one after another and each block is
 // latency-bound; a batch is what fits the 128 registers a lane has in a
 // 1,024-thread workgroup without spilling.
+static_assert(kMaxLoopsBig <= kTS, "load_rhs: one thread per entry");
 static_assert(kMaxLoopsBig <= 16 * 64, "at most 16 entries of a row per lane");
 // Entries past j1 are loaded from column 0 (always inside the row) and both
 // factors replaced by zero, so that the loads need no branches.
-template <typename T2>
-__device__ inline double2 dot_run(const T2 *__restrict__ row, const double2 *x, int j0, int j1) {
+__device__ inline double2 dot_run(const double2 *__restrict__ row, const double2 *x, int j0, int j1) {
     constexpr int D = 8;
     const double2 z = make_double2(0.0, 0.0);
     double2 a0 = z, a1 = z;
 #pragma unroll 1
     for (int e0 = 0; e0 < 16 && j0 + 64 * e0 < j1; e0 += D) {
-        T2 v[D];
+        double2 v[D];
 #pragma unroll
         for (int e = 0; e < D; ++e) {
             const int j = j0 + 64 * (e0 + e);
@@ -779,8 +1053,8 @@ __device__ inline double2 dot_run(const T2 *__restrict__ row, const double2 *x, 
         for (int e = 0; e < D; e += 2) {
             const int j = j0 + 64 * (e0 + e);
             const bool in0 = j < j1, in1 = j + 64 < j1;
-            a0 = zfma(a0, in0 ? ld2(v[e]) : z, x[in0 ? j : 0]);
-            a1 = zfma(a1, in1 ? ld2(v[e + 1]) : z, x[in1 ? j + 64 : 0]);
+            a0 = zfma(a0, in0 ? v[e] : z, x[in0 ? j : 0]);
+            a1 = zfma(a1, in1 ? v[e + 1] : z, x[in1 ? j + 64 : 0]);
         }
     }
     return make_double2(a0.x + a1.x, a0.y + a1.y);
@@ -822,34 +1096,41 @@ __device__ inline double2 wave_sum(double2 a) {
     return a;
 }
 
-// Right-hand side of row k < n of system r: the loop voltage (forward) or
-// rscale * conj(sum over chunks of (rr + j ri)) (adjoint).
+// Right-hand side of system r into sx[0 .. NP): the loop voltage (forward) or
+// rscale * conj(sum over chunks of (rr + j ri)) (adjoint; the chunks dealt to
+// as many threads per entry as the workgroup has, added up through sred).
 template <int RHS>
-__device__ inline double2 rhs_entry(int k, int NP, const SysRef &r) {
-    if (RHS == kRhsExcitation) return loop_voltage(r.phi, r.n, k, r.w);
-    const int S = r.S, s = r.s;
-    const void *rhs = r.rhs;
-    double rr = 0.0, ri = 0.0;
-    for (int c = 0; c < r.nchunk; ++c) {
-        if (RHS == kRhsPairs) {
-            const double2 v = ((const double2 *)rhs)[((size_t)c * S + s) * NP + k];
-            rr += v.x;
-            ri += v.y;
-        } else if (RHS == kRhsPlanarF32) {
-            const float *R = (const float *)rhs + (size_t)c * NP * 2 * S;
-            rr += (double)R[(size_t)(2 * s) * NP + k];
-            ri += (double)R[(size_t)(2 * s + 1) * NP + k];
-        } else {
-            const double *R = (const double *)rhs + (size_t)c * NP * 2 * S;
-            rr += R[(size_t)(2 * s) * NP + k];
-            ri += R[(size_t)(2 * s + 1) * NP + k];
+__device__ __forceinline__ void load_rhs(int NP, const SysRef &r, double2 *sx, double2 *sred) {
+    const int tid = threadIdx.x;
+    if (RHS == kRhsExcitation) {
+        for (int k = tid; k < NP; k += kTS)
+            sx[k] = k < r.n ? loop_voltage(r.phi, r.n, k, r.w) : make_double2(0.0, 0.0);
+        return;
+    }
+    const double2 *part = (const double2 *)r.rhs + (size_t)r.s * NP;
+    const int G = kTS / NP, k = tid % NP, c0 = tid / NP;  // NP <= kTS
+    double2 a = make_double2(0.0, 0.0);
+    if (c0 < G && k < r.n) {
+#pragma unroll 4
+        for (int c = c0; c < r.nchunk; c += G) {
+            const double2 v = part[(size_t)c * r.S * NP + k];
+            a.x += v.x;
+            a.y += v.y;
         }
     }
-    return make_double2(r.rscale * rr, -r.rscale * ri);
+    sred[tid] = a;
+    __syncthreads();
+    if (tid < NP) {
+        for (int e = 1; e < G; ++e) {
+            a.x += sred[e * NP + tid].x;
+            a.y += sred[e * NP + tid].y;
+        }
+        sx[tid] = make_double2(r.rscale * a.x, -r.rscale * a.y);
+    }
 }
 
 // sx <- U^-1 L^-1 P sx for one system's LU record A (unit lower L below the
-// diagonal, U on and above it; the row swaps piv first when PIV), the vector
+// diagonal, U on and above it; the row swaps piv first), the vector
 // in LDS, the kTS threads of the workgroup taking part: blocks of 16 rows,
 // dot products against the solved rows (wave r takes row r of the block and
 // stages its diagonal-block entries in LDS), then the 16x16 diagonal block
@@ -857,14 +1138,14 @@ __device__ inline double2 rhs_entry(int k, int NP, const SysRef &r) {
 //   The blocks follow one another, so each block's loads of its rows are
 // latency on the critical path.  With PF (rows of at most 64 kPf entries),
 // the next block's row entries (kPf per lane) and diagonal-block entries are
-// loaded while the current block's diagonal part is solved.  Identity swaps
-// (the records of the blocked LDL^T) are found by one vote and skipped.
+// loaded while the current block's diagonal part is solved.  Swaps that move
+// nothing are found by one vote and skipped.
 constexpr int kPf = 4;
-template <typename T2, bool PIV, bool PF>
-__device__ __forceinline__ void lu_apply_inverse(const T2 *__restrict__ A, const int *__restrict__ piv, int NP,
+template <bool PF>
+__device__ __forceinline__ void lu_apply_inverse(const double2 *__restrict__ A, const int *__restrict__ piv, int NP,
                                  double2 *sx, double2 *st, double2 (*sd)[17]) {
     const int tid = threadIdx.x;
-    if (PIV) {
+    {
         int moved = 0;
         for (int j = tid; j < NP; j += kTS) moved |= piv[j] != j;
         if (__syncthreads_or(moved)) {
@@ -886,9 +1167,9 @@ __device__ __forceinline__ void lu_apply_inverse(const T2 *__restrict__ A, const
     // PF: entries j = j0 + 64 e (e < kPf) of row r0 + r inside [j0, j1)
     // (others from column 0, always inside the row, and zeroed when used),
     // and the diagonal-block entry of column r0 + (q & 15)
-    T2 pf[kPf], pd;
+    double2 pf[kPf], pd;
     auto fetch = [&](int r0, int j0, int j1) {
-        const T2 *row = A + (size_t)(r0 + r) * NP;
+        const double2 *row = A + (size_t)(r0 + r) * NP;
 #pragma unroll
         for (int e = 0; e < kPf; ++e) {
             const int j = j0 + 64 * e;
@@ -904,7 +1185,7 @@ __device__ __forceinline__ void lu_apply_inverse(const T2 *__restrict__ A, const
             for (int e = 0; e < kPf; ++e) {
                 const int j = j0 + 64 * e;
                 const bool in = j < j1;
-                acc = zfma(acc, in ? ld2(pf[e]) : z, sx[in ? j : 0]);
+                acc = zfma(acc, in ? pf[e] : z, sx[in ? j : 0]);
             }
         } else {
             acc = dot_run(A + (size_t)(r0 + r) * NP, sx, j0, j1);
@@ -913,9 +1194,9 @@ __device__ __forceinline__ void lu_apply_inverse(const T2 *__restrict__ A, const
     };
     auto diag_entry = [&](int r0) {
         if constexpr (PF)
-            return ld2(pd);
+            return pd;
         else
-            return ld2(A[(size_t)(r0 + r) * NP + r0 + (q & 15)]);
+            return A[(size_t)(r0 + r) * NP + r0 + (q & 15)];
     };
     // forward: L y = P b, L unit lower; block r0 uses columns [0, r0)
     if (PF) fetch(0, q, 0);
@@ -1000,15 +1281,21 @@ __device__ __forceinline__ void write_solution(const SysRef &r, const double2 *s
 }
 
 // One workgroup per system (only those with only[s] == want when `only` is
-// set): right-hand side, the two triangular solves with the FP64 record,
-// outputs.
+// set): right-hand side, the triangular solves with the FP64 record, outputs.
+// Systems whose fmt is kFmtLDL hold a U, X, D^-1 record, and the forward solve
+// starts from the y that the factorisation left (its backward sweep only);
+// the others hold a pivoted LU.
 template <int RHS, class Src>
-__global__ __launch_bounds__(kTS) void k_lu_solve(int NP, int S, Src src,
-                                                  const double2 *__restrict__ Aall,
-                                                  const int *__restrict__ pivall,
-                                                  const int *__restrict__ only, int want) {
+__global__ __launch_bounds__(kTS) void k_big_solve(int NP, int S, Src src,
+                                                   const double2 *__restrict__ Aall,
+                                                   const int *__restrict__ pivall,
+                                                   const double2 *__restrict__ Xall,
+                                                   const double2 *__restrict__ Dall,
+                                                   const int *__restrict__ fmt,
+                                                   const int *__restrict__ only, int want) {
     __shared__ double2 sx[kMaxLoopsBig];
-    __shared__ double2 st[16];
+    __shared__ double2 sred[kTS];
+    __shared__ double2 st[64];
     __shared__ double2 sd[16][17];
     __shared__ int sFlag;
     const int s = blockIdx.x;
@@ -1016,16 +1303,28 @@ __global__ __launch_bounds__(kTS) void k_lu_solve(int NP, int S, Src src,
     if (only && only[s] != want) return;
     const int tid = threadIdx.x;
     const SysRef r = src.ref(s);
-    for (int k = tid; k < NP; k += kTS)
-        sx[k] = k < r.n ? rhs_entry<RHS>(k, NP, r) : make_double2(0.0, 0.0);
+    const double2 *A = Aall + (size_t)s * NP * NP;
     if (tid == 0) sFlag = 0;
-    __syncthreads();
-    if (NP <= 64 * kPf)  // uniform over the launch
-        lu_apply_inverse<double2, true, true>(Aall + (size_t)s * NP * NP, pivall + (size_t)s * NP,
-                                              NP, sx, st, sd);
-    else
-        lu_apply_inverse<double2, true, false>(Aall + (size_t)s * NP * NP, pivall + (size_t)s * NP,
-                                               NP, sx, st, sd);
+    const bool ldl = fmt && fmt[s] == kFmtLDL;  // uniform
+    if (ldl) {
+        const double2 *XT = Xall + (size_t)s * 64 * NP, *D = Dall + (size_t)s * 2 * NP;
+        if (RHS == kRhsExcitation) {
+            if (tid < NP) sx[tid] = D[NP + tid];
+            __syncthreads();
+            ldl_apply_inverse<double2, false, true>(A, XT, D, NP, sx, sred, st);
+        } else {
+            load_rhs<RHS>(NP, r, sx, sred);
+            __syncthreads();
+            ldl_apply_inverse<double2, true, true>(A, XT, D, NP, sx, sred, st);
+        }
+    } else {
+        load_rhs<RHS>(NP, r, sx, sred);
+        __syncthreads();
+        if (NP <= 64 * kPf)  // uniform over the launch
+            lu_apply_inverse<true>(A, pivall + (size_t)s * NP, NP, sx, st, sd);
+        else
+            lu_apply_inverse<false>(A, pivall + (size_t)s * NP, NP, sx, st, sd);
+    }
     write_solution<RHS>(r, sx, &sFlag);
 }
 
@@ -1069,13 +1368,15 @@ __device__ inline void block_max2(double &a, double &b, double *sm) {
 template <int RHS>
 __global__ __launch_bounds__(kTS) void k_solve_refined(int NP, int S, OneInst src,
                                                        const float2 *__restrict__ A32all,
+                                                       const float2 *__restrict__ Xall,
+                                                       const double2 *__restrict__ Dall,
                                                        int *__restrict__ fmt, int fail_fmt,
                                                        int max_iter, double tol) {
     __shared__ double2 sb[kMaxLoopsBig];
     __shared__ double2 sx[kMaxLoopsBig];
     __shared__ double2 sr[kMaxLoopsBig];
-    __shared__ double2 st[16];
-    __shared__ double2 sd[16][17];
+    __shared__ double2 sred[kTS];
+    __shared__ double2 st[64];
     __shared__ double sm[2 * (kTS / 64)];
     __shared__ int sFlag;
     const int s = blockIdx.x;
@@ -1089,11 +1390,11 @@ __global__ __launch_bounds__(kTS) void k_solve_refined(int NP, int S, OneInst sr
     const double *__restrict__ Rv = sys.R;
     const double *__restrict__ Cb = sys.Cb;
     const float2 *A = A32all + (size_t)s * NP * NP;
-    for (int k = tid; k < NP; k += kTS) {
-        const double2 v = k < n ? rhs_entry<RHS>(k, NP, sys) : make_double2(0.0, 0.0);
-        sb[k] = v;
-        sr[k] = v;
-    }
+    const float2 *XT = Xall + (size_t)s * 64 * NP;
+    const double2 *D = Dall + (size_t)s * 2 * NP;
+    load_rhs<RHS>(NP, sys, sr, sred);
+    __syncthreads();
+    for (int k = tid; k < NP; k += kTS) sb[k] = sr[k];
     if (tid == 0) sFlag = 0;
     __syncthreads();
     const int r = tid >> 6, q = tid & 63;  // wave r takes row r0 + r of each block
@@ -1101,7 +1402,7 @@ __global__ __launch_bounds__(kTS) void k_solve_refined(int NP, int S, OneInst sr
     double prev = 0.0;
     // step 0 solves for x_0 (d_0 = x_0); step i >= 1 for the correction d_i
     for (int it = 0; it <= max_iter; ++it) {
-        lu_apply_inverse<float2, false, false>(A, nullptr, NP, sr, st, sd);
+        ldl_apply_inverse<float2, true, true>(A, XT, D, NP, sr, sred, st);
         double dm = 0.0, xm = 0.0;
         for (int k = tid; k < NP; k += kTS) {
             const double2 d = sr[k];
@@ -1177,90 +1478,72 @@ hipError_t lu_big_launch(int NP, int S, const Src &src, double2 *A_d, int *piv_d
     return hipGetLastError();
 }
 
-// Blocked LDL^T of the systems marked kFmtLDL, in the storage type T2.
+// Blocked LDL^T of the S systems in the storage type T2 (invalid input and
+// small pivots are marked in fmt and left to the pivoted LU).
 template <typename T2, class Src>
-hipError_t blocked_ldl(const BigFactor &bf, int NP, int S, const Src &src, T2 *A_d, int *piv_d,
-                       hipStream_t st) {
-    T2 *wt = (T2 *)bf.wt, *tinv = (T2 *)bf.tinv;
-    hipLaunchKernelGGL((k_big_assemble<T2, Src>), dim3(S, NP / 16), dim3(kTB), 0, st, NP, S, src,
-                       A_d, bf.fmt, bf.zmax);
+hipError_t blocked_ldl(const BigFactor &bf, int NP, int S, const Src &src, T2 *A_d, hipStream_t st) {
+    T2 *X = (T2 *)bf.x;
+    const int nb = NP / 64;
+    hipLaunchKernelGGL((k_ldl_start<T2, Src>), dim3(S), dim3(kTB), 0, st, NP, S, src, A_d, X, bf.d,
+                       bf.fmt, bf.zmax);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    for (int k0 = 0; k0 < NP; k0 += 64) {
-        hipLaunchKernelGGL(k_ldl_big_diag<T2>, dim3(S), dim3(kTB), 0, st, NP, k0, S, A_d, piv_d,
-                           bf.fmt, bf.zmax, tinv);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        const int m = NP - k0 - 64;
-        if (m == 0) break;
-        hipLaunchKernelGGL(k_ldl_big_panel<T2>, dim3(S, m / 64), dim3(kTB), 0, st, NP, k0, S,
-                           (const int *)bf.fmt, A_d, (const T2 *)tinv, wt);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        const int nt = m / 64, T = nt * (nt + 1) / 2;
-        hipLaunchKernelGGL(k_ldl_big_update<T2>, dim3(8 * ((S + 7) / 8) * T), dim3(kTB), 0, st,
-                           NP, k0, S, (const int *)bf.fmt, A_d, (const T2 *)wt, T);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (int kb = 0; e == hipSuccess && kb + 1 < nb; ++kb) {
+        const int js = kb / kSuper * kSuper, T = nb - 1 - kb;
+        hipLaunchKernelGGL((k_ldl_step<T2, Src>), dim3(8 * ((S + 7) / 8) * T), dim3(kTB), 0, st, NP,
+                           S, src, kb, js, T, A_d, X, bf.d, bf.fmt, (const double *)bf.zmax);
+        if ((e = hipGetLastError()) != hipSuccess) break;
+        const int ns = js + kSuper;
+        if (kb + 1 < ns || ns + 1 >= nb) continue;
+        const int nt = nb - ns, Tt = nt * (nt + 1) / 2 - 1;
+        hipLaunchKernelGGL((k_ldl_trail<T2, Src>), dim3(8 * ((S + 7) / 8) * Tt), dim3(kTB), 0, st, NP,
+                           S, src, js, ns, Tt, A_d, bf.d, (const int *)bf.fmt);
+        e = hipGetLastError();
     }
-    return hipSuccess;
+    return e;
 }
 
 template <class Src>
-hipError_t lu_solve_any(int rhs_kind, int NP, int S, const Src &src, const double2 *A_d,
-                        const int *piv_d, const int *only, int want, hipStream_t st) {
-#define COSIM_LU_SOLVE(K)                                                                    \
-    hipLaunchKernelGGL((k_lu_solve<K, Src>), dim3(S), dim3(kTS), 0, st, NP, S, src, A_d, piv_d, \
-                       only, want);                                                          \
-    break
-    switch (rhs_kind) {
-        case kRhsExcitation: COSIM_LU_SOLVE(kRhsExcitation);
-        case kRhsPairs: COSIM_LU_SOLVE(kRhsPairs);
-        case kRhsPlanarF32: COSIM_LU_SOLVE(kRhsPlanarF32);
-        case kRhsPlanarF64: COSIM_LU_SOLVE(kRhsPlanarF64);
-        default: return hipErrorInvalidValue;
-    }
-#undef COSIM_LU_SOLVE
+hipError_t big_solve_any(int rhs_kind, const BigFactor &bf, int NP, int S, const Src &src,
+                         const double2 *A_d, const int *piv_d, const int *only, int want,
+                         hipStream_t st) {
+    const int *fmt = bf.ldl && !only ? bf.fmt : nullptr;
+    const double2 *X = bf.x, *D = bf.d;
+    if (rhs_kind == kRhsExcitation)
+        hipLaunchKernelGGL((k_big_solve<kRhsExcitation, Src>), dim3(S), dim3(kTS), 0, st, NP, S, src,
+                           A_d, piv_d, X, D, fmt, only, want);
+    else
+        hipLaunchKernelGGL((k_big_solve<kRhsPairs, Src>), dim3(S), dim3(kTS), 0, st, NP, S, src, A_d,
+                           piv_d, X, D, fmt, only, want);
     return hipGetLastError();
 }
 
-hipError_t refined_any(int rhs_kind, const BigRefine &rf, int NP, int S, const OneInst &src,
-                       int *fmt, int fail_fmt, hipStream_t st) {
-#define COSIM_REFINED(K)                                                                      \
-    hipLaunchKernelGGL(k_solve_refined<K>, dim3(S), dim3(kTS), 0, st, NP, S, src,              \
-                       (const float2 *)rf.A32, fmt, fail_fmt, rf.max_iter, rf.tol);           \
-    break
-    switch (rhs_kind) {
-        case kRhsExcitation: COSIM_REFINED(kRhsExcitation);
-        case kRhsPairs: COSIM_REFINED(kRhsPairs);
-        case kRhsPlanarF32: COSIM_REFINED(kRhsPlanarF32);
-        case kRhsPlanarF64: COSIM_REFINED(kRhsPlanarF64);
-        default: return hipErrorInvalidValue;
-    }
-#undef COSIM_REFINED
+hipError_t refined_any(int rhs_kind, const BigFactor &bf, const BigRefine &rf, int NP, int S,
+                       const OneInst &src, int fail_fmt, hipStream_t st) {
+    const float2 *X = (const float2 *)bf.x;
+    const double2 *D = bf.d;
+    if (rhs_kind == kRhsExcitation)
+        hipLaunchKernelGGL(k_solve_refined<kRhsExcitation>, dim3(S), dim3(kTS), 0, st, NP, S, src,
+                           (const float2 *)rf.A32, X, D, bf.fmt, fail_fmt, rf.max_iter, rf.tol);
+    else
+        hipLaunchKernelGGL(k_solve_refined<kRhsPairs>, dim3(S), dim3(kTS), 0, st, NP, S, src,
+                           (const float2 *)rf.A32, X, D, bf.fmt, fail_fmt, rf.max_iter, rf.tol);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_lu_big(int NP, int n, int S, int F, const double *M_d, const double *R_d,
-                         const double *C_d, const double *omega_d, double2 *A_d, int *piv_d,
-                         int32_t *status_d, hipStream_t st) {
-    if (NP % 64 != 0 || NP > kMaxLoopsBig) return hipErrorInvalidValue;
-    const OneInst src = one_inst(n, F, S, M_d, R_d, nullptr, C_d, omega_d, nullptr, nullptr, 0,
-                                 0.0, nullptr, nullptr, status_d);
-    return lu_big_launch(NP, S, src, A_d, piv_d, nullptr, 0, st);
-}
-
 hipError_t big_factor(const BigFactor &bf, const BigRefine &rf, int NP, int n, int S, int F,
-                      const double *M_d, const double *R_d, const double *C_d,
+                      const double *M_d, const double *R_d, const double *phi_d, const double *C_d,
                       const double *omega_d, double2 *A_d, int *piv_d, int32_t *status_d,
                       hipStream_t st) {
-    if (!bf.ldl) return launch_lu_big(NP, n, S, F, M_d, R_d, C_d, omega_d, A_d, piv_d, status_d, st);
-    if (NP % 64 != 0 || NP > kMaxLoopsBig || !bf.fmt || !bf.zmax || !bf.wt || !bf.tinv)
-        return hipErrorInvalidValue;
-    if (rf.on && !rf.A32) return hipErrorInvalidValue;
-    const OneInst src = one_inst(n, F, S, M_d, R_d, nullptr, C_d, omega_d, nullptr, nullptr, 0,
+    if (NP % 64 != 0 || NP > kMaxLoopsBig) return hipErrorInvalidValue;
+    const OneInst src = one_inst(n, F, S, M_d, R_d, phi_d, C_d, omega_d, nullptr, nullptr, 0,
                                  0.0, nullptr, nullptr, status_d);
-    hipError_t e = rf.on ? blocked_ldl<float2>(bf, NP, S, src, (float2 *)rf.A32, piv_d, st)
-                         : blocked_ldl<double2>(bf, NP, S, src, A_d, piv_d, st);
+    if (!bf.ldl) return lu_big_launch(NP, S, src, A_d, piv_d, nullptr, 0, st);
+    if (!bf.fmt || !bf.zmax || !bf.x || !bf.d) return hipErrorInvalidValue;
+    if (rf.on && !rf.A32) return hipErrorInvalidValue;
+    hipError_t e = rf.on ? blocked_ldl<float2>(bf, NP, S, src, (float2 *)rf.A32, st)
+                         : blocked_ldl<double2>(bf, NP, S, src, A_d, st);
     if (e != hipSuccess) return e;
     // pivoted FP64 LU (from a fresh Z) for the systems marked on the way
     return lu_big_launch(NP, S, src, A_d, piv_d, bf.fmt, kFmtNeedsPivot, st);
@@ -1274,51 +1557,41 @@ hipError_t big_solve(const BigFactor &bf, const BigRefine &rf, int NP, int n, in
     if (NP % 64 != 0 || NP > kMaxLoopsBig) return hipErrorInvalidValue;
     const OneInst src = one_inst(n, F, S, M_d, R_d, phi_d, C_d, omega_d, I_d, rhs_d, nchunk,
                                  rscale, gsys_d, mu_d, status_d);
-    if (!(bf.ldl && rf.on)) return lu_solve_any(rhs_kind, NP, S, src, A_d, piv_d, nullptr, 0, st);
+    if (!(bf.ldl && rf.on))
+        return big_solve_any(rhs_kind, bf, NP, S, src, A_d, piv_d, nullptr, 0, st);
     const bool fwd = rhs_kind == kRhsExcitation;
     const int fail = fwd ? kFmtRefineFailed : kFmtRefineFailedAdj;
     hipError_t e;
     // 1. the FP32 records, refined
-    if ((e = refined_any(rhs_kind, rf, NP, S, src, bf.fmt, fail, st)) != hipSuccess) return e;
+    if ((e = refined_any(rhs_kind, bf, rf, NP, S, src, fail, st)) != hipSuccess) return e;
     // 2. systems that already hold an FP64 record
     const int have[2] = {kFmtNeedsPivot, kFmtRefineFailed};
     for (int h = 0; h < (fwd ? 1 : 2); ++h)
-        if ((e = lu_solve_any(rhs_kind, NP, S, src, A_d, piv_d, bf.fmt, have[h], st)) != hipSuccess)
+        if ((e = big_solve_any(rhs_kind, bf, NP, S, src, A_d, piv_d, bf.fmt, have[h], st)) != hipSuccess)
             return e;
     // 3. systems whose refinement did not converge just now: pivoted FP64
     // record from a fresh Z, then the FP64 solve
     if ((e = lu_big_launch(NP, S, src, A_d, piv_d, bf.fmt, fail, st)) != hipSuccess) return e;
-    return lu_solve_any(rhs_kind, NP, S, src, A_d, piv_d, bf.fmt, fail, st);
-}
-
-hipError_t launch_lu_solve(int NP, int n, int S, int F, const double2 *A_d, const int *piv_d,
-                           const double *phi_d, const double *C_d, const double *omega_d,
-                           double2 *I_d, int rhs_kind, const void *rhs_d, int nchunk,
-                           double rscale, double *gsys_d, int32_t *status_d, hipStream_t st,
-                           double2 *mu_d) {
-    if (NP % 64 != 0 || NP > kMaxLoopsBig) return hipErrorInvalidValue;
-    const OneInst src = one_inst(n, F, S, nullptr, nullptr, phi_d, C_d, omega_d, I_d, rhs_d,
-                                 nchunk, rscale, gsys_d, mu_d, status_d);
-    return lu_solve_any(rhs_kind, NP, S, src, A_d, piv_d, nullptr, 0, st);
+    return big_solve_any(rhs_kind, bf, NP, S, src, A_d, piv_d, bf.fmt, fail, st);
 }
 
 hipError_t big_group_factor(const BigFactor &bf, const GroupArgs &g, int NP, int S,
                             double2 *A_d, int *piv_d, hipStream_t st) {
     if (NP % 64 != 0 || NP > kMaxLoopsBig || g.count < 1 || g.count > kGroupMax || !bf.fmt ||
-        !bf.zmax || !bf.wt || !bf.tinv)
+        !bf.zmax || !bf.x || !bf.d)
         return hipErrorInvalidValue;
     const GroupSrc src{g};
-    hipError_t e = blocked_ldl<double2>(bf, NP, S, src, A_d, piv_d, st);
+    hipError_t e = blocked_ldl<double2>(bf, NP, S, src, A_d, st);
     if (e != hipSuccess) return e;
     return lu_big_launch(NP, S, src, A_d, piv_d, bf.fmt, kFmtNeedsPivot, st);
 }
 
-hipError_t big_group_solve(const GroupArgs &g, int NP, int S, const double2 *A_d,
-                           const int *piv_d, int rhs_kind, hipStream_t st) {
+hipError_t big_group_solve(const BigFactor &bf, const GroupArgs &g, int NP, int S,
+                           const double2 *A_d, const int *piv_d, int rhs_kind, hipStream_t st) {
     if (NP % 64 != 0 || NP > kMaxLoopsBig || g.count < 1 || g.count > kGroupMax)
         return hipErrorInvalidValue;
     const GroupSrc src{g};
-    return lu_solve_any(rhs_kind, NP, S, src, A_d, piv_d, nullptr, 0, st);
+    return big_solve_any(rhs_kind, bf, NP, S, src, A_d, piv_d, nullptr, 0, st);
 }
 
 }  // namespace cosim
