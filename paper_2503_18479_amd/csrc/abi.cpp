@@ -236,7 +236,7 @@ int choose_chunks(const cosim_plan *p, Prec prec, size_t S, int variant) {
     const int tiles = p->P_pad / kPTile;
     const int cmax = std::max(1, std::min(tiles, 64));
     const size_t slots =
-        (size_t)std::max(1, p->cus) * (size_t)fused_blocks_per_cu(prec, p->NP, variant);
+        (size_t)std::max(1, p->cus) * (size_t)fused_blocks_per_cu(prec, p->NP, p->n, variant);
     int best = cmax;
     double best_fill = -1.0;
     for (int c = 1; c <= cmax; ++c) {

@@ -16,15 +16,17 @@
 // column lane%16) equals the operand layout of the adjoint product once the
 // contraction index p is permuted to pi(4kk + q) = row(q, kk), so no data
 // moves between the two.  B_z
-// itself is never written.  The forward K index (loop k) is likewise permuted
-// to sigma(4kk + q) = (NP/4) q + kk so that each lane reads NP/4 contiguous
-// elements of a G row.  Partial r and loss per (chunk, system) go to memory
-// and are summed in a fixed order by the solve/reduce kernels (no atomics).
+// itself is never written.  In FP32 the forward K index (loop k) is likewise
+// permuted to sigma(4kk + q) = (NP/4) q + kk so that each lane reads NP/4
+// contiguous elements of a G row.  Partial r and loss per (chunk, system) go
+// to memory and are summed in a fixed order by the solve/reduce kernels (no
+// atomics).
 //
 // BF16X3: G = Gh + Gl and I = Ih + Il with bf16 hi/lo parts; the product is
 // Gh Ih + Gh Il + Gl Ih accumulated in FP32 with 16x16x32 bf16 MFMA; w is split
 // the same way for the adjoint.
 #include <atomic>
+#include <type_traits>
 
 #include "internal.h"
 #include "epilogue.h"
@@ -65,16 +67,29 @@ __device__ inline T tcast(double x) {
     return (T)x;
 }
 
-// One workgroup: system block bx (4 waves of 16 NB systems) of P-chunk `chunk`.
-template <typename T, int NP, int NB, int LOSS, bool GRAD>
+// One workgroup: system block bx (4 waves of 16 NB systems) of P-chunk `chunk`,
+// for plans of at most NE loops (fused_extent): the adjoint's row blocks past
+// them are left out, and in FP64 the forward steps and the columns of G too,
+// whose loop index runs in natural order, 4 kk + q, so that the columns left
+// out would have added zeros at the end of each sum and the result does not
+// depend on NE.  (FP32 sums in the order of the permutation above, where the
+// padding is spread over the steps.)
+//   FP64 matrix-core issue bounds it: 64 loops, 65,536 points, 4,032 systems
+// run at KFP64AFTER where the form with one wave per SIMD, the padded steps and a
+// square root and a division per point took 2.86 ms (47 TFLOP/s).
+template <typename T, int NP, int NE, int NB, int LOSS, bool GRAD>
 __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chunk) {
     typedef typename Mma<T>::V V;
-    constexpr int KS = NP / 4;   // forward k-steps of 4
-    constexpr int IB = NP / 16;  // 16-row blocks of the adjoint output
-    constexpr int PT = kPTile;
-    constexpr int LDR = NP + (sizeof(T) == 4 ? 4 : 2);  // padded LDS row
-    __shared__ __attribute__((aligned(16))) T sG[PT * LDR];
-    __shared__ T sT[PT];
+    constexpr bool D = sizeof(T) == 8;
+    constexpr int NC = D ? NE : NP;      // columns of G that are read
+    constexpr int KS = NC / 4;           // forward k-steps of 4
+    constexpr int IB = (NE + 15) / 16;   // 16-row blocks of the adjoint output
+    constexpr int PT = D ? kPTile / 2 : kPTile;  // rows per tile (FP32: one flush)
+    constexpr int LDR = NC + (D ? 2 : 4);        // padded LDS row
+    __shared__ __attribute__((aligned(16))) T sGb[2][PT * LDR];
+    __shared__ T sTb[2][PT];
+    // loop index of step kk in lane group q
+    auto kidx = [](int q, int kk) { return D ? 4 * kk + q : KS * q + kk; };
 
     const T *__restrict__ G = (const T *)a.G;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -83,14 +98,14 @@ __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chun
     const int pb = chunk * a.rows_per_chunk;
     const int pe = min(a.P_pad, pb + a.rows_per_chunk);
 
-    // I as forward B operands: lane (r16, q), k-step kk holds I[sys][KS q + kk]
+    // I as forward B operands: lane (r16, q), k-step kk holds I[sys][kidx(q, kk)]
     T Ire[NB][KS], Iim[NB][KS];
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int s = sys0 + 16 * b + r16;
 #pragma unroll
         for (int kk = 0; kk < KS; ++kk) {
-            const int k = KS * q + kk;
+            const int k = kidx(q, kk);
             double2 v = make_double2(0.0, 0.0);
             if (s < a.S && k < a.n) v = a.I[(size_t)s * a.n + k];
             Ire[b][kk] = tcast<T>(v.x);
@@ -122,28 +137,45 @@ __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chun
 #pragma unroll
                 for (int m = 0; m < 4; ++m) r64[ib][b][c][m] = 0.0;
 
+    // Tiles are double-buffered in LDS: the next one is loaded into registers
+    // while the current one is used and stored after it, one barrier per tile.
     constexpr int E = 16 / sizeof(T);  // elements per 16-byte vector
-    constexpr int NV = PT * NP / E;
-    for (int p0 = pb; p0 < pe; p0 += PT) {
-        __syncthreads();
-        for (int v = threadIdx.x; v < NV; v += 256) {
-            const int e0 = v * E;
-            const int row = e0 / NP, col = e0 - row * NP;
-            const uint4 val = *(const uint4 *)(G + (size_t)(p0 + row) * NP + col);
-            *(uint4 *)(sG + row * LDR + col) = val;
+    constexpr int NV = PT * NC / E, VPT = (NV + 255) / 256;
+    uint4 stg[VPT];
+    double tstg = 0.0;
+    auto fetch = [&](int p0) {
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int e0 = min((int)threadIdx.x + 256 * u, NV - 1) * E;
+            const int row = e0 / NC, col = e0 - row * NC;
+            stg[u] = *(const uint4 *)(G + (size_t)(p0 + row) * NP + col);
         }
-        if (threadIdx.x < PT) {
-            const int p = p0 + threadIdx.x;
-            // a padded row's field is the incident field alone: the target |inc|
-            // makes its residual zero (inc = 0 outside the ratio mode)
-            sT[threadIdx.x] = p < a.P ? tcast<T>(a.T[p]) : tcast<T>(fabs(a.inc));
+        // a padded row's field is the incident field alone: the target |inc|
+        // makes its residual zero (inc = 0 outside the ratio mode)
+        const int p = p0 + (int)threadIdx.x % PT;
+        tstg = p < a.P ? a.T[p] : fabs(a.inc);
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int v = threadIdx.x + 256 * u, e0 = v * E;
+            const int row = e0 / NC, col = e0 - row * NC;
+            if (NV % 256 == 0 || v < NV) *(uint4 *)(sGb[buf] + row * LDR + col) = stg[u];
         }
-        __syncthreads();
-#pragma unroll 1
+        if (threadIdx.x < PT) sTb[buf][threadIdx.x] = tcast<T>(tstg);
+    };
+    fetch(pb);
+    stash(0);
+    __syncthreads();
+    for (int p0 = pb, buf = 0; p0 < pe; p0 += PT, buf ^= 1) {
+        const T *sG = sGb[buf];
+        const T *sT = sTb[buf];
+        fetch(min(p0 + PT, pe - PT));  // the last tile's fetch is not used
+#pragma unroll 2
         for (int sp = 0; sp < PT / 16; ++sp) {
             T af[KS];
 #pragma unroll
-            for (int kk = 0; kk < KS; ++kk) af[kk] = sG[(16 * sp + r16) * LDR + KS * q + kk];
+            for (int kk = 0; kk < KS; ++kk) af[kk] = sG[(16 * sp + r16) * LDR + kidx(q, kk)];
             V br[NB], bi[NB];
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
@@ -172,7 +204,8 @@ __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chun
                     T at[4];
 #pragma unroll
                     for (int kk = 0; kk < 4; ++kk)
-                        at[kk] = sG[(16 * sp + Mma<T>::row(q, kk)) * LDR + 16 * ib + r16];
+                        at[kk] = sG[(16 * sp + Mma<T>::row(q, kk)) * LDR +
+                                    (16 * IB > NC ? min(16 * ib + r16, NC - 1) : 16 * ib + r16)];
 #pragma unroll
                     for (int b = 0; b < NB; ++b)
 #pragma unroll
@@ -195,6 +228,8 @@ __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chun
                         racc[ib][b][c] = V{};
                     }
         }
+        stash(buf ^ 1);
+        __syncthreads();
     }
 
     // ---- partial results of this chunk -------------------------------------
@@ -221,9 +256,18 @@ __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chun
     }
 }
 
-template <typename T, int NP, int NB, int LOSS, bool GRAD>
-__global__ __launch_bounds__(256) void k_fused(FusedArgs a) {
-    fused_block<T, NP, NB, LOSS, GRAD>(a, blockIdx.x, blockIdx.y);
+// Loops that the kernel of a plan of n loops covers, in steps that leave out
+// whole 16-row blocks of the adjoint (and FP64 forward steps below 16).
+constexpr int fused_extent(bool fp64, int NP, int n) {
+    if (NP == 64) return n <= 48 ? 48 : 64;
+    return fp64 && n <= 8 ? 8 : n <= 16 ? 16 : 32;
+}
+
+// Two waves per SIMD where the registers allow it, so that the barriers and
+// the epilogue of one run beside the matrix-core work of the other.
+template <typename T, int NP, int NE, int NB, int LOSS, bool GRAD>
+__global__ __launch_bounds__(256, NB == 1 || NE < 64 ? 2 : 1) void k_fused(FusedArgs a) {
+    fused_block<T, NP, NE, NB, LOSS, GRAD>(a, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -606,12 +650,13 @@ __global__ __launch_bounds__(256, 2) void k_fused_bf16x3(FusedArgs a) {
 // and is its workgroup b - first[m] in (system block, chunk) order, system
 // blocks fastest.
 template <typename T, int NP, int LOSS, bool GRAD>
-__global__ __launch_bounds__(256) void k_fused_group(FusedGroup g) {
+__global__ __launch_bounds__(256, 2) void k_fused_group(FusedGroup g) {
     const int b = blockIdx.x;
     int m = 0;
     while (m + 1 < g.count && b >= g.first[m + 1]) ++m;
     const int loc = b - g.first[m], bxn = g.bx[m];
-    fused_block<T, NP, (sizeof(T) == 8 ? 1 : 2), LOSS, GRAD>(g.in[m], loc % bxn, loc / bxn);
+    // every member with the whole padded extent: the same sums as its own kernel's
+    fused_block<T, NP, NP, 1, LOSS, GRAD>(g.in[m], loc % bxn, loc / bxn);
 }
 template <int NP, int LOSS, bool GRAD>
 __global__ __launch_bounds__(256, 2) void k_fused_bf16x3_group(FusedGroup g) {
@@ -979,14 +1024,14 @@ struct Variant {
                // 3: the same eight-wave kernel with both groups in step
 };
 constexpr Variant kVarF64[] = {{1, 64, false, 0}, {2, 64, false, 0}};
-constexpr Variant kVarF32[] = {{2, 64, false, 0}, {1, 64, false, 0}};
+constexpr Variant kVarF32[] = {{1, 64, false, 0}, {2, 64, false, 0}};
 constexpr Variant kVarBF16[] = {{2, 64, false, 0}, {2, 32, false, 0}, {1, 64, false, 0},
                                 {1, 32, false, 0}, {2, 64, true, 0},  {2, 32, true, 0},
                                 {1, 64, true, 1},  {1, 32, true, 1},  {2, 32, true, 1},
                                 {2, 64, true, 1}, {2, 64, true, 2}, {1, 64, true, 2},
                                 {2, 64, true, 3}};
 // the group kernels hard-wire variant 0 of each precision
-static_assert(kVarF64[0].nb == 1 && kVarF32[0].nb == 2 && kVarBF16[0].nb == 2 &&
+static_assert(kVarF64[0].nb == 1 && kVarF32[0].nb == 1 && kVarBF16[0].nb == 2 &&
                   kVarBF16[0].pt == 64 && !kVarBF16[0].db && kVarBF16[0].pipe == 0,
               "k_fused_group / k_fused_bf16x3_group follow variant 0");
 
@@ -999,11 +1044,22 @@ hipError_t occupancy_of(K kernel, int *occ, int threads = 256) {
 
 template <typename T, int NP, int NB, int LOSS, bool GRAD>
 hipError_t go_typed(const FusedArgs &a, hipStream_t st, int *occ) {
-    if (occ) return occupancy_of(k_fused<T, NP, NB, LOSS, GRAD>, occ);
     const int per_block = 4 * 16 * NB;
     dim3 grid((a.S + per_block - 1) / per_block, a.nchunk);
-    hipLaunchKernelGGL((k_fused<T, NP, NB, LOSS, GRAD>), grid, dim3(256), 0, st, a);
-    return hipGetLastError();
+    auto go = [&](auto extent) {
+        constexpr int NE = decltype(extent)::value;
+        if (occ) return occupancy_of(k_fused<T, NP, NE, NB, LOSS, GRAD>, occ);
+        hipLaunchKernelGGL((k_fused<T, NP, NE, NB, LOSS, GRAD>), grid, dim3(256), 0, st, a);
+        return hipGetLastError();
+    };
+    const int ne = fused_extent(sizeof(T) == 8, NP, a.n);
+    if constexpr (NP == 64) {
+        return ne == 48 ? go(std::integral_constant<int, 48>{}) : go(std::integral_constant<int, 64>{});
+    } else {
+        if constexpr (sizeof(T) == 8)
+            if (ne == 8) return go(std::integral_constant<int, 8>{});
+        return ne == 16 ? go(std::integral_constant<int, 16>{}) : go(std::integral_constant<int, 32>{});
+    }
 }
 
 template <int NP, int NB, int PT, bool DB, int PIPE, int LOSS, bool GRAD>
@@ -1035,8 +1091,8 @@ hipError_t go_np(Prec prec, int variant, const FusedArgs &a, hipStream_t st, int
             break;
         case Prec::F32:
             switch (variant) {
-                case 0: return go_typed<float, NP, 2, LOSS, GRAD>(a, st, occ);
-                case 1: return go_typed<float, NP, 1, LOSS, GRAD>(a, st, occ);
+                case 0: return go_typed<float, NP, 1, LOSS, GRAD>(a, st, occ);
+                case 1: return go_typed<float, NP, 2, LOSS, GRAD>(a, st, occ);
             }
             break;
         case Prec::BF16X3:
@@ -1098,21 +1154,25 @@ int fused_systems_per_block(Prec prec, int NP, int variant) {
     return 64;
 }
 
-int fused_blocks_per_cu(Prec prec, int NP, int variant) {
-    // per (precision, NP 32 / 64, variant); the magnitude loss with gradient
-    // stands for every loss mode (their register and LDS use agree)
-    static std::atomic<int> cache[3][2][16];
-    const int pi = (int)prec, ni = NP == 32 ? 0 : 1;
+int fused_blocks_per_cu(Prec prec, int NP, int n, int variant) {
+    // per (precision, extent of the kernel, variant); the magnitude loss with
+    // gradient stands for every loss mode (their register and LDS use agree).
+    // BF16X3 has one kernel per padded size.
+    static std::atomic<int> cache[3][65][16];
+    const int pi = (int)prec;
     if (pi < 0 || pi > 2 || (NP != 32 && NP != 64) || variant < 0 || variant >= 16) return 1;
-    int v = cache[pi][ni][variant].load(std::memory_order_relaxed);
+    const int ne = prec == Prec::BF16X3 ? NP : fused_extent(prec == Prec::F64, NP, n);
+    int v = cache[pi][ne][variant].load(std::memory_order_relaxed);
     if (v > 0) return v;
     int occ = 0;
-    if (go_loss<COSIM_LOSS_MAG, true>(prec, NP, variant, FusedArgs{}, nullptr, &occ) != hipSuccess ||
+    FusedArgs probe{};
+    probe.n = n;
+    if (go_loss<COSIM_LOSS_MAG, true>(prec, NP, variant, probe, nullptr, &occ) != hipSuccess ||
         occ < 1) {
         (void)hipGetLastError();
         occ = 1;
     }
-    cache[pi][ni][variant].store(occ, std::memory_order_relaxed);
+    cache[pi][ne][variant].store(occ, std::memory_order_relaxed);
     return occ;
 }
 

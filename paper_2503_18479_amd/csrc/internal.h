@@ -147,7 +147,7 @@ hipError_t launch_adam(int count, double *C_d, const double *grad_d, double *m_d
 int fused_variant_count(Prec prec);
 int fused_systems_per_block(Prec prec, int NP, int variant);
 // Workgroups of the variant's fused kernel that one compute unit holds at once.
-int fused_blocks_per_cu(Prec prec, int NP, int variant);
+int fused_blocks_per_cu(Prec prec, int NP, int n, int variant);
 // The fused contraction of several plans (64 loops or fewer, one precision,
 // variant 0) in one launch: member m owns workgroups [first[m], first[m + 1])
 // (the last up to the launch's total), bx[m] system blocks times its chunks.
