@@ -344,9 +344,10 @@ class Plan:
             adam_step(C, g, m, v, t, lr=lr, betas=betas, eps=eps)
 
         if not graph:
-            for k in range(steps):
-                one_step()
-                hist[k].copy_(loss)
+            for k in range(steps):  # the step's loss straight into its row
+                self.loss_and_grad(C, omega, T, loss_mode=loss_mode, precision=precision,
+                                   out=(hist[k], g, st))
+                adam_step(C, g, m, v, t, lr=lr, betas=betas, eps=eps)
             return hist, st
         # warm the variant choice and the workspace on a copy, then capture
         C0, side = C.clone(), torch.cuda.Stream()

@@ -831,8 +831,6 @@ int cosim_solve(cosim_plan_t p, int B, int F, const double *C_d, const double *o
     } else if (p->ldl_ok) {
         HIP_TRY(launch_ldl(p->NP, p->n, S, F, p->M_d, p->R_d, C_d, omega_d, p->phi_d, p->fac, I,
                            status_d, st));
-        HIP_TRY(launch_solve_fallback(p->NP, p->n, S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
-                                      I, status_d, p->fac, st));
     } else {
         HIP_TRY(launch_solve_forward(p->NP, p->n, S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                                      I, status_d, p->fac, st));
@@ -1079,8 +1077,6 @@ static int loss_and_grad_impl(cosim_plan_t p, int B, int F, const double *C_d, c
     if (p->ldl_ok) {
         HIP_TRY(launch_ldl(p->NP, p->n, (int)S, F, p->M_d, p->R_d, C_d, omega_d, p->phi_d,
                            w.fac, w.I, status_d, st));
-        HIP_TRY(launch_solve_fallback(p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d,
-                                      omega_d, w.I, status_d, w.fac, st));
     } else {
         HIP_TRY(launch_solve_forward(p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d,
                                      omega_d, w.I, status_d, w.fac, st));
@@ -1092,12 +1088,21 @@ static int loss_and_grad_impl(cosim_plan_t p, int B, int F, const double *C_d, c
     a.lpart = w.lpart;
     HIP_TRY(launch_fused(prec, p->NP, variant, loss_mode, grad, a, st));
     if (ev) HIP_TRY(hipEventRecord(ev[2], st));
+    // with one frequency the replay forms the final sums as well
+    FinalSums fin;
+    if (grad && F == 1) {
+        fin.grad = grad_d;
+        fin.loss = loss_d;
+        fin.lpart = w.lpart;
+        fin.lscale = scale;
+    }
     if (grad)
         HIP_TRY(launch_replay_adjoint(p->NP, p->n, (int)S, F, w.fac, C_d, omega_d, w.I,
-                                      w.rpart, nchunk, scale, w.gsys, mu, status_d, st));
+                                      w.rpart, nchunk, scale, w.gsys, mu, status_d, st, fin));
     if (ev) HIP_TRY(hipEventRecord(ev[3], st));
-    HIP_TRY(launch_reduce(p->n, B, F, nchunk, grad ? w.gsys : nullptr, w.lpart, scale, grad_d,
-                          loss_d, st));
+    if (!fin.grad)
+        HIP_TRY(launch_reduce(p->n, B, F, nchunk, grad ? w.gsys : nullptr, w.lpart, scale, grad_d,
+                              loss_d, st));
     if (ev) HIP_TRY(hipEventRecord(ev[4], st));
     return COSIM_OK;
 }
@@ -1280,7 +1285,6 @@ static int enqueue_small_group(const ManyCall &mc, const std::vector<int> &g, in
     }
     hipEvent_t ev_fwd = pool->extra[group];
     if (launch_small_group(NP, sg, Sg, SmallPhase::Factor, gs) != hipSuccess ||
-        launch_small_group(NP, sg, Sg, SmallPhase::Fallback, gs) != hipSuccess ||
         hipEventRecord(ev_fwd, gs) != hipSuccess) {
         return fail(COSIM_EDEVICE, "grouped solve launch failed");
     }

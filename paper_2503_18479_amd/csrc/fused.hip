@@ -75,7 +75,7 @@ __device__ inline T tcast(double x) {
 // depend on NE.  (FP32 sums in the order of the permutation above, where the
 // padding is spread over the steps.)
 //   FP64 matrix-core issue bounds it: 64 loops, 65,536 points, 4,032 systems
-// run at KFP64AFTER where the form with one wave per SIMD, the padded steps and a
+// run at 2.16 ms (62.5 TFLOP/s) where the form with one wave per SIMD, the padded steps and a
 // square root and a division per point took 2.86 ms (47 TFLOP/s).
 template <typename T, int NP, int NE, int NB, int LOSS, bool GRAD>
 __device__ __forceinline__ void fused_block(const FusedArgs &a, int bx, int chunk) {

@@ -84,22 +84,26 @@ __host__ __device__ constexpr int ldl_col(int NP, int k) { return k * (2 * NP - 
 constexpr int kFlagPivot = 1 << 16;  // kernel-internal status bit, never returned
 
 // LDL^T fast path (all R_k > 0): factorises, records and solves,
-// I = Z^-1 (E - j w Phi) in I_d; marks systems that need pivoting
-// (fmt = kFmtNeedsPivot, I_d left for it) for launch_solve_fallback.
+// I = Z^-1 (E - j w Phi) in I_d, with pivoted Gauss-Jordan (and a kFmtGJ
+// record) for the systems that need pivoting.
 hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const double *R_d,
                       const double *C_d, const double *omega_d, const double *phi_d, GJFactor fac,
                       double2 *I_d, int32_t *status_d, hipStream_t st);
-// Pivoted Gauss-Jordan for the marked systems only (writes I and a kFmtGJ record).
-hipError_t launch_solve_fallback(int NP, int n, int S, int F, const double *M_d,
-                                 const double *R_d, const double *phi_d, const double *C_d,
-                                 const double *omega_d, double2 *I_d, int32_t *status_d,
-                                 GJFactor fac, hipStream_t st);
+// The final sums of a call with one frequency, formed by the adjoint replay in
+// place of launch_reduce when grad is set: dL/dC [S][n] and the loss [S] from
+// the partial losses [nchunk][S].
+struct FinalSums {
+    double *grad = nullptr, *loss = nullptr;
+    const double *lpart = nullptr;
+    double lscale = 0.0;
+};
 // Adjoint solve from the record and the per-system gradient terms.
 // mu_d (optional, [S][n]): the adjoint solution itself.
 hipError_t launch_replay_adjoint(int NP, int n, int S, int F, GJFactor fac, const double *C_d,
                                  const double *omega_d, double2 *I_d, const double2 *rpart_d,
                                  int nchunk, double rscale, double *gsys_d, double2 *mu_d,
-                                 int32_t *status_d, hipStream_t st);
+                                 int32_t *status_d, hipStream_t st,
+                                 const FinalSums &fin = FinalSums{});
 
 // Forward solve by pivoted Gauss-Jordan: Z I = E - j w Phi for S = B*F systems
 // (s = b*F + f); records the elimination (kFmtGJ) in `fac` when fac.L is set.
@@ -239,7 +243,7 @@ struct SmallGroup {
     int count;
     SmallInst in[kSmallGroupMax];
 };
-enum class SmallPhase { Factor, Fallback, Adjoint };
+enum class SmallPhase { Factor, Adjoint };
 // The final sums (k_reduce) of a group's members in one launch; member i owns
 // configurations [b0, b0 + B) of the launch.
 struct ReduceInst {
@@ -253,8 +257,9 @@ struct ReduceGroup {
     ReduceInst in[kGroupMax];
 };
 hipError_t launch_reduce_group(const ReduceGroup &g, int Btot, hipStream_t st);
-// One phase of the small-plan solver path (k_ldl with the forward solve, the
-// pivoted fallback of marked systems, the adjoint replay) over a group's S systems.
+// One phase of the small-plan solver path (factorisation with the forward
+// solve and the pivoted fallback of marked systems, or the adjoint replay) over
+// a group's S systems.
 hipError_t launch_small_group(int NP, const SmallGroup &g, int S, SmallPhase phase,
                               hipStream_t st);
 // Blocked LDL^T (pivoted LU for marked systems) of the group's systems into A_d.

@@ -105,9 +105,22 @@ __device__ inline double readlane_d(double x, int src) {
 // update.
 // One system s (block-uniform) of a plan with n loops, S systems, F
 // frequencies; the kernels below call it for their own system index.
+template <int NP>
+struct GjLds {
+    static constexpr int NT = GJShape<NP>::NT;
+    double2 sL[2][4][NP];      // multiplier columns of a panel
+    int sP[2][4];              // pivot rows of a panel
+    double2 sPiv[NP];
+    int sKof[NP];
+    double2 sU[NT][4][4][4];   // [group][step c][row in tile][col in tile]
+    double2 sUu[NT][4][4];     // [group][step c][col in tile]: u_c of the group's columns
+    double2 sW[2][4][4];       // W = (I + N)^-1, N[c][c'] = l_c'[p_c] (c' < c)
+    double2 sRb[4][4];         // rhs tiles of the pivot-row owners
+    int sFlag;
+};
 template <int NP, bool ADJ>
 __device__ __forceinline__ void gj_system(
-    int s, int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
+    GjLds<NP> &lds, int s, int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
     const double *__restrict__ phi, const double *__restrict__ C,
     const double *__restrict__ omega, const double2 *__restrict__ Iin,
     const double2 *__restrict__ rpart, int nchunk, double rscale, double2 *__restrict__ Iout,
@@ -122,15 +135,15 @@ __device__ __forceinline__ void gj_system(
     const int ti = t % NT, tj = t / NT;
     const int b = s / F, f = s - b * F;
 
-    __shared__ double2 sL[2][4][NP];      // multiplier columns of a panel
-    __shared__ int sP[2][4];              // pivot rows of a panel
-    __shared__ double2 sPiv[NP];
-    __shared__ int sKof[NP];
-    __shared__ double2 sU[NT][4][4][4];   // [group][step c][row in tile][col in tile]
-    __shared__ double2 sUu[NT][4][4];     // [group][step c][col in tile]: u_c of the group's columns
-    __shared__ double2 sW[2][4][4];       // W = (I + N)^-1, N[c][c'] = l_c'[p_c] (c' < c)
-    __shared__ double2 sRb[4][4];         // rhs tiles of the pivot-row owners
-    __shared__ int sFlag;
+    auto &sL = lds.sL;
+    auto &sP = lds.sP;
+    auto &sPiv = lds.sPiv;
+    auto &sKof = lds.sKof;
+    auto &sU = lds.sU;
+    auto &sUu = lds.sUu;
+    auto &sW = lds.sW;
+    auto &sRb = lds.sRb;
+    int &sFlag = lds.sFlag;
 
     if (t == 0) sFlag = 0;
     __syncthreads();
@@ -435,7 +448,8 @@ __global__ __launch_bounds__(GJShape<NP>::BLOCK) void k_gj(
     const double2 *__restrict__ rpart, int nchunk, double rscale, double2 *__restrict__ Iout,
     double *__restrict__ gsys, int32_t *__restrict__ status, bool or_status,
     GJFactor fac, bool fallback_only) {
-    gj_system<NP, ADJ>(blockIdx.x, n, S, F, M, Rv, phi, C, omega, Iin, rpart, nchunk, rscale,
+    __shared__ GjLds<NP> lds;
+    gj_system<NP, ADJ>(lds, blockIdx.x, n, S, F, M, Rv, phi, C, omega, Iin, rpart, nchunk, rscale,
                        Iout, gsys, status, or_status, fac, fallback_only);
 }
 
@@ -447,14 +461,63 @@ __device__ __forceinline__ int group_member(const SmallGroup &g, int sg) {
     return i;
 }
 
-// The forward fallback of a group's systems: one block per system, only those
-// the factorisation marked.
+// The forward fallback: workgroup i looks at the records of systems
+// kFbSystems i .. kFbSystems (i + 1) - 1 at once and eliminates the marked ones
+// (usually none) in turn.  One workgroup per system took 47 us to find
+// nothing among 86,016.
+constexpr int kFbSystems = 32;
+template <int NP, class Run>
+__device__ __forceinline__ void fallback_systems(int S, const Run &run, const int *fmt_at_thread) {
+    // fmt_at_thread: this thread's record word (threads below kFbSystems)
+    const int t = threadIdx.x;
+    __shared__ uint32_t sMask;
+    if (t < 64) {
+        const bool marked = fmt_at_thread && *fmt_at_thread == kFmtNeedsPivot;
+        const uint64_t m = __ballot(marked);
+        if (t == 0) sMask = (uint32_t)m;
+    }
+    __syncthreads();
+    uint32_t mask = sMask;
+    while (mask) {  // uniform
+        const int j = __ffs((int)mask) - 1;
+        mask &= mask - 1;
+        run(blockIdx.x * kFbSystems + j);
+        __syncthreads();
+    }
+}
+static_assert(kFbSystems == 32, "one bit per system");
+
 template <int NP>
-__global__ __launch_bounds__(GJShape<NP>::BLOCK) void k_gj_group(SmallGroup g) {
-    const int sg = blockIdx.x;
-    const SmallInst &e = g.in[group_member(g, sg)];
-    gj_system<NP, false>(sg - e.s0, e.n, e.S, e.F, e.M, e.R, e.phi, e.C, e.omega, nullptr, nullptr,
-                         0, 0.0, e.I, nullptr, e.status, false, e.fac, true);
+__global__ __launch_bounds__(GJShape<NP>::BLOCK) void k_gj_fallback(
+    int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
+    const double *__restrict__ phi, const double *__restrict__ C,
+    const double *__restrict__ omega, double2 *__restrict__ I, int32_t *__restrict__ status,
+    GJFactor fac) {
+    __shared__ GjLds<NP> lds;
+    const int s0 = blockIdx.x * kFbSystems + threadIdx.x;
+    auto run = [&](int s) {
+        gj_system<NP, false>(lds, s, n, S, F, M, Rv, phi, C, omega, nullptr, nullptr, 0, 0.0, I,
+                             nullptr, status, false, fac, true);
+    };
+    fallback_systems<NP>(S, run, threadIdx.x < kFbSystems && s0 < S ? fac.fmt + s0 : nullptr);
+}
+
+// The same over the S systems of a group.
+template <int NP>
+__global__ __launch_bounds__(GJShape<NP>::BLOCK) void k_gj_group(SmallGroup g, int S) {
+    __shared__ GjLds<NP> lds;
+    const int s0 = blockIdx.x * kFbSystems + threadIdx.x;
+    const int *fmt = nullptr;
+    if (threadIdx.x < kFbSystems && s0 < S) {
+        const SmallInst &e = g.in[group_member(g, s0)];
+        fmt = e.fac.fmt + (s0 - e.s0);
+    }
+    auto run = [&](int sg) {
+        const SmallInst &e = g.in[group_member(g, sg)];
+        gj_system<NP, false>(lds, sg - e.s0, e.n, e.S, e.F, e.M, e.R, e.phi, e.C, e.omega, nullptr,
+                             nullptr, 0, 0.0, e.I, nullptr, e.status, false, e.fac, true);
+    };
+    fallback_systems<NP>(S, run, fmt);
 }
 
 // Sum of a complex value over the 64 lanes of a wave (all lanes active):
@@ -662,8 +725,22 @@ __device__ __forceinline__ double2 ldl_backward(double2 x, const double2 *__rest
 // finite) is marked for the pivoted fallback.
 // The accumulators and the row state fit 256 registers, so two systems share
 // a SIMD: one wave's panel elimination runs while the other's MFMAs do.
+constexpr int kOneRound = 2048;  // systems resident at once: two waves on each of 1,024 SIMDs
+
+// One wave's LDS.  Panel rows (A, then L21) and V21 rows; a row holds 8 entries
+// padded to 9 (144 bytes), so that the row-per-lane accesses of 16 consecutive
+// lanes fall on disjoint LDS banks.
 template <int NP>
-__device__ __forceinline__ void ldl_system(
+struct LdlWaveLds {
+    double2 pan[NP][9], vv[NP][9];
+};
+// With KEEP (NP = 32) the lane's row of L stays in lrow (panel p, column 8 p +
+// c; zero on and above the diagonal and on padding) and z = D^-1 y in zout, for
+// a back substitution in the same wave; nothing is written to Z and status.
+// Returns whether the system needs the pivoted fallback; flag_out: input flags.
+template <int NP, bool KEEP>
+__device__ __forceinline__ bool ldl_system(
+    LdlWaveLds<NP> &lds, double2 (&lrow)[KEEP ? NP / 8 : 1][8], double2 &zout, int &flag_out,
     int s, int n, int F, const double *__restrict__ M, const double *__restrict__ Rv,
     const double *__restrict__ C, const double *__restrict__ omega,
     const double *__restrict__ phi, GJFactor fac, double2 *__restrict__ Z,
@@ -671,13 +748,8 @@ __device__ __forceinline__ void ldl_system(
     constexpr int NB = NP / 16;
     constexpr int NBLK = NB * (NB + 1) / 2;
     typedef double f64x4 __attribute__((ext_vector_type(4)));
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    // per wave: panel rows (A, then L21) and V21 rows; a row holds 8 entries
-    // padded to 9 (144 bytes), so that the row-per-lane accesses of 16
-    // consecutive lanes fall on disjoint LDS banks
+    const int lane = threadIdx.x & 63;
     constexpr int PW = 8;  // panel width
-    __shared__ double2 sPan[4][NP][PW + 1];
-    __shared__ double2 sV[4][NP][PW + 1];
     const int b = s / F, f = s - b * F;
     const double w = omega[f];
     const double *Cb = C + (size_t)b * n;
@@ -739,8 +811,14 @@ __device__ __forceinline__ void ldl_system(
     double2 y = lane < n ? loop_voltage(phi, n, lane, w) : make_double2(0.0, 0.0);
     double2 dk = make_double2(1.0, 0.0);  // D_i of the lane's own column
 
-    double2 (*pan)[PW + 1] = sPan[wv];
-    double2 (*vv)[PW + 1] = sV[wv];
+    auto &pan = lds.pan;
+    auto &vv = lds.vv;
+    if constexpr (KEEP) {
+#pragma unroll
+        for (int p = 0; p < NP / 8; ++p)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) lrow[p][c] = make_double2(0.0, 0.0);
+    }
     double2 *Ls = fac.L + (size_t)s * NP * NP;  // packed columns, see ldl_col
 #pragma unroll
     for (int bc = 0; bc < NB; ++bc) {
@@ -782,6 +860,14 @@ __device__ __forceinline__ void ldl_system(
             double2 l[PW];
 #pragma unroll
             for (int c = 0; c < PW; ++c) {
+                if (KEEP && k0 + c >= n) {  // uniform: identity padding, nothing below the diagonal
+                    l[c] = make_double2(0.0, 0.0);
+                    if (r < NP) {
+                        pan[r][c] = l[c];
+                        vv[r][c] = l[c];
+                    }
+                    continue;
+                }
                 double2 v = pan[rr][c];
                 double2 vc[PW];
 #pragma unroll
@@ -802,6 +888,11 @@ __device__ __forceinline__ void ldl_system(
                 }
                 __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
                 __builtin_amdgcn_wave_barrier();
+            }
+            if constexpr (KEEP) {
+#pragma unroll
+                for (int c = 0; c < PW; ++c)
+                    if (r > k0 + c && r < n) lrow[k0 / 8][c] = l[c];
             }
             // D_c = V_cc to the lane of column c
             if (r >= k0 && r < k0 + PW) dk = vv[r][r - k0];
@@ -850,26 +941,94 @@ __device__ __forceinline__ void ldl_system(
     double dmin = lane < n ? fabs(dk.x) + fabs(dk.y) : __builtin_inf();
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) dmin = fmin(dmin, __shfl_xor(dmin, off));
-    if (lane < n) Z[(size_t)s * n + lane] = cmul(y, dl);  // z = D^-1 L^-1 b
+    const bool pivot = (flag & COSIM_SYS_BAD_INPUT) || !(dmin >= 1e-5 * (double)zdiag);
+    zout = cmul(y, dl);  // z = D^-1 L^-1 b
+    flag_out = flag;
+    if (!KEEP && lane < n) Z[(size_t)s * n + lane] = zout;
     if (lane == 0) {
-        const bool pivot = (flag & COSIM_SYS_BAD_INPUT) || !(dmin >= 1e-5 * (double)zdiag);
-        status[s] = flag;
+        if (!KEEP) status[s] = flag;
         fac.fmt[s] = pivot ? kFmtNeedsPivot : kFmtLDL;
     }
+    return pivot;
+}
+
+// The whole forward solve of one system of at most 32 loops by one wave, the
+// block's only one: LDL^T, the back substitution from the rows of L in
+// registers, and the pivoted elimination if it is needed.  One launch in place
+// of three, and no read of the record: at these sizes the launches and the
+// memory round trips between them are the time (64 systems of one loop: 12.4
+// us in three launches).
+union Small32Lds {
+    LdlWaveLds<32> ldl;
+    struct {
+        double2 red[32 * 9], tr[128];
+    } bs;
+    GjLds<32> gj;
+    __device__ Small32Lds() {}
+};
+__device__ __forceinline__ void small32_system(
+    Small32Lds &lds, int s, int n, int S, int F, const double *__restrict__ M,
+    const double *__restrict__ Rv, const double *__restrict__ C, const double *__restrict__ omega,
+    const double *__restrict__ phi, const GJFactor &fac, double2 *__restrict__ I,
+    int32_t *__restrict__ status) {
+    const int lane = threadIdx.x;
+    double2 lrow[4][8], x;
+    int flag;
+    const bool pivot = ldl_system<32, true>(lds.ldl, lrow, x, flag, s, n, F, M, Rv, C, omega, phi,
+                                            fac, nullptr, nullptr);
+    __syncthreads();
+    if (pivot) {  // uniform
+        gj_system<32, false>(lds.gj, s, n, S, F, M, Rv, phi, C, omega, nullptr, nullptr, 0, 0.0, I,
+                             nullptr, status, false, fac, false);
+        return;
+    }
+    if (lane >= n) x = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int p = 3; p >= 0; --p) {
+        if (8 * p >= n) continue;  // uniform
+        int k1 = 8 * p + 8;
+        bs_block<32>(x, k1, lrow[p], lane, lds.bs.red, lds.bs.tr);
+    }
+    bool nonfinite = false;
+    if (lane < n) {
+        I[(size_t)s * n + lane] = x;
+        nonfinite = !(isfinite(x.x) && isfinite(x.y));
+    }
+    const bool any = __ballot(nonfinite) != 0;
+    if (lane == 0) status[s] = flag | (any ? COSIM_SYS_NONFINITE : 0);
+}
+// WPE waves per SIMD: 2 while every system is resident at once (no spills on
+// the single wave's way), 3 beyond (2,100 systems of 25 loops: 33 us against 39).
+template <int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void k_small32(
+    int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
+    const double *__restrict__ C, const double *__restrict__ omega,
+    const double *__restrict__ phi, GJFactor fac, double2 *__restrict__ I,
+    int32_t *__restrict__ status) {
+    __shared__ Small32Lds lds;
+    small32_system(lds, blockIdx.x, n, S, F, M, Rv, C, omega, phi, fac, I, status);
+}
+template <int WPE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void k_small32_group(
+    SmallGroup g) {
+    __shared__ Small32Lds lds;
+    const int sg = blockIdx.x;
+    const SmallInst &e = g.in[group_member(g, sg)];
+    small32_system(lds, sg - e.s0, e.n, e.S, e.F, e.M, e.R, e.C, e.omega, e.phi, e.fac, e.I,
+                   e.status);
 }
 
 // Forward solve of a system in the LDL^T format from the z the factorisation
 // left in I: x = L^-T z, written over it (systems handed to the pivoted
-// fallback are skipped; it writes their I).
+// fallback are skipped; it writes their I).  red, tr: as for ldl_backward.
 template <int NP>
 __device__ __forceinline__ void forward_system(int s, int n, GJFactor fac, double2 *__restrict__ I,
-                                               int32_t *__restrict__ status) {
-    __shared__ double2 sRed[4][NP * 9];
-    __shared__ double2 sTr[4][NP >= 64 ? 64 : 128];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+                                               int32_t *__restrict__ status, double2 *red,
+                                               double2 *tr) {
+    const int lane = threadIdx.x & 63;
     if (__builtin_amdgcn_readfirstlane(fac.fmt[s]) != kFmtLDL) return;
     double2 x = lane < n ? I[(size_t)s * n + lane] : make_double2(0.0, 0.0);
-    x = ldl_backward<NP, 2>(x, fac.L + (size_t)s * NP * NP, n, lane, sRed[wv], sTr[wv]);
+    x = ldl_backward<NP, 2>(x, fac.L + (size_t)s * NP * NP, n, lane, red, tr);
     bool nonfinite = false;
     if (lane < n) {
         I[(size_t)s * n + lane] = x;
@@ -883,39 +1042,64 @@ __global__ __launch_bounds__(256) void k_forward(int n, int S, GJFactor fac,
                                                  double2 *__restrict__ I,
                                                  int32_t *__restrict__ status) {
     const int s = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    __shared__ double2 sRed[4][NP * 9], sTr[4][64];
     if (s >= S) return;
-    forward_system<NP>(s, n, fac, I, status);
+    forward_system<NP>(s, n, fac, I, status, sRed[threadIdx.x >> 6], sTr[threadIdx.x >> 6]);
 }
 
-// One wave per system, four per block.
-template <int NP>
+// One wave per system, four per block.  With FWD the wave goes on to the back
+// substitution (forward_system) from the record it has just written: chosen
+// where all systems are resident at once (kOneRound), so that only latency
+// counts; for more, the separate launch hides the substitution's exchanges
+// better, with three to four waves per SIMD.
+template <int NP, bool FWD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_ldl(
     int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
     const double *__restrict__ C, const double *__restrict__ omega,
     const double *__restrict__ phi, GJFactor fac, double2 *__restrict__ Z,
     int32_t *__restrict__ status) {
+    __shared__ LdlWaveLds<NP> lds[4];
     const int s = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (s >= S) return;  // whole wave; the block never synchronises
-    ldl_system<NP>(s, n, F, M, Rv, C, omega, phi, fac, Z, status);
-}
-
-template <int NP>
-__global__ __launch_bounds__(256) void k_forward_group(SmallGroup g, int S) {
-    const int sg = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
-    if (sg >= S) return;
-    const SmallInst &e = g.in[group_member(g, sg)];
-    forward_system<NP>(sg - e.s0, e.n, e.fac, e.I, e.status);
+    double2 none[1][8], z;
+    int flag;
+    ldl_system<NP, false>(lds[threadIdx.x >> 6], none, z, flag, s, n, F, M, Rv, C, omega, phi, fac,
+                          Z, status);
+    if constexpr (FWD) {
+        __threadfence_block();  // this wave's record, z and status
+        LdlWaveLds<NP> &w = lds[threadIdx.x >> 6];
+        forward_system<NP>(s, n, fac, Z, status, &w.pan[0][0], &w.vv[0][0]);
+    }
 }
 
 // The same over the S systems of a group of plans (each wave resolves its own
 // member, so the waves of a block may serve different plans).
 template <int NP>
+__global__ __launch_bounds__(256) void k_forward_group(SmallGroup g, int S) {
+    const int sg = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    __shared__ double2 sRed[4][NP * 9], sTr[4][64];
+    if (sg >= S) return;
+    const SmallInst &e = g.in[group_member(g, sg)];
+    forward_system<NP>(sg - e.s0, e.n, e.fac, e.I, e.status, sRed[threadIdx.x >> 6],
+                       sTr[threadIdx.x >> 6]);
+}
+
+template <int NP, bool FWD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_ldl_group(
     SmallGroup g, int S) {
+    __shared__ LdlWaveLds<NP> lds[4];
     const int sg = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (sg >= S) return;
     const SmallInst &e = g.in[group_member(g, sg)];
-    ldl_system<NP>(sg - e.s0, e.n, e.F, e.M, e.R, e.C, e.omega, e.phi, e.fac, e.I, e.status);
+    double2 none[1][8], z;
+    int flag;
+    ldl_system<NP, false>(lds[threadIdx.x >> 6], none, z, flag, sg - e.s0, e.n, e.F, e.M, e.R, e.C,
+                          e.omega, e.phi, e.fac, e.I, e.status);
+    if constexpr (FWD) {
+        __threadfence_block();
+        LdlWaveLds<NP> &w = lds[threadIdx.x >> 6];
+        forward_system<NP>(sg - e.s0, e.n, e.fac, e.I, e.status, &w.pan[0][0], &w.vv[0][0]);
+    }
 }
 
 // Adjoint solve with a recorded factorisation, one wave per system, lane i
@@ -933,7 +1117,8 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
                                               const double2 *__restrict__ rpart, int nchunk,
                                               double rscale, double *__restrict__ gsys,
                                               double2 *__restrict__ mu,
-                                              int32_t *__restrict__ status) {
+                                              int32_t *__restrict__ status,
+                                              const FinalSums &fin) {
     __shared__ double2 sRed[4][NP * 9];  // per wave: the lane products of ldl_backward
     __shared__ double2 sTr[4][NP >= 64 ? 64 : 128];  // per wave: an 8x8 block of L, transposed
     const int lane = threadIdx.x & 63;
@@ -941,15 +1126,23 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
     const int b = s / F, f = s - b * F;
     const double w = omega[f];
     double2 x = make_double2(0.0, 0.0);
-    if (lane < n) {
+    {
+        // the chunks dealt to the 64 / w lanes that share entry k, w = 8, 16, 32
+        // or 64 >= n, and added across them by halves
+        const int w = n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 32 : 64;
+        const int k = lane & (w - 1);
         double rr = 0.0, ri = 0.0;
 #pragma unroll 8
-        for (int c = 0; c < nchunk; ++c) {  // loads ahead, sums in chunk order
-            const double2 v = rpart[((size_t)c * S + s) * NP + lane];
+        for (int c = lane / w; c < nchunk; c += 64 / w) {
+            const double2 v = rpart[((size_t)c * S + s) * NP + (k < NP ? k : 0)];
             rr += v.x;
             ri += v.y;
         }
-        x = make_double2(rscale * rr, -rscale * ri);
+        for (int off = 32; off >= w; off >>= 1) {
+            rr += __shfl_xor(rr, off);
+            ri += __shfl_xor(ri, off);
+        }
+        if (lane < n) x = make_double2(rscale * rr, -rscale * ri);
     }
     const double2 *__restrict__ Ls = fac.L + (size_t)s * NP * NP;
     constexpr int U = 8;
@@ -1020,9 +1213,17 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
         const double ck = C[(size_t)b * n + lane];
         // 2 Re(mu I / (j w C^2)) = 2 Im(mu I) / (w C^2)
         const double g = 2.0 * (x.x * Ik.y + x.y * Ik.x) / (w * ck * ck);
-        gsys[(size_t)s * n + lane] = g;
+        // with one frequency the system's term is the configuration's gradient
+        (fin.grad ? fin.grad : gsys)[(size_t)s * n + lane] = g;
         if (mu) mu[(size_t)s * n + lane] = x;
         nonfinite = !bad && !isfinite(g);
+    }
+    if (fin.grad) {  // and its partial losses the configuration's: the order of reduce_config
+        double acc = 0.0;
+        for (int c = lane; c < nchunk; c += 64) acc += fin.lpart[(size_t)c * S + s];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+        if (lane == 0) fin.loss[s] = fin.lscale * acc;
     }
     if (__ballot(nonfinite) != 0 && lane == 0) status[s] = flag | COSIM_SYS_NONFINITE;
 }
@@ -1036,10 +1237,11 @@ __global__ __launch_bounds__(256) void k_replay_adjoint(int n, int S, int F, GJF
                                                         int nchunk, double rscale,
                                                         double *__restrict__ gsys,
                                                         double2 *__restrict__ mu,
-                                                        int32_t *__restrict__ status) {
+                                                        int32_t *__restrict__ status,
+                                                        FinalSums fin) {
     const int s = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (s >= S) return;  // whole wave; no block-level synchronisation below
-    replay_system<NP>(s, n, S, F, fac, C, omega, I, rpart, nchunk, rscale, gsys, mu, status);
+    replay_system<NP>(s, n, S, F, fac, C, omega, I, rpart, nchunk, rscale, gsys, mu, status, fin);
 }
 
 template <int NP>
@@ -1048,40 +1250,54 @@ __global__ __launch_bounds__(256) void k_replay_adjoint_group(SmallGroup g, int 
     if (sg >= S) return;
     const SmallInst &e = g.in[group_member(g, sg)];
     replay_system<NP>(sg - e.s0, e.n, e.S, e.F, e.fac, e.C, e.omega, e.I, e.rpart, e.nchunk,
-                      e.rscale, e.gsys, e.mu, e.status);
+                      e.rscale, e.gsys, e.mu, e.status, FinalSums{});
 }
 
-// One 64-lane block per configuration b: dL/dC_b summed over frequencies per
-// loop, and the loss over frequencies and P-chunks, each lane taking every
-// 64th partial loss and the lanes combined by a fixed shuffle tree (both
-// orders are fixed, so repeated calls agree bit for bit).
+// One block per configuration b: dL/dC_b summed over frequencies per loop, and
+// the loss over frequencies and P-chunks, each thread taking every kTR-th
+// partial loss, the lanes of a wave combined by a fixed shuffle tree and the
+// waves in order (every order is fixed, so repeated calls agree bit for bit;
+// up to 64 partial losses it is the sum of the first wave alone, as
+// replay_system forms it).
+constexpr int kTR = 256;
 __device__ __forceinline__ void reduce_config(int b, int n, int B, int F, int nchunk,
                                               const double *__restrict__ gsys,
                                               const double *__restrict__ lpart, double lscale,
                                               double *__restrict__ grad,
                                               double *__restrict__ loss) {
+    __shared__ double sw[kTR / 64];
     const int S = B * F;
+    double part = 0.0;
+    if (loss) {
+        const int m = F * nchunk;
+#pragma unroll 4
+        for (int e = threadIdx.x; e < m; e += kTR) {
+            const int c = e / F, f = e - c * F;  // consecutive lanes: consecutive f
+            part += lpart[(size_t)c * S + (size_t)b * F + f];
+        }
+    }
     if (grad) {
-        for (int k = threadIdx.x; k < n; k += blockDim.x) {
+        for (int k = threadIdx.x; k < n; k += kTR) {
             double acc = 0.0;
+#pragma unroll 4
             for (int f = 0; f < F; ++f) acc += gsys[((size_t)b * F + f) * n + k];
             grad[(size_t)b * n + k] = acc;
         }
     }
     if (loss) {
-        const int m = F * nchunk;
-        double acc = 0.0;
-        for (int e = threadIdx.x; e < m; e += 64) {
-            const int c = e / F, f = e - c * F;  // consecutive lanes: consecutive f
-            acc += lpart[(size_t)c * S + (size_t)b * F + f];
-        }
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
-        if (threadIdx.x == 0) loss[b] = lscale * acc;
+        for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
+        if ((threadIdx.x & 63) == 0) sw[threadIdx.x >> 6] = part;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int w = 1; w < kTR / 64; ++w) part += sw[w];
+            loss[b] = lscale * part;
+        }
     }
 }
 
-__global__ __launch_bounds__(64) void k_reduce(int n, int B, int F, int nchunk,
+__global__ __launch_bounds__(kTR) void k_reduce(int n, int B, int F, int nchunk,
                                                const double *__restrict__ gsys,
                                                const double *__restrict__ lpart, double lscale,
                                                double *__restrict__ grad,
@@ -1089,7 +1305,7 @@ __global__ __launch_bounds__(64) void k_reduce(int n, int B, int F, int nchunk,
     reduce_config(blockIdx.x, n, B, F, nchunk, gsys, lpart, lscale, grad, loss);
 }
 
-__global__ __launch_bounds__(64) void k_reduce_group(ReduceGroup g) {
+__global__ __launch_bounds__(kTR) void k_reduce_group(ReduceGroup g) {
     const int bg = blockIdx.x;
     int i = 0;
     while (i + 1 < g.count && bg >= g.in[i + 1].b0) ++i;
@@ -1136,42 +1352,45 @@ hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const doub
     const dim3 grid((S + 3) / 4);
     switch (NP) {
         case 32:
-            hipLaunchKernelGGL(k_ldl<32>, grid, dim3(256), 0, st, n, S, F, M_d, R_d, C_d, omega_d,
-                               phi_d, fac, I_d, status_d);
-            hipLaunchKernelGGL(k_forward<32>, grid, dim3(256), 0, st, n, S, fac, I_d, status_d);
-            break;
+            if (S <= kOneRound)
+                hipLaunchKernelGGL(k_small32<2>, dim3(S), dim3(64), 0, st, n, S, F, M_d, R_d, C_d,
+                                   omega_d, phi_d, fac, I_d, status_d);
+            else
+                hipLaunchKernelGGL(k_small32<3>, dim3(S), dim3(64), 0, st, n, S, F, M_d, R_d, C_d,
+                                   omega_d, phi_d, fac, I_d, status_d);
+            return hipGetLastError();
         case 64:
-            hipLaunchKernelGGL(k_ldl<64>, grid, dim3(256), 0, st, n, S, F, M_d, R_d, C_d, omega_d,
-                               phi_d, fac, I_d, status_d);
-            hipLaunchKernelGGL(k_forward<64>, grid, dim3(256), 0, st, n, S, fac, I_d, status_d);
+            if (S <= kOneRound) {
+                hipLaunchKernelGGL((k_ldl<64, true>), grid, dim3(256), 0, st, n, S, F, M_d, R_d,
+                                   C_d, omega_d, phi_d, fac, I_d, status_d);
+            } else {
+                hipLaunchKernelGGL((k_ldl<64, false>), grid, dim3(256), 0, st, n, S, F, M_d, R_d,
+                                   C_d, omega_d, phi_d, fac, I_d, status_d);
+                hipLaunchKernelGGL(k_forward<64>, grid, dim3(256), 0, st, n, S, fac, I_d, status_d);
+            }
             break;
         default:
             return hipErrorInvalidValue;
     }
+    hipLaunchKernelGGL(k_gj_fallback<64>, dim3((S + kFbSystems - 1) / kFbSystems),
+                       dim3(GJShape<64>::BLOCK), 0, st, n, S, F, M_d, R_d, phi_d, C_d, omega_d, I_d,
+                       status_d, fac);
     return hipGetLastError();
-}
-
-hipError_t launch_solve_fallback(int NP, int n, int S, int F, const double *M_d,
-                                 const double *R_d, const double *phi_d, const double *C_d,
-                                 const double *omega_d, double2 *I_d, int32_t *status_d,
-                                 GJFactor fac, hipStream_t st) {
-    return launch_gj<false>(NP, n, S, F, M_d, R_d, phi_d, C_d, omega_d, nullptr, nullptr, 0, 0.0,
-                            I_d, nullptr, status_d, false, fac, true, st);
 }
 
 hipError_t launch_replay_adjoint(int NP, int n, int S, int F, GJFactor fac, const double *C_d,
                                  const double *omega_d, double2 *I_d, const double2 *rpart_d,
                                  int nchunk, double rscale, double *gsys_d, double2 *mu_d,
-                                 int32_t *status_d, hipStream_t st) {
+                                 int32_t *status_d, hipStream_t st, const FinalSums &fin) {
     const dim3 grid((S + 3) / 4);
     switch (NP) {
         case 32:
             hipLaunchKernelGGL(k_replay_adjoint<32>, grid, dim3(256), 0, st, n, S, F, fac, C_d,
-                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d);
+                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d, fin);
             break;
         case 64:
             hipLaunchKernelGGL(k_replay_adjoint<64>, grid, dim3(256), 0, st, n, S, F, fac, C_d,
-                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d);
+                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d, fin);
             break;
         default:
             return hipErrorInvalidValue;
@@ -1191,14 +1410,14 @@ hipError_t launch_solve_adjoint(int NP, int n, int S, int F, const double *M_d,
 hipError_t launch_reduce(int n, int B, int F, int nchunk, const double *gsys_d,
                          const double *lpart_d, double lscale, double *grad_d, double *loss_d,
                          hipStream_t st) {
-    hipLaunchKernelGGL(k_reduce, dim3(B), dim3(64), 0, st, n, B, F, nchunk, gsys_d, lpart_d,
+    hipLaunchKernelGGL(k_reduce, dim3(B), dim3(kTR), 0, st, n, B, F, nchunk, gsys_d, lpart_d,
                        lscale, grad_d, loss_d);
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_group(const ReduceGroup &g, int Btot, hipStream_t st) {
     if (Btot <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_reduce_group, dim3(Btot), dim3(64), 0, st, g);
+    hipLaunchKernelGGL(k_reduce_group, dim3(Btot), dim3(kTR), 0, st, g);
     return hipGetLastError();
 }
 
@@ -1206,30 +1425,32 @@ hipError_t launch_small_group(int NP, const SmallGroup &g, int S, SmallPhase pha
                               hipStream_t st) {
     if (S <= 0) return hipSuccess;
     const dim3 wave_grid((S + 3) / 4);
-#define COSIM_SMALL_GROUP(NPC)                                                                   \
-    switch (phase) {                                                                             \
-        case SmallPhase::Factor:                                                                 \
-            hipLaunchKernelGGL(k_ldl_group<NPC>, wave_grid, dim3(256), 0, st, g, S);             \
-            hipLaunchKernelGGL(k_forward_group<NPC>, wave_grid, dim3(256), 0, st, g, S);         \
-            break;                                                                               \
-        case SmallPhase::Fallback:                                                               \
-            hipLaunchKernelGGL(k_gj_group<NPC>, dim3(S), dim3(GJShape<NPC>::BLOCK), 0, st, g);   \
-            break;                                                                               \
-        case SmallPhase::Adjoint:                                                                \
-            hipLaunchKernelGGL(k_replay_adjoint_group<NPC>, wave_grid, dim3(256), 0, st, g, S);   \
-            break;                                                                               \
-    }
-    switch (NP) {
-        case 32:
-            COSIM_SMALL_GROUP(32)
+    if (NP != 32 && NP != 64) return hipErrorInvalidValue;
+    switch (phase) {
+        case SmallPhase::Factor:
+            if (NP == 32) {
+                if (S <= kOneRound)
+                    hipLaunchKernelGGL(k_small32_group<2>, dim3(S), dim3(64), 0, st, g);
+                else
+                    hipLaunchKernelGGL(k_small32_group<3>, dim3(S), dim3(64), 0, st, g);
+                break;
+            }
+            if (S <= kOneRound) {
+                hipLaunchKernelGGL((k_ldl_group<64, true>), wave_grid, dim3(256), 0, st, g, S);
+            } else {
+                hipLaunchKernelGGL((k_ldl_group<64, false>), wave_grid, dim3(256), 0, st, g, S);
+                hipLaunchKernelGGL(k_forward_group<64>, wave_grid, dim3(256), 0, st, g, S);
+            }
+            hipLaunchKernelGGL(k_gj_group<64>, dim3((S + kFbSystems - 1) / kFbSystems),
+                               dim3(GJShape<64>::BLOCK), 0, st, g, S);
             break;
-        case 64:
-            COSIM_SMALL_GROUP(64)
+        case SmallPhase::Adjoint:
+            if (NP == 32)
+                hipLaunchKernelGGL(k_replay_adjoint_group<32>, wave_grid, dim3(256), 0, st, g, S);
+            else
+                hipLaunchKernelGGL(k_replay_adjoint_group<64>, wave_grid, dim3(256), 0, st, g, S);
             break;
-        default:
-            return hipErrorInvalidValue;
     }
-#undef COSIM_SMALL_GROUP
     return hipGetLastError();
 }
 
