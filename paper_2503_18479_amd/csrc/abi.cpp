@@ -74,10 +74,151 @@ GLRule make_gl_rule() {
     return r;
 }
 
+// Appends to `out` the vertices of the closed polygon v[0 .. n) that remain
+// when straight runs of segments are merged: field and flux of a straight
+// filament do not depend on where it is cut, and every segment costs the same
+// in assembly (a square of 32 segments: 8 times less for G, 64 times for M).
+// A run ends where a vertex turns back or lies further from the chord than the
+// rounding of the coordinates, 4 units in the last place of the loop's
+// largest.  The first vertex kept is one where the polygon turns.
+void merge_straight(const double *v, int n, std::vector<double> &out) {
+    double big = 0.0;
+    for (int i = 0; i < 3 * n; ++i) big = std::max(big, std::fabs(v[i]));
+    const double tol = 4.0 * 2.220446049250313e-16 * big;
+    // whether the vertices strictly between a and b (indices modulo n, b > a)
+    // lie on the segment a -> b in order
+    auto straight = [&](int a, int b) {
+        const double *p = v + 3 * (a % n), *q = v + 3 * (b % n);
+        const double d[3] = {q[0] - p[0], q[1] - p[1], q[2] - p[2]};
+        const double L2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+        if (!(L2 > 0.0)) return false;
+        double last = 0.0;
+        for (int i = a + 1; i < b; ++i) {
+            const double *r = v + 3 * (i % n);
+            const double w[3] = {r[0] - p[0], r[1] - p[1], r[2] - p[2]};
+            const double t = (w[0] * d[0] + w[1] * d[1] + w[2] * d[2]) / L2;
+            double off = 0.0;
+            for (int c = 0; c < 3; ++c) off = std::max(off, std::fabs(w[c] - t * d[c]));
+            if (!(t > last && t < 1.0 && off <= tol)) return false;
+            last = t;
+        }
+        return true;
+    };
+    int start = 0;
+    while (start < n && straight(start + n - 1, start + n + 1)) ++start;
+    std::vector<int> keep;
+    if (start < n)
+        for (int a = start; a < start + n;) {
+            keep.push_back(a % n);
+            // the run as far as each vertex continues its neighbours' segments,
+            // then (a slow bend) as far as it is straight as a whole
+            int b = a + 1;
+            while (b < start + n && straight(b - 1, b + 1)) ++b;
+            if (!straight(a, b)) {
+                b = a + 1;
+                while (b < start + n && straight(a, b + 1)) ++b;
+            }
+            a = b;
+        }
+    if (keep.size() < 3) {  // degenerate: as given
+        keep.resize(n);
+        for (int i = 0; i < n; ++i) keep[i] = i;
+    }
+    for (int i : keep) out.insert(out.end(), v + 3 * i, v + 3 * i + 3);
+}
+
 template <typename T>
 void dfree(T *&p) {
     if (p) (void)hipFree((void *)p);
     p = nullptr;
+}
+
+// Device blocks of destroyed plans' operators, kept for the next plan: a new
+// allocation of some hundred MB has to be mapped and, once the memory that
+// the driver holds cleared is used up, cleared at about 36 GB/s (15 ms for
+// the 539 MB of 256 loops at 65,536 points, where assembly takes 0.4 ms).  At most
+// kPoolBlocks blocks and kPoolBytes in all; the oldest go back first, and all
+// of a device's when an allocation there fails.  A block is handed out after
+// the device has been waited for (whatever still ran on it when its plan was
+// destroyed, on any stream, has ended), within cosim_assemble, which waits
+// itself.
+struct BlockPool {
+    struct Block {
+        int device;
+        void *p;
+        size_t bytes;
+    };
+    static constexpr size_t kPoolBlocks = 8, kPoolBytes = (size_t)1 << 30;
+    std::mutex mu;
+    std::vector<Block> idle;  // oldest first
+    size_t total = 0;
+
+    Block remove(size_t i) {
+        const Block b = idle[i];
+        idle.erase(idle.begin() + i);
+        total -= b.bytes;
+        return b;
+    }
+    // A block of at least `bytes` on the current device; *got: its size.
+    hipError_t take(int device, size_t bytes, void **out, size_t *got) {
+        bytes = (bytes + 65535) / 65536 * 65536;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            size_t best = idle.size();
+            for (size_t i = 0; i < idle.size(); ++i)
+                if (idle[i].device == device && idle[i].bytes >= bytes &&
+                    idle[i].bytes <= bytes + bytes / 4 &&
+                    (best == idle.size() || idle[i].bytes < idle[best].bytes))
+                    best = i;
+            if (best < idle.size()) {
+                const Block b = remove(best);
+                *out = b.p;
+                *got = b.bytes;
+            } else {
+                *out = nullptr;
+            }
+        }
+        if (*out) {
+            const hipError_t e = hipDeviceSynchronize();
+            if (e != hipSuccess) {
+                (void)hipFree(*out);
+                *out = nullptr;
+            }
+            return e;
+        }
+        *got = bytes;
+        hipError_t e = hipMalloc(out, bytes);
+        if (e == hipSuccess) return e;
+        (void)hipGetLastError();
+        std::vector<Block> back;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            for (size_t i = idle.size(); i-- > 0;)
+                if (idle[i].device == device) back.push_back(remove(i));
+        }
+        if (back.empty()) {
+            *out = nullptr;
+            return e;
+        }
+        for (const Block &b : back) (void)hipFree(b.p);
+        if ((e = hipMalloc(out, bytes)) != hipSuccess) *out = nullptr;
+        return e;
+    }
+    void give(int device, void *p, size_t bytes) {
+        if (!p) return;
+        std::vector<Block> back;
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            idle.push_back(Block{device, p, bytes});
+            total += bytes;
+            while (idle.size() > kPoolBlocks || total > kPoolBytes) back.push_back(remove(0));
+        }
+        for (const Block &b : back) (void)hipFree(b.p);  // waits for the device
+    }
+};
+BlockPool &block_pool() {
+    static BlockPool *pool = new BlockPool;  // never destroyed: plans may outlive static objects
+    return *pool;
 }
 
 void plan_free_workspace(cosim_plan *p) {
@@ -512,6 +653,12 @@ int cosim_geometry_create(int n_loops, const int32_t *seg_off, const double *ver
         }
         g->area_z[k] = 0.5 * acc;
     }
+    g->mseg_off.assign(1, 0);
+    for (int k = 0; k < n_loops; ++k) {
+        merge_straight(g->verts.data() + 3 * (size_t)seg_off[k], seg_off[k + 1] - seg_off[k],
+                       g->mverts);
+        g->mseg_off.push_back((int32_t)(g->mverts.size() / 3));
+    }
     *out = g;
     return COSIM_OK;
 }
@@ -577,12 +724,7 @@ int cosim_assemble_component(cosim_geom_t g, int P, const double *pts_d, double 
     const bool want64 = precisions & (1 << COSIM_FP64), want32 = precisions & (1 << COSIM_FP32);
     const bool want16 = precisions & (1 << COSIM_BF16X3);
 
-    int32_t *seg_d = nullptr;
-    double *verts_d = nullptr, *wa_d = nullptr;
     auto cleanup = [&](int code) {
-        dfree(seg_d);
-        dfree(verts_d);
-        dfree(wa_d);
         if (code != COSIM_OK) {
             cosim_plan_destroy(p);
             (void)hipGetLastError();
@@ -594,25 +736,59 @@ int cosim_assemble_component(cosim_geom_t g, int P, const double *pts_d, double 
         return cleanup(fail(COSIM_EDEVICE, "hipGetDevice failed"));
     const size_t gsz = (size_t)p->P_pad * p->NP;
     const size_t n = (size_t)g->n;
-    // every precision keeps G row-major and transposed: the fused kernels read
+    // Every precision keeps G row-major and transposed: the fused kernels read
     // the bf16 transposed copy, the matrix-core contraction kernel every
-    // precision's (the adjoint's operands are runs of points of one loop)
-    if ((want64 && (hipMalloc((void **)&p->G64, gsz * sizeof(double)) != hipSuccess ||
-                    hipMalloc((void **)&p->GT64, gsz * sizeof(double)) != hipSuccess)) ||
-        (want32 && (hipMalloc((void **)&p->G32, gsz * sizeof(float)) != hipSuccess ||
-                    hipMalloc((void **)&p->GT32, gsz * sizeof(float)) != hipSuccess)) ||
-        (want16 && (hipMalloc((void **)&p->Ghi, gsz * sizeof(uint16_t)) != hipSuccess ||
-                    hipMalloc((void **)&p->Glo, gsz * sizeof(uint16_t)) != hipSuccess ||
-                    hipMalloc((void **)&p->GThi, gsz * sizeof(uint16_t)) != hipSuccess ||
-                    hipMalloc((void **)&p->GTlo, gsz * sizeof(uint16_t)) != hipSuccess)) ||
-        hipMalloc((void **)&p->M_d, n * n * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&p->phi_d, 3 * n * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&p->R_d, n * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&p->T_ratio, (size_t)P * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&seg_d, (n + 1) * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc((void **)&verts_d, 3 * (size_t)g->V * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&wa_d, n * sizeof(double)) != hipSuccess)
+    // precision's (the adjoint's operands are runs of points of one loop).
+    // One allocation holds all of it, and one copy brings the host's part (R,
+    // the excitation, wire radii, vertices, offsets): every allocation, free
+    // and small copy costs tens of microseconds.
+    size_t bytes = 0;
+    auto take = [&](size_t count, size_t size) {
+        const size_t at = bytes;
+        bytes += (count * size + 255) / 256 * 256;
+        return at;
+    };
+    const size_t oG64 = take(want64 ? gsz : 0, 8), oGT64 = take(want64 ? gsz : 0, 8);
+    const size_t oG32 = take(want32 ? gsz : 0, 4), oGT32 = take(want32 ? gsz : 0, 4);
+    const size_t oGhi = take(want16 ? gsz : 0, 2), oGlo = take(want16 ? gsz : 0, 2);
+    const size_t oGThi = take(want16 ? gsz : 0, 2), oGTlo = take(want16 ? gsz : 0, 2);
+    const size_t oM = take(n * n, 8), oT = take((size_t)P, 8);
+    const size_t oHost = bytes;
+    const size_t oR = take(n, 8), oPhi = take(3 * n, 8), oWa = take(n, 8);
+    const size_t oVerts = take(g->mverts.size(), 8), oSeg = take(n + 1, sizeof(int32_t));
+    if (block_pool().take(p->device, bytes, &p->arena, &p->arena_bytes) != hipSuccess) {
+        p->arena = nullptr;
         return cleanup(fail(COSIM_ENOMEM, "device allocation for the operators failed"));
+    }
+    char *base = (char *)p->arena;
+    if (want64) {
+        p->G64 = (double *)(base + oG64);
+        p->GT64 = (double *)(base + oGT64);
+    }
+    if (want32) {
+        p->G32 = (float *)(base + oG32);
+        p->GT32 = (float *)(base + oGT32);
+    }
+    if (want16) {
+        p->Ghi = (uint16_t *)(base + oGhi);
+        p->Glo = (uint16_t *)(base + oGlo);
+        p->GThi = (uint16_t *)(base + oGThi);
+        p->GTlo = (uint16_t *)(base + oGTlo);
+    }
+    p->M_d = (double *)(base + oM);
+    p->T_ratio = (double *)(base + oT);
+    p->R_d = (double *)(base + oR);
+    p->phi_d = (double *)(base + oPhi);
+    const double *wa_d = (const double *)(base + oWa), *verts_d = (const double *)(base + oVerts);
+    const int32_t *seg_d = (const int32_t *)(base + oSeg);
+    std::vector<char> host(bytes - oHost, 0);
+    std::memcpy(host.data() + (oR - oHost), g->R.data(), n * 8);
+    std::memcpy(host.data() + (oPhi - oHost), p->exc_h.data(), 3 * n * 8);
+    std::memcpy(host.data() + (oWa - oHost), g->wire_a.data(), n * 8);
+    std::memcpy(host.data() + (oVerts - oHost), g->mverts.data(), g->mverts.size() * 8);
+    std::memcpy(host.data() + (oSeg - oHost), g->mseg_off.data(), (n + 1) * sizeof(int32_t));
+    int max_segs = 0;
+    for (int k = 0; k < g->n; ++k) max_segs = std::max(max_segs, g->mseg_off[k + 1] - g->mseg_off[k]);
     hipError_t e = hipSuccess;
 #define ASM_TRY(x)                                                                      \
     do {                                                                                \
@@ -620,14 +796,10 @@ int cosim_assemble_component(cosim_geom_t g, int P, const double *pts_d, double 
         if (e != hipSuccess)                                                            \
             return cleanup(fail(COSIM_EDEVICE, "%s failed: %s", #x, hipGetErrorString(e))); \
     } while (0)
-    ASM_TRY(hipMemcpyAsync(seg_d, g->seg_off.data(), (n + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    ASM_TRY(hipMemcpyAsync(verts_d, g->verts.data(), 3 * (size_t)g->V * sizeof(double), hipMemcpyHostToDevice, st));
-    ASM_TRY(hipMemcpyAsync(wa_d, g->wire_a.data(), n * sizeof(double), hipMemcpyHostToDevice, st));
-    ASM_TRY(hipMemcpyAsync(p->R_d, g->R.data(), n * sizeof(double), hipMemcpyHostToDevice, st));
-    ASM_TRY(hipMemcpyAsync(p->phi_d, p->exc_h.data(), 3 * n * sizeof(double), hipMemcpyHostToDevice, st));
+    ASM_TRY(hipMemcpyAsync(base + oHost, host.data(), host.size(), hipMemcpyHostToDevice, st));
     ASM_TRY(launch_assemble_G(g->n, p->NP, P, p->P_pad, component, seg_d, verts_d, pts_d, p->G64,
                               p->G32, p->Ghi, p->Glo, p->GT64, p->GT32, p->GThi, p->GTlo, st));
-    ASM_TRY(launch_assemble_M(g->n, seg_d, verts_d, wa_d, make_gl_rule(), p->M_d, st));
+    ASM_TRY(launch_assemble_M(g->n, max_segs, seg_d, verts_d, wa_d, make_gl_rule(), p->M_d, st));
     p->M_h.resize(n * n);
     ASM_TRY(hipMemcpyAsync(p->M_h.data(), p->M_d, n * n * sizeof(double), hipMemcpyDeviceToHost, st));
     ASM_TRY(hipStreamSynchronize(st));
@@ -641,18 +813,8 @@ int cosim_plan_destroy(cosim_plan_t p) {
     if (!p) return COSIM_OK;
     for (hipEvent_t e : p->events) (void)hipEventDestroy(e);
     p->events.clear();
-    dfree(p->G64);
-    dfree(p->GT64);
-    dfree(p->G32);
-    dfree(p->GT32);
-    dfree(p->Ghi);
-    dfree(p->Glo);
-    dfree(p->GThi);
-    dfree(p->GTlo);
-    dfree(p->M_d);
-    dfree(p->phi_d);
-    dfree(p->R_d);
-    dfree(p->T_ratio);
+    block_pool().give(p->device, p->arena, p->arena_bytes);
+    p->arena = nullptr;
     plan_free_workspace(p);
     // the parameter-gradient workspace has its own lifetime: a growing regular
     // workspace must not free it while a call still holds its address

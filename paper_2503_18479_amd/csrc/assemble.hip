@@ -1,6 +1,10 @@
 // One-time operator assembly on gfx950: the Biot-Savart field matrix G and
 // the Neumann inductance matrix M.  Both are plain-ALU kernels (FP64 sqrt,
-// division and asinh dominate); they run once per geometry and point set.
+// division and asinh dominate); they run once per geometry and point set, on
+// the loops with straight runs of segments merged (merge_straight in abi.cpp).
+#include <type_traits>
+
+#include "epilogue.h"
 #include "internal.h"
 
 namespace cosim {
@@ -16,38 +20,58 @@ __device__ inline uint16_t bf16_rne(float x) {
 }
 __device__ inline float bf16_to_f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
+// 1/x from the hardware reciprocal and two Newton steps (about 1 ulp), by
+// division outside the range where they are safe.
+__device__ inline double rcp_safe(double x) {
+    if (__builtin_expect(x > 1e-280 && x < 1e280, 1)) {
+        double r = __builtin_amdgcn_rcp(x);
+        r = fma(r, fma(-x, r, 1.0), r);
+        return fma(r, fma(-x, r, 1.0), r);
+    }
+    return 1.0 / x;
+}
+
+// Vector from a point to a vertex, its length and the reciprocal of that.
+struct Arm {
+    double x, y, z, l, il;
+};
+__device__ inline Arm arm(double x, double y, double z) {
+    Arm a{x, y, z, 0.0, 0.0};
+    mag_inv(fma(x, x, fma(y, y, z * z)), a.l, a.il);
+    return a;
+}
+
 // Cartesian component `comp` (0 x, 1 y, 2 z) of the field per ampere of the
 // straight filament v1 -> v2 at point p.  With a = v1 - p, b = v2 - p:
 //   mu0/(4pi) (a x b)_comp (|a|+|b|) / (|a||b| (|a||b| + a.b)).
 // For a.b < 0 the last factor is evaluated as (|a||b| - a.b)/|a x b|^2, its
 // equal that does not cancel beside the filament.
-__device__ inline double b_filament(int comp, double ax, double ay, double az, double la,
-                                    double bx, double by, double bz, double lb) {
-    double cx = ay * bz - az * by;
-    double cy = az * bx - ax * bz;
-    double cz = ax * by - ay * bx;
-    double dot = ax * bx + ay * by + az * bz;
-    double ab = la * lb;
-    double inv;
-    if (dot >= 0.0) {
-        inv = 1.0 / (ab + dot);
-    } else {
-        inv = (ab - dot) / (cx * cx + cy * cy + cz * cz);
-    }
+__device__ inline double b_filament(int comp, const Arm &a, const Arm &b) {
+    const double cx = a.y * b.z - a.z * b.y;
+    const double cy = a.z * b.x - a.x * b.z;
+    const double cz = a.x * b.y - a.y * b.x;
+    const double dot = a.x * b.x + a.y * b.y + a.z * b.z;
+    const double ab = a.l * b.l;
+    const double num = dot >= 0.0 ? 1.0 : ab - dot;
+    const double den = dot >= 0.0 ? ab + dot : cx * cx + cy * cy + cz * cz;
     const double cc = comp == 2 ? cz : comp == 1 ? cy : cx;
-    return cc * (la + lb) * inv / ab;
+    return cc * (a.l + b.l) * (num * rcp_safe(den)) * (a.il * b.il);
 }
 
-// Block: 64 points x 4 waves.  Wave w evaluates loops w, w+4, ... for the 64
-// points of its lanes (every lane of a wave walks the same vertices, so each
-// vertex load is one cache line for the whole wave), one chunk of 64 loops at a time; each chunk of
-// the block tile [64][64] is staged in LDS and written out row-major, so that
-// a row segment of G is one contiguous store, and transposed, so that a
-// column segment of each transposed copy is one too.  Copies the plan did not
-// ask for are null and skipped.
+// Block: 64 points x one chunk of KC = 32 or 64 loops (grid: points x chunks),
+// 4 waves.  Wave w evaluates loops w, w+4, ... for the 64 points of its lanes
+// (every lane of a wave walks the same vertices, so each vertex load is one
+// cache line for the whole wave); the tile [64][KC] is staged in LDS and written
+// out in 16-byte stores, row-major and transposed, so that a row segment of G
+// and a column segment of each transposed copy are contiguous runs.  Copies
+// the plan did not ask for are null and skipped.
+//   FP64 vector work and the stores take about the same time: 256 loops of
+// four segments at 65,536 points, every copy (539 MB), 224 us (square root and
+// two divisions per segment, 8-byte and smaller stores: 261 us; 32 segments per
+// loop: 1.81 ms).
 constexpr int kGPts = 64;
-constexpr int kGLoops = 64;
 
+template <int KC>
 __global__ __launch_bounds__(256) void k_assemble_G(int n, int NP, int P, int P_pad, int comp,
                                                     const int32_t *__restrict__ seg_off,
                                                     const double *__restrict__ verts,
@@ -60,82 +84,78 @@ __global__ __launch_bounds__(256) void k_assemble_G(int n, int NP, int P, int P_
                                                     float *__restrict__ GT32,
                                                     uint16_t *__restrict__ GThi,
                                                     uint16_t *__restrict__ GTlo) {
-    __shared__ double tile[kGPts][kGLoops + 1];
+    __shared__ double tile[kGPts][KC + 1];
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int p = blockIdx.x * kGPts + lane;
+    const int p0 = blockIdx.x * kGPts, k0 = blockIdx.y * KC;
+    const int p = p0 + lane;
     double px = 0.0, py = 0.0, pz = 0.0;
     if (p < P) {
-        px = pts[3 * p + 0];
-        py = pts[3 * p + 1];
-        pz = pts[3 * p + 2];
+        px = pts[3 * (size_t)p + 0];
+        py = pts[3 * (size_t)p + 1];
+        pz = pts[3 * (size_t)p + 2];
     }
-    const int prow0 = blockIdx.x * kGPts;
-    for (int k0 = 0; k0 < NP; k0 += kGLoops) {
-        const int kc = min(kGLoops, NP - k0);
-        for (int kk = wave; kk < kc; kk += 4) {
-            const int k = k0 + kk;
-            double acc = 0.0;
-            if (k < n && p < P) {
-                const int v0 = seg_off[k], v1 = seg_off[k + 1];
-                // first vertex relative to p; distances are shared by neighbouring segments
-                double fx = verts[3 * v0 + 0] - px, fy = verts[3 * v0 + 1] - py,
-                       fz = verts[3 * v0 + 2] - pz;
-                double fl = sqrt(fx * fx + fy * fy + fz * fz);
-                double ax = fx, ay = fy, az = fz, la = fl;
-                for (int v = v0 + 1; v <= v1; ++v) {
-                    double bx, by, bz, lb;
-                    if (v < v1) {
-                        bx = verts[3 * v + 0] - px;
-                        by = verts[3 * v + 1] - py;
-                        bz = verts[3 * v + 2] - pz;
-                        lb = sqrt(bx * bx + by * by + bz * bz);
-                    } else {  // closing segment back to the first vertex
-                        bx = fx; by = fy; bz = fz; lb = fl;
-                    }
-                    acc += b_filament(comp, ax, ay, az, la, bx, by, bz, lb);
-                    ax = bx; ay = by; az = bz; la = lb;
-                }
-                acc *= kMu0Over4Pi;
+    for (int kk = wave; kk < KC; kk += 4) {
+        const int k = k0 + kk;
+        double acc = 0.0;
+        if (k < n && p < P) {
+            const int v0 = seg_off[k], v1 = seg_off[k + 1];
+            // distances are shared by neighbouring segments
+            const Arm first = arm(verts[3 * v0] - px, verts[3 * v0 + 1] - py, verts[3 * v0 + 2] - pz);
+            Arm a = first;
+            for (int v = v0 + 1; v < v1; ++v) {
+                const Arm b = arm(verts[3 * v] - px, verts[3 * v + 1] - py, verts[3 * v + 2] - pz);
+                acc += b_filament(comp, a, b);
+                a = b;
             }
-            tile[lane][kk] = acc;
+            acc += b_filament(comp, a, first);  // closing segment
+            acc *= kMu0Over4Pi;
         }
-        __syncthreads();
-        for (int e = threadIdx.x; e < kGPts * kc; e += 256) {
-            const int r = e / kc, kk = e - r * kc;
-            const int pr = prow0 + r;
-            if (pr >= P_pad) continue;
-            const double g = tile[r][kk];
-            const size_t o = (size_t)pr * NP + k0 + kk;
-            const float g32 = (float)g;
-            if (G64) G64[o] = g;  // copies the plan did not ask for are null
-            if (G32) G32[o] = g32;
-            if (Ghi) {
-                const uint16_t hi = bf16_rne(g32);
-                Ghi[o] = hi;
-                Glo[o] = bf16_rne(g32 - bf16_to_f(hi));
-            }
-        }
-        // transposed copies [NP][P_pad]: each loop's column is contiguous in p
-        if (GT64 || GT32 || GThi) {
-            for (int e = threadIdx.x; e < kGPts * kc; e += 256) {
-                const int kk = e / kGPts, r = e - kk * kGPts;
-                const int pr = prow0 + r;
-                if (pr >= P_pad) continue;
-                const double g = tile[r][kk];
-                const float g32 = (float)g;
-                const size_t o = (size_t)(k0 + kk) * P_pad + pr;
-                if (GT64) GT64[o] = g;
-                if (GT32) GT32[o] = g32;
-                if (GThi) {
-                    const uint16_t hi = bf16_rne(g32);
-                    GThi[o] = hi;
-                    GTlo[o] = bf16_rne(g32 - bf16_to_f(hi));
-                }
-            }
-        }
-        __syncthreads();
+        tile[lane][kk] = acc;
     }
+    __syncthreads();
+    // NV consecutive entries of the tile's rows (TR: columns) per thread, E
+    // such runs per row; P_pad is a multiple of 64, so every row exists
+    auto split = [](double g, uint16_t &hi, uint16_t &lo) {
+        const float g32 = (float)g;
+        hi = bf16_rne(g32);
+        lo = bf16_rne(g32 - bf16_to_f(hi));
+    };
+    auto put = [&](auto tr, double *__restrict__ o64, float *__restrict__ o32,
+                   uint16_t *__restrict__ oh, uint16_t *__restrict__ ol) {
+        constexpr bool TR = decltype(tr)::value;
+        constexpr int ROWS = TR ? KC : kGPts, COLS = TR ? kGPts : KC;
+        const size_t ld = TR ? (size_t)P_pad : (size_t)NP;
+        const size_t o0 = TR ? (size_t)k0 * ld + p0 : (size_t)p0 * ld + k0;
+        auto at = [&](int r, int c) { return TR ? tile[c][r] : tile[r][c]; };
+        if (o64)
+            for (int e = threadIdx.x; e < ROWS * COLS / 2; e += 256) {
+                const int r = e / (COLS / 2), c = 2 * (e % (COLS / 2));
+                *(double2 *)(o64 + o0 + r * ld + c) = make_double2(at(r, c), at(r, c + 1));
+            }
+        if (o32)
+            for (int e = threadIdx.x; e < ROWS * COLS / 4; e += 256) {
+                const int r = e / (COLS / 4), c = 4 * (e % (COLS / 4));
+                *(float4 *)(o32 + o0 + r * ld + c) =
+                    make_float4((float)at(r, c), (float)at(r, c + 1), (float)at(r, c + 2),
+                                (float)at(r, c + 3));
+            }
+        if (oh)
+            for (int e = threadIdx.x; e < ROWS * COLS / 8; e += 256) {
+                const int r = e / (COLS / 8), c = 8 * (e % (COLS / 8));
+                __attribute__((aligned(16))) uint16_t h[8], l[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) split(at(r, c + j), h[j], l[j]);
+                auto pack = [](const uint16_t *v) {
+                    return make_uint4(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16,
+                                      v[4] | (uint32_t)v[5] << 16, v[6] | (uint32_t)v[7] << 16);
+                };
+                *(uint4 *)(oh + o0 + r * ld + c) = pack(h);
+                *(uint4 *)(ol + o0 + r * ld + c) = pack(l);
+            }
+    };
+    put(std::false_type{}, G64, G32, Ghi, Glo);
+    put(std::true_type{}, GT64, GT32, GThi, GTlo);
 }
 
 // ----------------------------------------------------------------------------
@@ -223,46 +243,55 @@ __device__ double neumann_pair(V3 x1, V3 x2, V3 y1, V3 y2, double a, const GLRul
     return kMu0Over4Pi * c * acc;
 }
 
-// One block per unordered loop pair (k <= l); threads stride over the
-// segment pairs, then a fixed-order tree reduction (deterministic).
-__global__ __launch_bounds__(256) void k_assemble_M(int n, const int32_t *__restrict__ seg_off,
-                                                    const double *__restrict__ verts,
-                                                    const double *__restrict__ wire_a, GLRule gl,
-                                                    double *__restrict__ M) {
-    __shared__ double red[256];
-    // linear pair index -> (k, l), k <= l, row-major over the upper triangle
-    const long long idx = blockIdx.x;
-    int k = 0;
-    long long rem = idx;
-    while (rem >= n - k) {
-        rem -= n - k;
-        ++k;
-    }
-    const int l = k + (int)rem;
-    const int ka = seg_off[k], kn = seg_off[k + 1] - ka;
-    const int la = seg_off[l], ln = seg_off[l + 1] - la;
-    const double a = (k == l) ? wire_a[k] : 0.0;
+// One group of TP threads per unordered loop pair (k <= l), striding over the
+// segment pairs; a fixed-order tree reduction (deterministic).  TP follows the
+// largest number of segment pairs: a wave for up to 64 (four-sided loops have
+// 16), else a whole workgroup of up to 1,024 threads.
+template <int TB, int TP>
+__global__ __launch_bounds__(TB) void k_assemble_M(int n, const int32_t *__restrict__ seg_off,
+                                                   const double *__restrict__ verts,
+                                                   const double *__restrict__ wire_a, GLRule gl,
+                                                   double *__restrict__ M) {
+    __shared__ double red[TB];
+    // linear pair index -> (k, l), k <= l, row-major over the upper triangle:
+    // row k starts at k (2 n - k + 1) / 2
+    const long long idx = (long long)blockIdx.x * (TB / TP) + threadIdx.x / TP;
+    const long long pairs = (long long)n * (n + 1) / 2;
+    const bool in = idx < pairs;
+    const double m = 2.0 * n + 1.0;
+    int k = (int)((m - sqrt(fmax(m * m - 8.0 * (double)idx, 0.0))) * 0.5);
+    k = min(max(k, 0), n - 1);
+    auto row = [&](long long r) { return r * (2LL * n - r + 1) / 2; };
+    while (in && row(k) > idx) --k;
+    while (in && k + 1 < n && row(k + 1) <= idx) ++k;
     double acc = 0.0;
-    for (int e = threadIdx.x; e < kn * ln; e += blockDim.x) {
-        const int s = e / ln, t = e - s * ln;
-        const int s2 = (s + 1 == kn) ? 0 : s + 1;
-        const int t2 = (t + 1 == ln) ? 0 : t + 1;
-        const double *p = verts + 3 * (size_t)(ka + s);
-        const double *p2 = verts + 3 * (size_t)(ka + s2);
-        const double *q = verts + 3 * (size_t)(la + t);
-        const double *q2 = verts + 3 * (size_t)(la + t2);
-        acc += neumann_pair({p[0], p[1], p[2]}, {p2[0], p2[1], p2[2]}, {q[0], q[1], q[2]},
-                            {q2[0], q2[1], q2[2]}, a, gl);
+    int l = 0;
+    if (in) {
+        l = k + (int)(idx - row(k));
+        const int ka = seg_off[k], kn = seg_off[k + 1] - ka;
+        const int la = seg_off[l], ln = seg_off[l + 1] - la;
+        const double a = (k == l) ? wire_a[k] : 0.0;
+        for (int e = threadIdx.x % TP; e < kn * ln; e += TP) {
+            const int s = e / ln, t = e - s * ln;
+            const int s2 = (s + 1 == kn) ? 0 : s + 1;
+            const int t2 = (t + 1 == ln) ? 0 : t + 1;
+            const double *p = verts + 3 * (size_t)(ka + s);
+            const double *p2 = verts + 3 * (size_t)(ka + s2);
+            const double *q = verts + 3 * (size_t)(la + t);
+            const double *q2 = verts + 3 * (size_t)(la + t2);
+            acc += neumann_pair({p[0], p[1], p[2]}, {p2[0], p2[1], p2[2]}, {q[0], q[1], q[2]},
+                                {q2[0], q2[1], q2[2]}, a, gl);
+        }
     }
     red[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    for (int w = TP / 2; w > 0; w >>= 1) {
+        if ((int)(threadIdx.x % TP) < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        M[(size_t)k * n + l] = red[0];
-        M[(size_t)l * n + k] = red[0];
+    if (in && threadIdx.x % TP == 0) {
+        M[(size_t)k * n + l] = red[threadIdx.x];
+        M[(size_t)l * n + k] = red[threadIdx.x];
     }
 }
 
@@ -272,18 +301,32 @@ hipError_t launch_assemble_G(int n, int NP, int P, int P_pad, int comp, const in
                              const double *verts_d, const double *pts_d, double *G64,
                              float *G32, uint16_t *Ghi, uint16_t *Glo, double *GT64,
                              float *GT32, uint16_t *GThi, uint16_t *GTlo, hipStream_t st) {
-    const int blocks = (P_pad + kGPts - 1) / kGPts;
-    hipLaunchKernelGGL(k_assemble_G, dim3(blocks), dim3(256), 0, st, n, NP, P, P_pad, comp, seg_off_d,
-                       verts_d, pts_d, G64, G32, Ghi, Glo, GT64, GT32, GThi, GTlo);
+    if (P_pad % kGPts != 0 || NP % 32 != 0 || (NP > 32 && NP % 64 != 0)) return hipErrorInvalidValue;
+    const unsigned blocks = (unsigned)(P_pad / kGPts);
+    if (NP == 32)
+        hipLaunchKernelGGL(k_assemble_G<32>, dim3(blocks), dim3(256), 0, st, n, NP, P, P_pad, comp,
+                           seg_off_d, verts_d, pts_d, G64, G32, Ghi, Glo, GT64, GT32, GThi, GTlo);
+    else
+        hipLaunchKernelGGL(k_assemble_G<64>, dim3(blocks, NP / 64), dim3(256), 0, st, n, NP, P,
+                           P_pad, comp, seg_off_d, verts_d, pts_d, G64, G32, Ghi, Glo, GT64, GT32,
+                           GThi, GTlo);
     return hipGetLastError();
 }
 
-hipError_t launch_assemble_M(int n, const int32_t *seg_off_d, const double *verts_d,
+hipError_t launch_assemble_M(int n, int max_segs, const int32_t *seg_off_d, const double *verts_d,
                              const double *wire_a_d, const GLRule &gl, double *M_d,
                              hipStream_t st) {
     const long long pairs = (long long)n * (n + 1) / 2;
-    hipLaunchKernelGGL(k_assemble_M, dim3((unsigned)pairs), dim3(256), 0, st, n, seg_off_d,
-                       verts_d, wire_a_d, gl, M_d);
+    const long long sp = (long long)max_segs * max_segs;
+    if (sp <= 64)
+        hipLaunchKernelGGL((k_assemble_M<256, 64>), dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0,
+                           st, n, seg_off_d, verts_d, wire_a_d, gl, M_d);
+    else if (sp <= 256)
+        hipLaunchKernelGGL((k_assemble_M<256, 256>), dim3((unsigned)pairs), dim3(256), 0, st, n,
+                           seg_off_d, verts_d, wire_a_d, gl, M_d);
+    else
+        hipLaunchKernelGGL((k_assemble_M<1024, 1024>), dim3((unsigned)pairs), dim3(1024), 0, st, n,
+                           seg_off_d, verts_d, wire_a_d, gl, M_d);
     return hipGetLastError();
 }
 

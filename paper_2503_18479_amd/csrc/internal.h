@@ -59,7 +59,8 @@ hipError_t launch_assemble_G(int n, int NP, int P, int P_pad, int comp, const in
                              float *G32, uint16_t *Ghi, uint16_t *Glo, double *GT64,
                              float *GT32, uint16_t *GThi, uint16_t *GTlo, hipStream_t st);
 
-hipError_t launch_assemble_M(int n, const int32_t *seg_off_d, const double *verts_d,
+// max_segs: the largest number of segments of a loop.
+hipError_t launch_assemble_M(int n, int max_segs, const int32_t *seg_off_d, const double *verts_d,
                              const double *wire_a_d, const GLRule &gl, double *M_d,
                              hipStream_t st);
 
@@ -436,6 +437,9 @@ struct cosim_geom {
     int n = 0, V = 0;
     std::vector<int32_t> seg_off;
     std::vector<double> verts, wire_a, R, area_z;
+    // the same loops with straight runs of segments merged, as assembly reads them
+    std::vector<int32_t> mseg_off;
+    std::vector<double> mverts;
 };
 
 struct cosim_plan {
@@ -450,7 +454,9 @@ struct cosim_plan {
     std::vector<double> R_geom;  // series resistances of the geometry (without port impedances)
     std::vector<double> R_h;     // what R_d holds
     std::vector<double> exc_h;   // what phi_d holds: [3][n], see loop_voltage
-    // operators (device)
+    // operators (device), all inside one allocation
+    void *arena = nullptr;
+    size_t arena_bytes = 0;
     // [P_pad][NP] row-major per precision, and transposed [NP][P_pad] copies
     double *G64 = nullptr, *GT64 = nullptr;
     float *G32 = nullptr, *GT32 = nullptr;
