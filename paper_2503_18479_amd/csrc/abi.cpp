@@ -1972,8 +1972,10 @@ struct cosim_sp {
     void *blas = nullptr;
     std::vector<int> ix, iy;  // host copies of the index pairs
     ~cosim_sp() {
-        dfree(d.S0);
-        dfree(d.K);
+        dfree(d.S0T);
+        dfree(d.KT);
+        dfree(d.rowptr);
+        dfree(d.rowent);
         dfree(d.r0);
         dfree(d.exc);
         dfree(d.ix);
@@ -1985,14 +1987,14 @@ struct cosim_sp {
         dfree(w.Y);
         dfree(w.Rp);
         dfree(w.lpart);
+        dfree(w.lu);
+        dfree(w.piv);
+        dfree(w.dinv);
         sp_blas_destroy(blas);
     }
 };
 
 namespace {
-
-std::once_flag g_sp_lds_once;
-hipError_t g_sp_lds_err = hipSuccess;
 
 int sp_check_device(const cosim_sp *p) {
     int dev = -1;
@@ -2003,7 +2005,7 @@ int sp_check_device(const cosim_sp *p) {
     return COSIM_OK;
 }
 
-// P-chunk of the contractions: about sqrt(P n0) rows (a multiple of 256), which
+// P-chunk of the FP32 contractions: about sqrt(P n0) rows (a multiple of 256), which
 // balances the chunk of B_comb (S rows entries) against the per-chunk partial
 // sums (S n0 P / rows entries), and at most 2^28 / S rows
 int sp_rows(int P, int n0, size_t systems) {
@@ -2020,21 +2022,40 @@ int sp_ensure(cosim_sp *p, int B) {
     dfree(p->w.Y);
     dfree(p->w.Rp);
     dfree(p->w.lpart);
+    dfree(p->w.lu);
+    dfree(p->w.piv);
+    dfree(p->w.dinv);
     p->cap = 0;
     const size_t S = (size_t)B * p->d.F, n0 = (size_t)p->d.n0;
     const int rows = sp_rows(p->d.P, p->d.n0, S);
     const int nchunk = (p->d.P + rows - 1) / rows;
+    const bool f32 = p->prec_mask & (1 << COSIM_FP32), f64 = p->prec_mask & (1 << COSIM_FP64);
+    // partial sums of either precision for every batch up to B (a smaller
+    // batch may split the points further)
+    size_t parts = f32 ? (size_t)nchunk * S : 0;
+    for (int b = std::min(B, 64); f64; b = std::min(B, b + 64)) {
+        parts = std::max(parts, (size_t)sp_fused_chunks(p->d, b) * b * p->d.F);
+        if (b == B) break;
+    }
+    // factor records for up to 2^17 systems (8.6 GB at 64 ports); larger
+    // batches are factored in slabs
+    const size_t slots = std::min<size_t>(S, (size_t)1 << 17);
+    const size_t psz = f64 ? sizeof(double2) : sizeof(float2);
     if (hipMalloc((void **)&p->w.X, S * n0 * sizeof(double2)) != hipSuccess ||
         hipMalloc(&p->w.Xg, S * n0 * sizeof(double2)) != hipSuccess ||
-        hipMalloc(&p->w.Y, S * (size_t)rows * sizeof(double2)) != hipSuccess ||
-        hipMalloc(&p->w.Rp, (size_t)nchunk * S * n0 * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&p->w.lpart, (size_t)nchunk * S * sizeof(double)) != hipSuccess) {
+        (f32 && hipMalloc(&p->w.Y, S * (size_t)rows * sizeof(float2)) != hipSuccess) ||
+        hipMalloc(&p->w.Rp, parts * n0 * psz) != hipSuccess ||
+        hipMalloc((void **)&p->w.lpart, parts * sizeof(double)) != hipSuccess ||
+        hipMalloc((void **)&p->w.lu, slots * n0 * n0 * sizeof(double2)) != hipSuccess ||
+        hipMalloc((void **)&p->w.piv, slots * n0 * sizeof(int)) != hipSuccess ||
+        hipMalloc((void **)&p->w.dinv, slots * n0 * sizeof(double2)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(COSIM_ENOMEM, "S-parameter workspace for %d configurations failed", B);
     }
     p->w.B = B;
     p->w.rows = rows;
     p->w.nchunk = nchunk;
+    p->w.slots = (int)slots;
     p->cap = (size_t)B;
     return COSIM_OK;
 }
@@ -2088,8 +2109,6 @@ int cosim_sp_create(int n0, int n1, int F, int P, int ncomp, const double *S0_d,
     } while (0)
     hipStream_t st = (hipStream_t)stream;
     SP_TRY(hipGetDevice(&p->device));
-    std::call_once(g_sp_lds_once, [] { g_sp_lds_err = sp_set_lds_limit(); });
-    SP_TRY(g_sp_lds_err);
     p->N = N;
     p->prec_mask = precisions;
     SpDev &d = p->d;
@@ -2102,15 +2121,29 @@ int cosim_sp_create(int n0, int n1, int F, int P, int ncomp, const double *S0_d,
     p->ix.assign(idx_x, idx_x + nvar);
     p->iy.assign(idx_y, idx_y + nvar);
     const size_t nf = (size_t)F * P * ncomp * n0;
-    SP_TRY(hipMalloc((void **)&d.S0, (size_t)F * n0 * n0 * sizeof(double2)));
-    SP_TRY(hipMalloc((void **)&d.K, (size_t)F * n0 * n0 * sizeof(double2)));
+    SP_TRY(hipDeviceGetAttribute(&d.cus, hipDeviceAttributeMultiprocessorCount, p->device));
+    // the variable entries of each row of S_C11 and S_C12, in their order
+    std::vector<int> rowptr(n0 + 1, 0), rowent(std::max(nvar, 1), 0);
+    for (int e = 0; e < nvar; ++e)
+        if (idx_x[e] < n0) ++rowptr[idx_x[e] + 1];
+    for (int r = 0; r < n0; ++r) rowptr[r + 1] += rowptr[r];
+    {
+        std::vector<int> at(rowptr.begin(), rowptr.end() - 1);
+        for (int e = 0; e < nvar; ++e)
+            if (idx_x[e] < n0) rowent[at[idx_x[e]]++] = e;
+    }
+    SP_TRY(hipMalloc((void **)&d.S0T, (size_t)F * n0 * n0 * sizeof(double2)));
+    SP_TRY(hipMalloc((void **)&d.KT, (size_t)F * n0 * n0 * sizeof(double2)));
+    SP_TRY(hipMalloc((void **)&d.rowptr, rowptr.size() * sizeof(int)));
+    SP_TRY(hipMalloc((void **)&d.rowent, rowent.size() * sizeof(int)));
+    SP_TRY(hipMemcpyAsync(d.rowptr, rowptr.data(), rowptr.size() * sizeof(int), hipMemcpyHostToDevice, st));
+    SP_TRY(hipMemcpyAsync(d.rowent, rowent.data(), rowent.size() * sizeof(int), hipMemcpyHostToDevice, st));
     SP_TRY(hipMalloc((void **)&d.r0, (size_t)F * n0 * sizeof(double2)));
     SP_TRY(hipMalloc((void **)&d.exc, (size_t)n1 * sizeof(double2)));
     SP_TRY(hipMalloc((void **)&d.ix, std::max(nvar, 1) * sizeof(int)));
     SP_TRY(hipMalloc((void **)&d.iy, std::max(nvar, 1) * sizeof(int)));
     SP_TRY(hipMalloc((void **)&d.fields64, nf * sizeof(double2)));
     if (precisions & (1 << COSIM_FP32)) SP_TRY(hipMalloc((void **)&d.fields32, nf * sizeof(float2)));
-    SP_TRY(hipMemcpyAsync(d.S0, S0_d, (size_t)F * n0 * n0 * sizeof(double2), hipMemcpyDeviceToDevice, st));
     SP_TRY(hipMemcpyAsync(d.fields64, fields_d, nf * sizeof(double2), hipMemcpyDeviceToDevice, st));
     SP_TRY(hipMemcpyAsync(d.exc, exc, (size_t)n1 * sizeof(double2), hipMemcpyHostToDevice, st));
     if (nvar > 0) {
@@ -2118,7 +2151,7 @@ int cosim_sp_create(int n0, int n1, int F, int P, int ncomp, const double *S0_d,
         SP_TRY(hipMemcpyAsync(d.iy, p->iy.data(), nvar * sizeof(int), hipMemcpyHostToDevice, st));
     }
     if (d.fields32) SP_TRY(sp_to_c64(nf, d.fields64, d.fields32, st));
-    SP_TRY(sp_prep(d, (const double2 *)sc_const_d, st));
+    SP_TRY(sp_prep(d, (const double2 *)S0_d, (const double2 *)sc_const_d, st));
     SP_TRY(sp_blas_create(&p->blas));
     SP_TRY(hipStreamSynchronize(st));  // host index copies and the caller's inputs are done with
 #undef SP_TRY
@@ -2150,7 +2183,7 @@ int cosim_sp_field(cosim_sp_t p, int B, const double *values_d, double *x_d, dou
     if (rc != COSIM_OK) return rc;
     if ((rc = sp_ensure(p, B)) != COSIM_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
-    HIP_TRY(sp_forward(p->d, B, (const double2 *)values_d, p->w.X, p->w.Xg, 0, status_d, st));
+    HIP_TRY(sp_forward(p->d, p->w, B, (const double2 *)values_d, 0, status_d, st));
     const size_t S = (size_t)B * p->d.F;
     if (x_d)
         HIP_TRY(hipMemcpyAsync(x_d, p->w.X, S * p->d.n0 * sizeof(double2), hipMemcpyDeviceToDevice, st));

@@ -379,31 +379,39 @@ constexpr int kSpMaxPorts = 64;
 // unless noted).
 struct SpDev {
     int n0 = 0, n1 = 0, F = 0, P = 0, ncomp = 0, nvar = 0;
-    double2 *S0 = nullptr;        // [F][n0][n0]
-    double2 *K = nullptr;         // [F][n0][n0]  I - S_C11,const S0
+    int cus = 0;                  // compute units of the device
+    double2 *S0T = nullptr;       // [F][n0][n0]  S0 transposed
+    double2 *KT = nullptr;        // [F][n0][n0]  I - S_C11,const S0, transposed
     double2 *r0 = nullptr;        // [F][n0]      S_C12,const exc
     double2 *exc = nullptr;       // [n1]
     int *ix = nullptr, *iy = nullptr;  // [nvar] rows / columns of the variable entries
+    int *rowptr = nullptr;        // [n0 + 1] and
+    int *rowent = nullptr;        // [nvar]: the entries of each row < n0, in their order
     double2 *fields64 = nullptr;  // [F][P][ncomp][n0]
     float2 *fields32 = nullptr;   // the same in complex64 (FP32 contractions)
 };
 // Workspace for B configurations (s = b F + f).
 struct SpWork {
-    int B = 0, rows = 0, nchunk = 0;  // P-chunk of the contractions
+    int B = 0, rows = 0, nchunk = 0;  // P-chunk of the FP32 contractions
+    int slots = 0;                    // systems the factor record holds
+    double2 *lu = nullptr;            // [slots][n0][n0] recorded factors (SpLu in sparam.hip)
+    int *piv = nullptr;               // [slots][n0]
+    double2 *dinv = nullptr;          // [slots][n0]
     double2 *X = nullptr;             // [S][n0] forward solution, FP64
-    void *Xg = nullptr;               // [F][B][n0] GEMM operand (complex128 or complex64)
-    void *Y = nullptr;                // [F][B][rows] B_comb, then conj(w), of one chunk
+    void *Xg = nullptr;               // [F][B][n0] contraction operand (complex128 or complex64)
+    void *Y = nullptr;                // [F][B][rows] B_comb, then conj(w), of one chunk (FP32)
     void *Rp = nullptr;               // [nchunk][F][B][n0] conj(fields^H w) per chunk
     double *lpart = nullptr;          // [nchunk][F][B] loss partial sums
 };
-// The S-parameter pipeline's complex contractions run on rocBLAS; its handle.
+// The FP32 contractions and the materialised B_comb run on rocBLAS; its handle.
 hipError_t sp_blas_create(void **handle);
 void sp_blas_destroy(void *handle);
-hipError_t sp_prep(const SpDev &d, const double2 *sc_const, hipStream_t st);
-hipError_t sp_set_lds_limit();
+hipError_t sp_prep(const SpDev &d, const double2 *S0, const double2 *sc_const, hipStream_t st);
+// Chunks of points (partial sums per system) of the FP64 contraction.
+int sp_fused_chunks(const SpDev &d, int B);
 hipError_t sp_to_c64(size_t count, const double2 *a, float2 *b, hipStream_t st);
-// Forward solves: X and Xg (prec 0: complex128, 1: complex64), status.
-hipError_t sp_forward(const SpDev &d, int B, const double2 *values, double2 *X, void *Xg, int prec,
+// Forward solves: w.X and w.Xg (prec 0: complex128, 1: complex64), status.
+hipError_t sp_forward(const SpDev &d, const SpWork &w, int B, const double2 *values, int prec,
                       int32_t *status, hipStream_t st);
 // B_comb of every component: out[b][f][p][c] from the complex128 Xg of sp_forward.
 hipError_t sp_field(void *blas, const SpDev &d, int B, const double2 *Xg64, double2 *out,

@@ -8,19 +8,21 @@
 //
 // Kernels:
 //   k_sp_prep   per frequency: K = I - S_C11,const S0 and r0 = S_C12,const exc
-//               (the constant parts; the variable entries are applied per system);
-//   k_sp_solve  one workgroup of four waves per system, the n0 x n0 matrix in
-//               LDS (rows padded to a multiple of 16 plus 4 entries): A = K minus the variable rows of S_C11 S0, the
+//               (the constant parts; the variable entries are applied per
+//               system) and S0, both transposed;
+//   k_sp_lu     one wave per system: A = K minus the variable rows of S_C11 S0,
 //               right-hand side r0 plus the variable entries of S_C12 exc, LU with
 //               partial pivoting (largest |re| + |im|, ties to the lower row)
-//               applied to the right-hand side as it goes, back substitution.
-//               The adjoint form builds A^H and the right-hand side from the
-//               contraction's partial sums, and ends with the gradient of every
-//               variable entry;
+//               applied to the right-hand side as it goes, back substitution;
+//               the factor is recorded;
+//   k_sp_adjoint  one wave per system: the right-hand side from the
+//               contraction's partial sums, A^H lam = r with the recorded
+//               factor, and the gradient of every variable entry;
+//   k_sp_fused  FP64: B_comb = fields x, the loss epilogue and fields^H w in one
+//               pass over the rows of the loss component, on matrix cores;
 //   rocBLAS complex GEMMs (per frequency, strided over frequencies, in P-chunks)
-//               for B_comb = fields x and fields^H w, only on the rows of the
-//               loss component;
-//   k_sp_epilogue  loss terms and conj(w) in place of B_comb per chunk;
+//               with k_sp_epilogue between them for FP32, and for the
+//               materialised B_comb;
 //   k_sp_reduce    fixed-order loss sums;
 //   k_sp_rc, k_sp_rc_backward  the RC preprocessing of Eq. 2-3 and its chain rule.
 #include <rocblas/rocblas.h>
@@ -48,11 +50,6 @@ __device__ inline double2 zinv(double2 a) {
     return make_double2(a.x * d, -a.y * d);
 }
 __device__ inline double2 zconj(double2 a) { return make_double2(a.x, -a.y); }
-
-// LDS row stride (complex entries) of the per-system matrix: a multiple of 16
-// plus 4, so that the 16 lanes of one 16-byte access pass (4 rows x 4
-// consecutive columns in the trailing update) fall on distinct banks
-__host__ __device__ inline int sp_ld(int n0) { return (n0 + 15) / 16 * 16 + 4; }
 
 template <int CTRL>
 __device__ inline int dpp_i(int x) {
@@ -91,11 +88,13 @@ __device__ inline double rl(double v, int src) {
 }
 __device__ inline double2 rl2(double2 v, int src) { return make_double2(rl(v.x, src), rl(v.y, src)); }
 
-// K[f] = I - S11c[f] S0[f], r0[f] = S12c[f] exc; grid (n0, F), 64 threads.
+// K[f] = I - S11c[f] S0[f] and S0[f], both stored transposed, and r0[f] =
+// S12c[f] exc; grid (n0, F), 64 threads.
 __global__ __launch_bounds__(64) void k_sp_prep(int n0, int n1, int F, const double2 *__restrict__ S0,
                                                 const double2 *__restrict__ scc,
                                                 const double2 *__restrict__ exc,
-                                                double2 *__restrict__ K, double2 *__restrict__ r0) {
+                                                double2 *__restrict__ KT, double2 *__restrict__ S0T,
+                                                double2 *__restrict__ r0) {
     const int i = blockIdx.x, f = blockIdx.y, lane = threadIdx.x;
     const int N = n0 + n1;
     const double2 *S0f = S0 + (size_t)f * n0 * n0;
@@ -108,7 +107,8 @@ __global__ __launch_bounds__(64) void k_sp_prep(int n0, int n1, int F, const dou
                 acc.x = fma(a.x, b.x, fma(-a.y, b.y, acc.x));
                 acc.y = fma(a.x, b.y, fma(a.y, b.x, acc.y));
             }
-        K[((size_t)f * n0 + i) * n0 + j] = make_double2((i == j ? 1.0 : 0.0) - acc.x, -acc.y);
+        KT[((size_t)f * n0 + j) * n0 + i] = make_double2((i == j ? 1.0 : 0.0) - acc.x, -acc.y);
+        S0T[((size_t)f * n0 + j) * n0 + i] = S0f[(size_t)i * n0 + j];
     }
     if (lane == 0) {
         double2 acc = make_double2(0.0, 0.0);
@@ -122,186 +122,287 @@ __global__ __launch_bounds__(64) void k_sp_prep(int n0, int n1, int F, const dou
     }
 }
 
-// One workgroup of four waves per system s = b F + f; the matrix in LDS (rows
-// padded to sp_ld(n0) entries) and the right-hand side after it.  Elimination
-// step k: every wave finds the pivot row itself (shuffles over column k), the
-// row exchange runs over columns, the trailing update over (row, column
-// quarter) with four threads per row, two workgroup barriers per step; wave 0
-// then runs the back substitution and writes the outputs.
-// ADJ = false: solves A x = S_C12 exc, writes X[s][n0] (FP64) and the GEMM
-// operand Xg[f][b][n0] (PREC 0: complex128, 1: complex64).  ADJ = true:
-// right-hand side r = rscale conj(sum over chunks of Rp[c][f][b][:]) (the chunks
-// hold conj(fields^H w)), solves A^H lam = r and writes the gradient of every
-// variable entry to grad[s][nvar].
-template <bool ADJ, int PREC>
-__global__ __launch_bounds__(256) void k_sp_solve(SpDev d, int B, const double2 *__restrict__ values,
-                                                  double2 *__restrict__ X, void *Xg,
-                                                  const void *Rp, int nchunk, double rscale,
-                                                  double2 *__restrict__ grad,
-                                                  int32_t *__restrict__ status) {
-    extern __shared__ double2 sa[];
-    const int n0 = d.n0, ld = sp_ld(n0), F = d.F, nvar = d.nvar;
-    double2 *sx = sa + (size_t)n0 * ld;  // right-hand side, then solution
-    const int s = blockIdx.x;
-    const int b = s / F, f = s - b * F;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const double2 *K = d.K + (size_t)f * n0 * n0;
-    const double2 *S0f = d.S0 + (size_t)f * n0 * n0;
-    const double2 *v = values + (size_t)s * nvar;
-    __shared__ int s_ix[256], s_iy[256];
-    __shared__ double2 s_v[256];
-    // A = K - sum over variable S_C11 entries (r, c) of v e_r S0[c][:]
-#pragma unroll 4
-    for (int e = tid; e < n0 * n0; e += 256) {
-        const int i = e / n0, j = e - i * n0;
-        sa[i * ld + j] = K[e];
+// 1/a by the hardware reciprocal and two Newton steps of |a|^2 where that is
+// safe, else by division.
+__device__ inline double2 zinv_fast(double2 a) {
+    const double q = fma(a.x, a.x, a.y * a.y);
+    if (__builtin_expect(q > 1e-280 && q < 1e280, 1)) {
+        double r = __builtin_amdgcn_rcp(q);
+        r = fma(r, fma(-q, r, 1.0), r);
+        r = fma(r, fma(-q, r, 1.0), r);
+        return make_double2(a.x * r, -a.y * r);
     }
-    double2 x = make_double2(0.0, 0.0);  // thread i < n0: right-hand side entry i
-    if (!ADJ && tid < n0) x = d.r0[(size_t)f * n0 + tid];
-    // the variable entries, 256 at a time through LDS; thread j owns column j,
-    // so repeated rows keep their order
-    for (int e0 = 0; e0 < nvar; e0 += 256) {
-        const int ne = min(256, nvar - e0);
-        __syncthreads();
-        if (tid < ne) {
-            s_ix[tid] = d.ix[e0 + tid];
-            s_iy[tid] = d.iy[e0 + tid];
-            s_v[tid] = v[e0 + tid];
-        }
-        __syncthreads();
-        if (tid < n0) {
-            const int j = tid;
-#pragma unroll 4
-            for (int e = 0; e < ne; ++e) {
-                const int r = s_ix[e], c = s_iy[e];
-                if (r < n0 && c < n0) sa[r * ld + j] = zfms(sa[r * ld + j], s_v[e], S0f[(size_t)c * n0 + j]);
-                if (!ADJ && r == j && c >= n0) {
-                    const double2 t = zmul(s_v[e], d.exc[c - n0]);
-                    x.x += t.x;
-                    x.y += t.y;
-                }
-            }
-        }
-    }
-    if (tid < n0) {
-        const int i = tid;
-        if (ADJ) {
-            double sr = 0.0, si = 0.0;
-#pragma unroll 8
-            for (int c = 0; c < nchunk; ++c) {
-                const size_t o = (((size_t)c * F + f) * B + b) * n0 + i;
-                if (PREC == 0) {
-                    const double2 t = ((const double2 *)Rp)[o];
-                    sr += t.x;
-                    si += t.y;
-                } else {
-                    const float2 t = ((const float2 *)Rp)[o];
-                    sr += (double)t.x;
-                    si += (double)t.y;
-                }
-            }
-            x = make_double2(rscale * sr, -rscale * si);
-        }
-        sx[i] = x;
-    }
-    __syncthreads();
-    if (ADJ) {
-        // A -> A^H in place: thread i takes row i right of the diagonal and
-        // column i below it (disjoint from every other thread's entries)
-        if (tid < n0) {
-            const int i = tid;
-            sa[i * ld + i] = zconj(sa[i * ld + i]);
-            for (int j = i + 1; j < n0; ++j) {
-                const double2 t = sa[i * ld + j];
-                sa[i * ld + j] = zconj(sa[j * ld + i]);
-                sa[j * ld + i] = zconj(t);
-            }
-        }
-        __syncthreads();
-    }
-    // LU with partial pivoting, right-hand side eliminated alongside
+    return zinv(a);
+}
+// Record of the LU of a launch's systems: factor rows [n0][n0] in the order of
+// A's rows (row r holds U from the step that took it as pivot row on, and L
+// before), pivot row and 1/pivot per step.
+struct SpLu {
+    double2 *f;
+    int *piv;
+    double2 *dinv;
+};
+
+// One system's elimination: lane r holds row r, 32 columns at a time in
+// registers.  Rows are not exchanged; `step` is the step that took the lane's
+// row as its pivot row (64: none yet).
+struct SpElim {
+    double2 t;       // right-hand side entry of the lane's row
+    int step = 64;
+    int pk = 0;      // lane k: pivot row of step k
+    double2 dk;      // lane k: 1 / pivot of step k
     int flag = 0;
-    const int ur = tid >> 2, uq = tid & 3;  // update: row k + 1 + ur, columns = uq mod 4
-    for (int k = 0; k < n0; ++k) {
-        // pivot: largest |re| + |im| in column k (compared in FP32; a NaN wins)
+};
+// Steps kbase .. kbase + cnt - 1 on a[0 .. W): each takes a[0] as its column,
+// picks the pivot row, reads its entries as wave-uniform values and writes the
+// updated columns one place to the left, so that the loop body is the same
+// for every step.
+template <int W>
+__device__ __forceinline__ void sp_steps(double2 (&a)[32], SpElim &e, int kbase, int cnt, int n0, int lane,
+                                         double2 *__restrict__ frow) {
+#pragma unroll 1
+    for (int k = kbase; k < kbase + cnt; ++k) {
+        const bool open = e.step == 64 && lane < n0;
         float mg = -1.0f;
-        if (lane >= k && lane < n0) {
-            const double2 a = sa[lane * ld + k];
-            mg = (float)(fabs(a.x) + fabs(a.y));
-            if (!(mg == mg)) mg = __builtin_inff();
+        if (open) {
+            mg = (float)(fabs(a[0].x) + fabs(a[0].y));
+            if (!(mg == mg)) mg = __builtin_inff();  // a NaN wins
         }
         const int p = wave_amax(mg, lane);
-        __syncthreads();  // every wave has read column k
-        if (p != k) {
-            for (int j = tid; j < n0; j += 256) {
-                const double2 t = sa[k * ld + j];
-                sa[k * ld + j] = sa[p * ld + j];
-                sa[p * ld + j] = t;
-            }
-            if (tid == 0) {
-                const double2 t = sx[k];
-                sx[k] = sx[p];
-                sx[p] = t;
+        const double2 d = rl2(a[0], p);
+        if (!(d.x != 0.0 || d.y != 0.0)) e.flag |= COSIM_SYS_SINGULAR;
+        const double2 inv = zinv_fast(d);
+        double2 l = zmul(a[0], inv);
+        l.x = open && lane != p ? l.x : 0.0;
+        l.y = open && lane != p ? l.y : 0.0;
+        // (componentwise: a select of the struct would put the array in memory)
+        const bool low = open && lane != p;
+        const double2 fv = make_double2(low ? l.x : a[0].x, low ? l.y : a[0].y);
+        if (lane < n0) frow[k] = fv;
+        const double2 tp = rl2(e.t, p);
+        e.t = zfms(e.t, l, tp);
+#pragma unroll
+        for (int j = 1; j < W; ++j) a[j - 1] = zfms(a[j], l, rl2(a[j], p));
+        if (lane == p) e.step = k;
+        if (lane == k) {
+            e.pk = p;
+            e.dk = inv;
+        }
+    }
+}
+
+// Columns c0 .. c0 + 31 of the lane's row of A (zero past n0); with RHS also
+// the variable entries of the right-hand side.
+template <bool RHS>
+__device__ __forceinline__ void sp_load_columns(const SpDev &d, int f, const double2 *__restrict__ v, int lane,
+                                                int c0, double2 (&a)[32], double2 &t) {
+    const int n0 = d.n0;
+    const double2 *KT = d.KT + (size_t)f * n0 * n0, *S0T = d.S0T + (size_t)f * n0 * n0;
+    const bool in = lane < n0;
+#pragma unroll
+    for (int j = 0; j < 32; ++j) {
+        const bool ok = in && c0 + j < n0;
+        const double2 k = KT[ok ? (size_t)(c0 + j) * n0 + lane : 0];
+        a[j].x = ok ? k.x : 0.0;
+        a[j].y = ok ? k.y : 0.0;
+    }
+    int e = in ? d.rowptr[lane] : 0;
+    const int end = in ? d.rowptr[lane + 1] : 0;
+    for (; e < end; ++e) {  // each row's entries in their order
+        const int i = d.rowent[e], c = d.iy[i];
+        const double2 x = v[i];
+        if (c < n0) {
+#pragma unroll
+            for (int j = 0; j < 32; ++j)
+                if (c0 + j < n0) a[j] = zfms(a[j], x, S0T[(size_t)(c0 + j) * n0 + c]);
+        } else if (RHS) {
+            const double2 w = zmul(x, d.exc[c - n0]);
+            t.x += w.x;
+            t.y += w.y;
+        }
+    }
+}
+
+// One wave per system s = s0 + blockIdx.x: LU with partial pivoting, two halves
+// of 32 columns one after the other, and the solution x of A x = S_C12 exc:
+// writes X[s][n0] (FP64), the contraction's operand Xg[f][b][n0] (PREC 0:
+// complex128, 1: complex64), the status and the record.  Without barriers the
+// waves of a SIMD hide each other's pivot chains; the four-wave form with
+// the matrix in LDS and three barriers per column took 592 us for 2,560
+// systems of 64 ports, this one 290 (three waves per SIMD spill: 395).
+template <int PREC>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_sp_lu(
+    SpDev d, int B, int s0, const double2 *__restrict__ values, double2 *__restrict__ X, void *Xg,
+    SpLu rec, int32_t *__restrict__ status) {
+    const int n0 = d.n0, lane = threadIdx.x, slot = blockIdx.x, s = s0 + slot;
+    const int b = s / d.F, f = s - b * d.F;
+    const double2 *v = values + (size_t)s * d.nvar;
+    double2 *frow = rec.f + ((size_t)slot * n0 + min(lane, n0 - 1)) * n0;
+    SpElim e;
+    e.dk = make_double2(0.0, 0.0);
+    e.t = lane < n0 ? d.r0[(size_t)f * n0 + lane] : make_double2(0.0, 0.0);
+    double2 a[32];
+    sp_load_columns<true>(d, f, v, lane, 0, a, e.t);
+    auto half = [&](int kbase) {
+        const int left = n0 - kbase;  // > 0
+        sp_steps<32>(a, e, kbase, min(left, 8), n0, lane, frow);
+        if (left > 8) sp_steps<24>(a, e, kbase + 8, min(left - 8, 8), n0, lane, frow);
+        if (left > 16) sp_steps<16>(a, e, kbase + 16, min(left - 16, 8), n0, lane, frow);
+        if (left > 24) sp_steps<8>(a, e, kbase + 24, min(left - 24, 8), n0, lane, frow);
+    };
+    half(0);
+    if (n0 > 32) {
+        sp_load_columns<false>(d, f, v, lane, 32, a, e.t);
+        // the steps of the first half on these columns
+        for (int k0 = 0; k0 < 32; k0 += 8) {
+            double2 l8[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) l8[u] = frow[k0 + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + u;
+                const int p = __builtin_amdgcn_readlane(e.pk, k);
+                const double2 l = e.step > k ? l8[u] : make_double2(0.0, 0.0);
+#pragma unroll
+                for (int j = 0; j < 32; ++j) a[j] = zfms(a[j], l, rl2(a[j], p));
             }
         }
-        __syncthreads();
-        const double2 dk = sa[k * ld + k];
-        if (!(dk.x != 0.0 || dk.y != 0.0)) flag |= COSIM_SYS_SINGULAR;
-        const int i = k + 1 + ur;
-        if (i < n0) {
-            const double2 l = zmul(sa[i * ld + k], zinv(dk));
-            if (uq == 0) sx[i] = zfms(sx[i], l, sx[k]);
-            // this thread's columns j = k + 1 + uq + 4t, four at a time with every
-            // load issued before the stores (the LDS round trips overlap)
-            int j = k + 1 + uq;
-            for (; j + 12 < n0; j += 16) {
-                double2 a[4], u[4];
+        half(32);
+    }
+    // back substitution: x_k, then its column off the rows of earlier steps
+    double2 x = make_double2(0.0, 0.0);
+    for (int k1 = n0; k1 > 0; k1 -= 8) {
+        double2 u8[8];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    a[t] = sa[i * ld + j + 4 * t];
-                    u[t] = sa[k * ld + j + 4 * t];
-                }
+        for (int u = 0; u < 8; ++u) u8[u] = frow[max(k1 - 1 - u, 0)];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) sa[i * ld + j + 4 * t] = zfms(a[t], l, u[t]);
-            }
-            for (; j < n0; j += 4) sa[i * ld + j] = zfms(sa[i * ld + j], l, sa[k * ld + j]);
+        for (int u = 0; u < 8; ++u) {
+            const int k = k1 - 1 - u;
+            if (k < 0) continue;  // uniform
+            const int p = __builtin_amdgcn_readlane(e.pk, k);
+            const double2 xk = zmul(rl2(e.t, p), rl2(e.dk, k));
+            if (lane == k) x = xk;
+            const double2 c = e.step < k ? u8[u] : make_double2(0.0, 0.0);
+            e.t = zfms(e.t, c, xk);
         }
-        __syncthreads();
     }
-    if (tid >= 64) return;  // wave 0 finishes alone (no barrier below)
-    x = lane < n0 ? sx[lane] : make_double2(0.0, 0.0);
-    for (int k = n0 - 1; k >= 0; --k) {
-        const double2 xk = zmul(rl2(x, k), zinv(sa[k * ld + k]));
-        if (lane == k) x = xk;
-        if (lane < k) x = zfms(x, sa[lane * ld + k], xk);
-    }
+    int flag = e.flag;
     const bool finite = isfinite(x.x) && isfinite(x.y);
     if (__ballot(lane < n0 && !finite) != 0) flag |= COSIM_SYS_NONFINITE;
     if (flag & COSIM_SYS_SINGULAR) x = make_double2(__builtin_nan(""), __builtin_nan(""));
-    if (!ADJ) {
-        if (lane == 0) status[s] = flag;
-        if (lane < n0) {
-            X[(size_t)s * n0 + lane] = x;
-            const size_t o = ((size_t)f * B + b) * n0 + lane;
-            if (PREC == 0) ((double2 *)Xg)[o] = x;
-            else ((float2 *)Xg)[o] = make_float2((float)x.x, (float)x.y);
-        }
-        return;
+    if (lane == 0) status[s] = flag;
+    if (lane < n0) {
+        X[(size_t)s * n0 + lane] = x;
+        const size_t o = ((size_t)f * B + b) * n0 + lane;
+        if (PREC == 0) ((double2 *)Xg)[o] = x;
+        else ((float2 *)Xg)[o] = make_float2((float)x.x, (float)x.y);
+        rec.piv[(size_t)slot * n0 + lane] = e.pk;
+        rec.dinv[(size_t)slot * n0 + lane] = e.dk;
     }
+}
+
+// t - conj(l) u
+__device__ inline double2 zfmsc(double2 t, double2 l, double2 u) {
+    return make_double2(fma(-l.x, u.x, fma(-l.y, u.y, t.x)), fma(-l.x, u.y, fma(l.y, u.x, t.y)));
+}
+
+// One wave per system s = s0 + i, four per block: r = rscale conj(sum over chunks
+// of Rp[c][f][b][:]) (the chunks hold conj(fields^H w)), A^H lam = r with the
+// record of k_sp_lu (A = P^T L U: U^H z = r, L^H v = z, lam at pivot row k is
+// v_k; both sweeps take the recorded row of each step, lane k its entry k), and
+// the gradient of every variable entry to grad[s][nvar].
+template <int PREC>
+__global__ __launch_bounds__(256) void k_sp_adjoint(SpDev d, int B, int s0, int count,
+                                                    const double2 *__restrict__ X, const void *Rp,
+                                                    int nchunk, double rscale, SpLu rec,
+                                                    double2 *__restrict__ grad,
+                                                    int32_t *__restrict__ status) {
+    const int n0 = d.n0, F = d.F, nvar = d.nvar, lane = threadIdx.x & 63;
+    const int slot = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (slot >= count) return;  // whole wave
+    const int s = s0 + slot, b = s / F, f = s - b * F;
+    const int li = min(lane, n0 - 1);
+    double2 t = make_double2(0.0, 0.0);
+    {
+        double sr = 0.0, si = 0.0;
+#pragma unroll 8
+        for (int c = 0; c < nchunk; ++c) {
+            const size_t o = (((size_t)c * F + f) * B + b) * n0 + li;
+            if (PREC == 0) {
+                const double2 r = ((const double2 *)Rp)[o];
+                sr += r.x;
+                si += r.y;
+            } else {
+                const float2 r = ((const float2 *)Rp)[o];
+                sr += (double)r.x;
+                si += (double)r.y;
+            }
+        }
+        if (lane < n0) t = make_double2(rscale * sr, -rscale * si);
+    }
+    const double2 *__restrict__ fac = rec.f + (size_t)slot * n0 * n0;
+    const int pk = rec.piv[(size_t)slot * n0 + li];
+    const double2 dk = rec.dinv[(size_t)slot * n0 + li];
+    auto load = [&](double2 (&q)[8], int j0) {  // entry `lane` of the rows of steps j0 .. j0 + 7
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int p = __builtin_amdgcn_readlane(pk, min(max(j0 + u, 0), n0 - 1));
+            q[u] = fac[(size_t)p * n0 + li];
+        }
+    };
+    double2 q[8], nq[8];
+    load(q, 0);
+    for (int j0 = 0; j0 < n0; j0 += 8) {  // U^H z = r
+        load(nq, j0 + 8);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int j = j0 + u;
+            if (j >= n0) continue;  // uniform
+            const double2 z = zmulc(rl2(t, j), rl2(dk, j));
+            const double2 w = zfmsc(t, q[u], z);
+            if (lane == j) t = z;
+            else if (lane > j) t = w;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = nq[u];
+    }
+    load(q, n0 - 8);
+    for (int j1 = n0; j1 > 0; j1 -= 8) {  // L^H v = z
+        load(nq, j1 - 16);
+#pragma unroll
+        for (int u = 7; u >= 0; --u) {
+            const int j = j1 - 8 + u;
+            if (j < 0) continue;  // uniform
+            const double2 vj = rl2(t, j);
+            const double2 w = zfmsc(t, q[u], vj);
+            if (lane < j) t = w;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = nq[u];
+    }
+    // lam to the lane of its row
+    const int to = 4 * (lane < n0 ? pk : lane);
+    auto send = [&](double x) {
+        return __hiloint2double(__builtin_amdgcn_ds_permute(to, __double2hiint(x)),
+                                __builtin_amdgcn_ds_permute(to, __double2loint(x)));
+    };
+    double2 x = make_double2(send(t.x), send(t.y));
+    int flag = status[s];
+    const bool finite = isfinite(x.x) && isfinite(x.y);
+    if (__ballot(lane < n0 && !finite) != 0) flag |= COSIM_SYS_NONFINITE;
+    if (flag & COSIM_SYS_SINGULAR) x = make_double2(__builtin_nan(""), __builtin_nan(""));
+    if (lane == 0) status[s] = flag;
     // gradient: 2 lam_r conj(exc_j) for S_C12 entries (r, n0 + j), 2 lam_r
     // conj((S0 x)_c) for S_C11 entries (r, c), 0 for S_C21 / S_C22 entries
-    if (lane == 0 && flag) status[s] |= flag;
     // y = S0 x once (lane c: row c, x broadcast from the forward solution)
     const double2 xs = lane < n0 ? X[(size_t)s * n0 + lane] : make_double2(0.0, 0.0);
     double2 y = make_double2(0.0, 0.0);
-    if (lane < n0) {
-        const double2 *row = S0f + (size_t)lane * n0;
+    const double2 *col = d.S0T + (size_t)f * n0 * n0 + li;
 #pragma unroll 8
-        for (int k = 0; k < n0; ++k) {
-            const double2 a = row[k], xk = rl2(xs, k);
-            y.x = fma(a.x, xk.x, fma(-a.y, xk.y, y.x));
-            y.y = fma(a.x, xk.y, fma(a.y, xk.x, y.y));
-        }
+    for (int k = 0; k < n0; ++k) {
+        const double2 a = col[(size_t)k * n0], xk = rl2(xs, k);
+        y.x = fma(a.x, xk.x, fma(-a.y, xk.y, y.x));
+        y.y = fma(a.x, xk.y, fma(a.y, xk.x, y.y));
     }
     // lane e % 64 forms entry e
     for (int e0 = 0; e0 < nvar; e0 += 64) {
@@ -322,30 +423,147 @@ __global__ __launch_bounds__(256) void k_sp_solve(SpDev d, int B, const double2 
     }
 }
 
-// Loss terms of one P-chunk and conj(w) in place of B_comb; grid (B, F).
-// Y[f][b][rows] (PREC 0 complex128, 1 complex64) holds B_comb of rows
-// p0 .. p0 + nrows - 1 of the loss component; lpart[f][b] receives the chunk's
-// sum of loss terms.
-template <int PREC, int LOSS>
+// The FP64 contraction in one pass: B_comb = fields x for 64 configurations of
+// one frequency per workgroup (16 per wave, x as matrix-core B operands in
+// registers), the loss epilogue on the accumulators, and conj(fields^H w) from
+// the same rows, whose accumulators are the B operand of the second product
+// (see fused.hip: row q + 4 m in register m of lane group q).  The four real
+// products of a complex one run as separate matrix-core operations; rows come
+// in tiles of 16 through two LDS buffers, the next one loaded into registers
+// while the current one is used.  NE: ports rounded up to 16.
+//   Matrix-core issue bounds it (16 P n0 flops per system): 64 ports, 16,384
+// points, 2,560 systems in 753 us (57 TFLOP/s), where two library products and the
+// epilogue between them took 1.71 ms and moved B_comb through memory three
+// times.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+__device__ inline f64x4 mma64(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+template <int NE, int LOSS, bool GRAD>
+__global__ __launch_bounds__(256, 2) void k_sp_fused(SpDev d, int B, int comp, int tiles_per_chunk,
+                                                     const double2 *__restrict__ Xg,
+                                                     const double *__restrict__ T,
+                                                     double2 *__restrict__ Rp,
+                                                     double *__restrict__ lpart) {
+    constexpr int KS = NE / 4, IB = NE / 16, LD = NE + 1;
+    constexpr int VPT = 16 * NE / 256;  // row entries per thread and tile
+    __shared__ double2 sGb[2][16 * LD];
+    __shared__ double sTb[2][16];
+    const int n0 = d.n0, F = d.F, P = d.P;
+    const int f = blockIdx.y, chunk = blockIdx.z;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int r16 = lane & 15, q = lane >> 4;
+    const int b = blockIdx.x * 64 + 16 * wave + r16;  // this lane's configuration
+    const int pb = chunk * tiles_per_chunk * 16;
+    const int pe = min(P, pb + tiles_per_chunk * 16);
+    const size_t prow = (size_t)d.ncomp * n0;
+    const double2 *G = d.fields64 + (size_t)f * P * prow + (size_t)comp * n0;
+    double xr[KS], xi[KS];
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+        const int k = 4 * kk + q;
+        double2 v = make_double2(0.0, 0.0);
+        if (b < B && k < n0) v = Xg[((size_t)f * B + b) * n0 + k];
+        xr[kk] = v.x;
+        xi[kk] = v.y;
+    }
+    f64x4 rr[IB], ri[IB];
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) rr[ib] = ri[ib] = f64x4{0, 0, 0, 0};
+    double lacc = 0.0;
+    double2 stg[VPT];
+    double tstg = 0.0;
+    auto fetch = [&](int p0) {  // zero rows and targets past the last point
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int e = threadIdx.x + 256 * u, row = e / NE, k = e % NE;
+            const bool in = p0 + row < P && k < n0;
+            stg[u] = in ? G[(size_t)(p0 + row) * prow + k] : make_double2(0.0, 0.0);
+        }
+        const int p = p0 + ((int)threadIdx.x & 15);
+        tstg = p < P ? T[p] : 0.0;
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int u = 0; u < VPT; ++u) {
+            const int e = threadIdx.x + 256 * u;
+            sGb[buf][(e / NE) * LD + e % NE] = stg[u];
+        }
+        if (threadIdx.x < 16) sTb[buf][threadIdx.x] = tstg;
+    };
+    fetch(pb);
+    stash(0);
+    __syncthreads();
+    for (int p0 = pb, buf = 0; p0 < pe; p0 += 16, buf ^= 1) {
+        const double2 *sG = sGb[buf];
+        fetch(min(p0 + 16, pe - 1));  // past the chunk's end: not used
+        f64x4 rx = f64x4{0, 0, 0, 0}, ry = rx, br = rx, bi = rx;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            const double2 g = sG[r16 * LD + 4 * kk + q];
+            rx = mma64(g.x, xr[kk], rx);
+            bi = mma64(g.x, xi[kk], bi);
+            ry = mma64(g.y, xi[kk], ry);
+            bi = mma64(g.y, xr[kk], bi);
+        }
+        f64x4 ni;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            double vx = rx[m] - ry[m], vy = bi[m];
+            lacc += epilogue<LOSS>(vx, vy, sTb[buf][q + 4 * m]);
+            br[m] = vx;
+            bi[m] = vy;
+            ni[m] = -vy;
+        }
+        if (GRAD) {
+            // G conj(w): re = Gr wr + Gi wi, im = Gi wr - Gr wi
+#pragma unroll
+            for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const double2 g = sG[(q + 4 * m) * LD + 16 * ib + r16];
+                    rr[ib] = mma64(g.x, br[m], rr[ib]);
+                    ri[ib] = mma64(g.y, br[m], ri[ib]);
+                    rr[ib] = mma64(g.y, bi[m], rr[ib]);
+                    ri[ib] = mma64(g.x, ni[m], ri[ib]);
+                }
+        }
+        stash(buf ^ 1);
+        __syncthreads();
+    }
+    lacc += __shfl_xor(lacc, 16);
+    lacc += __shfl_xor(lacc, 32);
+    if (b >= B) return;
+    const size_t o = ((size_t)chunk * F + f) * B + b;
+    if (q == 0) lpart[o] = lacc;
+    if (GRAD) {
+#pragma unroll
+        for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int k = 16 * ib + q + 4 * m;
+                if (k < n0) Rp[o * n0 + k] = make_double2(rr[ib][m], ri[ib][m]);
+            }
+    }
+}
+
+// Loss terms of one P-chunk and conj(w) in place of B_comb (FP32); grid (B, F).
+// Y[f][b][rows] holds B_comb of rows p0 .. p0 + nrows - 1 of the loss
+// component; lpart[f][b] receives the chunk's sum of loss terms.
+template <int LOSS>
 __global__ __launch_bounds__(256) void k_sp_epilogue(int B, int F, int rows, int p0, int nrows,
-                                                     void *Y, const double *__restrict__ T,
+                                                     float2 *__restrict__ Y,
+                                                     const double *__restrict__ T,
                                                      double *__restrict__ lpart, bool grad) {
     __shared__ double red[4];
     const int b = blockIdx.x, f = blockIdx.y;
     const size_t base = ((size_t)f * B + b) * rows;
     double acc = 0.0;
     for (int p = threadIdx.x; p < nrows; p += 256) {
-        if (PREC == 0) {
-            double2 *y = (double2 *)Y + base + p;
-            double vx = y->x, vy = y->y;
-            acc += epilogue<LOSS>(vx, vy, T[p0 + p]);
-            if (grad) *y = make_double2(vx, -vy);
-        } else {
-            float2 *y = (float2 *)Y + base + p;
-            float vx = y->x, vy = y->y;
-            acc += epilogue<LOSS>(vx, vy, (float)T[p0 + p]);
-            if (grad) *y = make_float2(vx, -vy);
-        }
+        float2 *y = Y + base + p;
+        float vx = y->x, vy = y->y;
+        acc += epilogue<LOSS>(vx, vy, (float)T[p0 + p]);
+        if (grad) *y = make_float2(vx, -vy);
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
@@ -354,15 +572,18 @@ __global__ __launch_bounds__(256) void k_sp_epilogue(int B, int F, int rows, int
     if (threadIdx.x == 0) lpart[(size_t)f * B + b] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// loss[b] = lscale * sum over f, then chunks, of lpart[c][f][b]
-__global__ void k_sp_reduce(int B, int F, int nchunk, const double *__restrict__ lpart, double lscale,
-                            double *__restrict__ loss) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
+// loss[b] = lscale * sum over chunks and f of lpart[c][f][b], one wave per
+// configuration, lanes in a fixed shuffle tree.
+__global__ __launch_bounds__(256) void k_sp_reduce(int B, int F, int nchunk,
+                                                   const double *__restrict__ lpart, double lscale,
+                                                   double *__restrict__ loss) {
+    const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (b >= B) return;  // whole wave
     double acc = 0.0;
-    for (int f = 0; f < F; ++f)
-        for (int c = 0; c < nchunk; ++c) acc += lpart[((size_t)c * F + f) * B + b];
-    loss[b] = lscale * acc;
+    for (int e = lane; e < F * nchunk; e += 64) acc += lpart[(size_t)e * B + b];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+    if (lane == 0) loss[b] = lscale * acc;
 }
 
 // Eq. 2-3 per (b, f, k)
@@ -427,15 +648,61 @@ hipError_t cgemm(rocblas_handle h, int prec, rocblas_operation ta, int m, int n,
         (rocblas_float_complex *)C, ldc, (rocblas_stride)sC, batch));
 }
 
-size_t lds_bytes(int n0) { return ((size_t)n0 * sp_ld(n0) + 64) * sizeof(double2); }
+SpLu record(const SpWork &w) { return SpLu{w.lu, w.piv, w.dinv}; }
 
-template <bool ADJ, int PREC>
-hipError_t launch_solve(const SpDev &d, int B, const double2 *values, double2 *X, void *Xg,
-                        const void *Rp, int nchunk, double rscale, double2 *grad, int32_t *status,
-                        hipStream_t st) {
+// Forward solves of the systems s0 .. s0 + count - 1 into the record's slots.
+hipError_t launch_lu(const SpDev &d, const SpWork &w, int B, int s0, int count, const double2 *values,
+                     int prec, int32_t *status, hipStream_t st) {
+    if (prec == 0)
+        hipLaunchKernelGGL(k_sp_lu<0>, dim3(count), dim3(64), 0, st, d, B, s0, values, w.X, w.Xg,
+                           record(w), status);
+    else
+        hipLaunchKernelGGL(k_sp_lu<1>, dim3(count), dim3(64), 0, st, d, B, s0, values, w.X, w.Xg,
+                           record(w), status);
+    return hipGetLastError();
+}
+
+// The adjoint solves and gradients.  A batch beyond the record's capacity is
+// factored again, slab by slab.
+hipError_t launch_adjoint(const SpDev &d, const SpWork &w, int B, const double2 *values, int nchunk,
+                          double rscale, int prec, double2 *grad, int32_t *status, hipStream_t st) {
     const int S = B * d.F;
-    hipLaunchKernelGGL((k_sp_solve<ADJ, PREC>), dim3(S), dim3(256), lds_bytes(d.n0), st, d, B, values,
-                       X, Xg, Rp, nchunk, rscale, grad, status);
+    hipError_t e;
+    for (int s0 = 0; s0 < S; s0 += w.slots) {
+        const int count = std::min(w.slots, S - s0);
+        if (S > w.slots && (e = launch_lu(d, w, B, s0, count, values, prec, status, st)) != hipSuccess)
+            return e;
+        const dim3 grid((count + 3) / 4);
+        if (prec == 0)
+            hipLaunchKernelGGL(k_sp_adjoint<0>, grid, dim3(256), 0, st, d, B, s0, count, w.X, w.Rp, nchunk,
+                               rscale, record(w), grad, status);
+        else
+            hipLaunchKernelGGL(k_sp_adjoint<1>, grid, dim3(256), 0, st, d, B, s0, count, w.X, w.Rp, nchunk,
+                               rscale, record(w), grad, status);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <int NE>
+hipError_t launch_fused(const SpDev &d, const SpWork &w, int B, const double *T, int comp, int loss_mode,
+                        bool grad, hipStream_t st) {
+    const int tiles = (d.P + 15) / 16, nck = sp_fused_chunks(d, B);
+    const int tpc = (tiles + nck - 1) / nck;
+    const dim3 grid((B + 63) / 64, d.F, (tiles + tpc - 1) / tpc);
+    const double2 *x = (const double2 *)w.Xg;
+    double2 *rp = (double2 *)w.Rp;
+#define SP_FUSED(LS, GR)                                                                              \
+    hipLaunchKernelGGL((k_sp_fused<NE, LS, GR>), grid, dim3(256), 0, st, d, B, comp, tpc, x, T, rp, \
+                       w.lpart)
+    if (loss_mode == COSIM_LOSS_MAG) {
+        if (grad) SP_FUSED(COSIM_LOSS_MAG, true);
+        else SP_FUSED(COSIM_LOSS_MAG, false);
+    } else {
+        if (grad) SP_FUSED(COSIM_LOSS_COMPLEX, true);
+        else SP_FUSED(COSIM_LOSS_COMPLEX, false);
+    }
+#undef SP_FUSED
     return hipGetLastError();
 }
 
@@ -452,31 +719,41 @@ void sp_blas_destroy(void *handle) {
     if (handle) (void)rocblas_destroy_handle((rocblas_handle)handle);
 }
 
-hipError_t sp_prep(const SpDev &d, const double2 *scc, hipStream_t st) {
-    hipLaunchKernelGGL(k_sp_prep, dim3(d.n0, d.F), dim3(64), 0, st, d.n0, d.n1, d.F, d.S0, scc,
-                       d.exc, d.K, d.r0);
+hipError_t sp_prep(const SpDev &d, const double2 *S0, const double2 *scc, hipStream_t st) {
+    hipLaunchKernelGGL(k_sp_prep, dim3(d.n0, d.F), dim3(64), 0, st, d.n0, d.n1, d.F, S0, scc, d.exc,
+                       d.KT, d.S0T, d.r0);
     return hipGetLastError();
 }
 
-hipError_t sp_set_lds_limit() {
-    const int bytes = (int)lds_bytes(kSpMaxPorts);
-    hipError_t e;
-    if ((e = hipFuncSetAttribute((const void *)k_sp_solve<false, 0>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess ||
-        (e = hipFuncSetAttribute((const void *)k_sp_solve<false, 1>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess ||
-        (e = hipFuncSetAttribute((const void *)k_sp_solve<true, 0>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess ||
-        (e = hipFuncSetAttribute((const void *)k_sp_solve<true, 1>,
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, bytes)) != hipSuccess)
-        return e;
-    return hipSuccess;
+// Chunks of whole 16-row tiles: the fewest whose workgroups fill the last round
+// of resident ones (two per compute unit) to 95%, else the best fill; 64 at
+// most, as the partial sums are written and read once per chunk.
+int sp_fused_chunks(const SpDev &d, int B) {
+    const long long wgs = (long long)((B + 63) / 64) * d.F, slots = 2LL * std::max(1, d.cus);
+    const int tiles = (d.P + 15) / 16, most = std::min(tiles, 64);
+    int best = 1;
+    double fill = 0.0;
+    for (int c = 1; c <= most; ++c) {
+        const int tpc = (tiles + c - 1) / c, cc = (tiles + tpc - 1) / tpc;
+        const long long n = wgs * cc;
+        const double x = (double)n / (double)((n + slots - 1) / slots * slots);
+        if (x > fill) {
+            fill = x;
+            best = cc;
+        }
+        if (x >= 0.95) break;
+    }
+    return best;
 }
 
-hipError_t sp_forward(const SpDev &d, int B, const double2 *values, double2 *X, void *Xg, int prec,
+hipError_t sp_forward(const SpDev &d, const SpWork &w, int B, const double2 *values, int prec,
                       int32_t *status, hipStream_t st) {
-    return prec == 0 ? launch_solve<false, 0>(d, B, values, X, Xg, nullptr, 0, 0.0, nullptr, status, st)
-                     : launch_solve<false, 1>(d, B, values, X, Xg, nullptr, 0, 0.0, nullptr, status, st);
+    const int S = B * d.F;
+    for (int s0 = 0; s0 < S; s0 += w.slots) {
+        const hipError_t e = launch_lu(d, w, B, s0, std::min(w.slots, S - s0), values, prec, status, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t sp_field(void *handle, const SpDev &d, int B, const double2 *Xg64, double2 *out,
@@ -493,12 +770,28 @@ hipError_t sp_field(void *handle, const SpDev &d, int B, const double2 *Xg64, do
 hipError_t sp_loss_and_grad(void *handle, const SpDev &d, const SpWork &w, int B,
                             const double2 *values, const double *T, int comp, int loss_mode, int prec,
                             double *loss, double2 *grad, int32_t *status, hipStream_t st) {
+    hipError_t e = sp_forward(d, w, B, values, prec, status, st);
+    if (e != hipSuccess) return e;
+    const double scale = 1.0 / ((double)d.F * d.P);
+    if (prec == 0) {
+        const bool g = grad != nullptr;
+        switch ((d.n0 + 15) / 16) {
+            case 1: e = launch_fused<16>(d, w, B, T, comp, loss_mode, g, st); break;
+            case 2: e = launch_fused<32>(d, w, B, T, comp, loss_mode, g, st); break;
+            case 3: e = launch_fused<48>(d, w, B, T, comp, loss_mode, g, st); break;
+            default: e = launch_fused<64>(d, w, B, T, comp, loss_mode, g, st); break;
+        }
+        if (e != hipSuccess) return e;
+        const int nck = sp_fused_chunks(d, B);
+        hipLaunchKernelGGL(k_sp_reduce, dim3((B + 3) / 4), dim3(256), 0, st, B, d.F, nck, w.lpart,
+                           scale, loss);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        return g ? launch_adjoint(d, w, B, values, nck, scale, 0, grad, status, st) : hipSuccess;
+    }
     rocblas_handle h = (rocblas_handle)handle;
     if (rocblas_set_stream(h, st) != rocblas_status_success) return hipErrorInvalidValue;
-    hipError_t e = sp_forward(d, B, values, w.X, w.Xg, prec, status, st);
-    if (e != hipSuccess) return e;
-    const void *fields = prec == 0 ? (const void *)d.fields64 : (const void *)d.fields32;
-    const size_t esz = prec == 0 ? sizeof(double2) : sizeof(float2);
+    const void *fields = d.fields32;
+    const size_t esz = sizeof(float2);
     const int lda = d.ncomp * d.n0;
     const size_t sA = (size_t)d.P * d.ncomp * d.n0;
     const bool want_grad = grad != nullptr;
@@ -509,16 +802,11 @@ hipError_t sp_loss_and_grad(void *handle, const SpDev &d, const SpWork &w, int B
         if ((e = cgemm(h, prec, rocblas_operation_transpose, nr, B, d.n0, A, lda, sA, w.Xg, d.n0,
                        (size_t)B * d.n0, w.Y, w.rows, (size_t)B * w.rows, d.F)) != hipSuccess)
             return e;
-#define SP_EPI(PR, LS)                                                                         \
-    hipLaunchKernelGGL((k_sp_epilogue<PR, LS>), dim3(B, d.F), dim3(256), 0, st, B, d.F, w.rows, \
-                       p0, nr, w.Y, T, w.lpart + (size_t)c * d.F * B, want_grad)
-        if (prec == 0) {
-            if (loss_mode == COSIM_LOSS_MAG) SP_EPI(0, COSIM_LOSS_MAG);
-            else SP_EPI(0, COSIM_LOSS_COMPLEX);
-        } else {
-            if (loss_mode == COSIM_LOSS_MAG) SP_EPI(1, COSIM_LOSS_MAG);
-            else SP_EPI(1, COSIM_LOSS_COMPLEX);
-        }
+#define SP_EPI(LS)                                                                         \
+    hipLaunchKernelGGL((k_sp_epilogue<LS>), dim3(B, d.F), dim3(256), 0, st, B, d.F, w.rows, \
+                       p0, nr, (float2 *)w.Y, T, w.lpart + (size_t)c * d.F * B, want_grad)
+        if (loss_mode == COSIM_LOSS_MAG) SP_EPI(COSIM_LOSS_MAG);
+        else SP_EPI(COSIM_LOSS_COMPLEX);
 #undef SP_EPI
         if ((e = hipGetLastError()) != hipSuccess) return e;
         if (!want_grad) continue;
@@ -528,15 +816,11 @@ hipError_t sp_loss_and_grad(void *handle, const SpDev &d, const SpWork &w, int B
                        (size_t)B * w.rows, Rc, d.n0, (size_t)B * d.n0, d.F)) != hipSuccess)
             return e;
     }
-    const double scale = 1.0 / ((double)d.F * d.P);
-    hipLaunchKernelGGL(k_sp_reduce, dim3((B + 255) / 256), dim3(256), 0, st, B, d.F, w.nchunk,
-                       w.lpart, scale, loss);
+    hipLaunchKernelGGL(k_sp_reduce, dim3((B + 3) / 4), dim3(256), 0, st, B, d.F, w.nchunk, w.lpart,
+                       scale, loss);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (!want_grad) return hipSuccess;
-    return prec == 0 ? launch_solve<true, 0>(d, B, values, w.X, nullptr, w.Rp, w.nchunk, scale, grad,
-                                             status, st)
-                     : launch_solve<true, 1>(d, B, values, w.X, nullptr, w.Rp, w.nchunk, scale, grad,
-                                             status, st);
+    return launch_adjoint(d, w, B, values, w.nchunk, scale, 1, grad, status, st);
 }
 
 hipError_t sp_to_c64(size_t count, const double2 *a, float2 *b, hipStream_t st) {
