@@ -22,8 +22,11 @@
 //      system) entries over the waves in a fixed order, applies the loss
 //      epilogue and stores w transposed in LDS (8 consecutive points per lane
 //      make the adjoint's B operand);
-//   3. each wave multiplies G^T for its loop range (A operands from the
-//      transposed copy of G, 8 consecutive points per lane) by w.
+//   3. each wave multiplies G^T for its loop range (A operands of 8
+//      consecutive points per lane) by w.  They come from the transposed copy
+//      of G, or, in BF16X3 with both products and up to 512 loops, from the
+//      rows the wave has already read for the forward product, turned in LDS
+//      (transpose_ops), so that G is read from memory once.
 // At the end each wave writes its rows of r per (chunk, system) in FP64 and the
 // workgroup its per-system loss; the solves sum the chunks in a fixed order.
 // No atomics: results are deterministic.
@@ -40,6 +43,7 @@
 // Workgroups are numbered so that the system blocks of one chunk of points run
 // on one XCD side by side and share the chunk's rows of G in its L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "epilogue.h"
 #include "internal.h"
@@ -116,6 +120,53 @@ struct PolBF3 {
         return o;
     }
 };
+
+// The adjoint's A operands of a wave's 32 points x 64 loops from its forward
+// operands g[kk][h] (loops 32 kk + 8 q .. + 7 of point 16 h + r16): lane (r16, q)
+// receives points 8 q .. 8 q + 7 of loop 16 kt + r16 in t[kt].  One bf16 plane at
+// a time goes through `buf`, the wave's own 4,608 bytes of LDS, as rows of points,
+// and comes back by transposing reads (measured on gfx950: the 16 lanes of a
+// group give the addresses of four rows of 16 entries, four lanes per row, and
+// lane i receives entry i of the four rows).  A wave's LDS operations stay in
+// order, so the planes need no wait between them.
+constexpr int kTurnLd = 72;  // entries per row of points, padded
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+template <int KS>
+__device__ __forceinline__ void transpose_ops(const PolBF3::Op (&g)[KS][2], int ks, int tiles, char *buf,
+                                              int r16, int q, PolBF3::Op (&t)[2 * KS]) {
+    static_assert(KS == 2, "64 loops per wave");
+    auto *m = (__attribute__((address_space(3))) short *)buf;
+    auto order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+#pragma unroll
+    for (int plane = 0; plane < 2; ++plane) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+            if (kk < ks)  // uniform
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    *(__attribute__((address_space(3))) u32x4 *)(m + (16 * h + r16) * kTurnLd + 32 * kk +
+                                                                 8 * q) =
+                        __builtin_bit_cast(u32x4, plane == 0 ? g[kk][h].h : g[kk][h].l);
+        order();
+#pragma unroll
+        for (int kt = 0; kt < 2 * KS; ++kt) {
+            if (kt >= tiles) continue;  // uniform
+            s16x4 v[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                v[e] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4 *)(m + (8 * q + 4 * e + (r16 >> 2)) * kTurnLd +
+                                                                16 * kt + 4 * (r16 & 3)));
+            typedef short s16x8 __attribute__((ext_vector_type(8)));
+            const s16x8 w = __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7);
+            (plane == 0 ? t[kt].h : t[kt].l) = __builtin_bit_cast(bf16x8, w);
+        }
+        order();
+    }
+}
 
 template <typename T>
 struct PolScalar {
@@ -222,7 +273,10 @@ __device__ __forceinline__ void mfma_block(const MfmaArgs &a, int b) {
     const int pe = min(a.P_pad, pb + a.rows_per_chunk);
     // this wave's loop steps [kb, kb + ks) of 32 loops
     const int m = a.NP >> 5;
-    const int kb = (wave * m) / W, ks = ((wave + 1) * m) / W - kb;
+    const int kb = (wave * m) / W;
+    // steps and 16-loop tiles that are padding only are left out (zeros added)
+    const int ks = max(0, min(((wave + 1) * m) / W, (a.n + 31) >> 5) - kb);
+    const int tiles = min(2 * ks, (a.n - 32 * kb + 15) >> 4);
     const int NP = a.NP;
 
     Acc *red = (Acc *)smem;
@@ -262,6 +316,9 @@ __device__ __forceinline__ void mfma_block(const MfmaArgs &a, int b) {
     const int nthr = 64 * W;
 
     constexpr bool PF = KS <= 2 && sizeof(Op) <= 32;
+    // the adjoint's operands from the forward's, in the wave's slot of red
+    constexpr bool TURN = std::is_same<Pol, PolBF3>::value && KS == 2 && FWD && ADJ;
+    static_assert(!TURN || kSub * RS * sizeof(Acc) >= kSub * kTurnLd * 2, "one plane fits the slot");
     Op ga[KS][2], gt[2 * KS];  // operands loaded ahead (PF)
     auto load_g = [&](int p, int kk, int h) {
         return Pol::load(a.G, a.Glo, (size_t)(p + 16 * h + r16) * NP + 32 * (kb + kk) + 8 * q);
@@ -280,10 +337,12 @@ __device__ __forceinline__ void mfma_block(const MfmaArgs &a, int b) {
         if (pb < pe) prefetch_g(pb);
 
     for (int p0 = pb; p0 < pe; p0 += kSub) {
-        if constexpr (PF && ADJ) {
+        if constexpr (TURN) {
+            transpose_ops(ga, ks, tiles, (char *)(red + (size_t)wave * kSub * RS), r16, q, gt);
+        } else if constexpr (PF && ADJ) {
 #pragma unroll
             for (int kt = 0; kt < 2 * KS; ++kt)
-                if (kt < 2 * ks) gt[kt] = load_gt(p0, kt);
+                if (kt < tiles) gt[kt] = load_gt(p0, kt);
         }
         // 1. partial B of this wave's loop range
         if constexpr (FWD) {
@@ -370,7 +429,7 @@ __device__ __forceinline__ void mfma_block(const MfmaArgs &a, int b) {
             // 3. r += G^T w for this wave's loops: 16 loops per tile
 #pragma unroll
             for (int kt = 0; kt < 2 * KS; ++kt) {
-                if (kt < 2 * ks) {
+                if (kt < tiles) {
                     const Op A = PF ? gt[kt] : load_gt(p0, kt);
 #pragma unroll
                     for (int t = 0; t < NC; ++t)
@@ -399,7 +458,7 @@ __device__ __forceinline__ void mfma_block(const MfmaArgs &a, int b) {
     if constexpr (ADJ) {
 #pragma unroll
         for (int kt = 0; kt < 2 * KS; ++kt) {
-            if (kt < 2 * ks) {
+            if (kt < tiles) {  // (entries past n are never read)
 #pragma unroll
                 for (int mm = 0; mm < 4; ++mm) {
                     const int k = 32 * kb + 16 * kt + Pol::row(q, mm);
