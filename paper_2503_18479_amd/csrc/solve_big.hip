@@ -334,6 +334,15 @@ __device__ inline double2 z_entry(const SysRef &r, int i, int j) {
     return make_double2(i == j ? 1.0 : 0.0, 0.0);
 }
 
+// The same entry in two parts, so that a tile's loads are issued together and
+// without a branch: w M_ij off the diagonal (0 in the padding; the address
+// stays inside M), and the diagonal entry, padding 1.
+__device__ inline double z_off(const SysRef &r, int i, int j) {
+    const double v = r.w * r.M[(size_t)min(i, r.n - 1) * r.n + min(j, r.n - 1)];
+    return i < r.n && j < r.n ? v : 0.0;
+}
+__device__ inline double2 z_diag(const SysRef &r, int i) { return z_entry(r, i, i); }
+
 // 1/a of a pivot that is checked afterwards: hardware reciprocal and two
 // Newton steps (error at the rounding of the result, no division sequence).
 __device__ inline double2 zinv_nr(double2 a) {
@@ -430,8 +439,9 @@ struct LdlLds {
     double2 sy[64 * kSuper];  // y of the same rows
     double2 sp[64][17];       // 16 columns of the diagonal block
     double2 sx[16][17];       // inverse of their unit lower triangle
-    double2 sdv[16], sdi[16]; // their pivots and 1/pivots
+    double2 sdi[16];          // 1/pivots
     double2 st[64];           // right-hand side of the block
+    double2 sz[64];           // diagonal of Z in the block (first super-panel)
     double sm[kTB / 64];
     int si[kTB / 64];
     int flag;
@@ -443,64 +453,52 @@ struct LdlLds {
 // l % 16, the whole symmetric block.  Step c subtracts l_r = a_rc / d_c times
 // row c from the rows below it; a column that has been eliminated holds the
 // matching column of X from then on (it starts as e_c), so each step costs
-// four complex multiply-adds per lane, with row c reaching the lanes as DPP
-// broadcasts inside the 16-lane rows and column c through one exchange.  A
-// serial chain of 16 steps; returns the smallest |re| + |im| of a pivot
-// (0 if one is NaN).
+// four complex multiply-adds per lane, with row c reaching the lanes as 64-bit
+// DPP broadcasts inside the 16-lane rows and column c through one exchange.  A
+// serial chain of 16 steps, straight-line code: the lanes that hold column c
+// store it as it stands at its own step (rows above c unused), the others
+// store to their own places in sx, which the inverse overwrites at the end, so
+// that no store needs a branch.
 template <int C>
 __device__ __forceinline__ double row_bcast(double x) {
     // DPP row_newbcast: lane C of each row of 16
-    const int lo = __double2loint(x), hi = __double2hiint(x);
-    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x150 + C, 0xF, 0xF, false),
-                            __builtin_amdgcn_update_dpp(lo, lo, 0x150 + C, 0xF, 0xF, false));
+    const long v = __double_as_longlong(x);
+    return __longlong_as_double(__builtin_amdgcn_mov_dpp(v, 0x150 + C, 0xF, 0xF, true));
 }
 __device__ inline double lane_value(double x, int src) {  // src uniform over the wave
     return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
                             __builtin_amdgcn_readlane(__double2loint(x), src));
 }
 template <int C>
-__device__ __forceinline__ void ldl16_step(double2 (&a)[4], double2 (&v)[4], double2 &dv, double2 &di,
-                                           double &dmin, int r, int q) {
+__device__ __forceinline__ void ldl16_step(LdlLds &m, int p0, double2 (&a)[4], int r, int q) {
     constexpr int Q = C >> 2, U = C & 3;
     const double2 d = make_double2(lane_value(a[U].x, 16 * Q + C), lane_value(a[U].y, 16 * Q + C));
     const double2 col = make_double2(__shfl(a[U].x, 16 * Q + r), __shfl(a[U].y, 16 * Q + r));
+    double2 *dst = q == Q ? &m.sp[p0 + r][4 * Q] : &m.sx[r][4 * q];
+    dst[U] = a[U];
     const double2 inv = zinv_nr(d);
-    const double ad = fabs(d.x) + fabs(d.y);
-    dmin = ad == ad ? fmin(dmin, ad) : 0.0;
-    if (r == C) {
-        dv = d;
-        di = inv;
-    }
     const double2 l = r > C ? zmul(col, inv) : make_double2(0.0, 0.0);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int k = 1; k <= 4; ++k) {  // the next pivot's column first, column c last
+        const int u = (U + k) & 3;
         const double2 row = make_double2(row_bcast<C>(a[u].x), row_bcast<C>(a[u].y));
-        if (u == U && q == Q) {
-            v[u] = a[u];
-            a[u] = make_double2(r == C ? 1.0 : -l.x, -l.y);
-        } else {
-            a[u] = zfms(a[u], l, row);
+        a[u] = zfms(a[u], l, row);
+        if (u == U) {
+            a[u].x = q == Q ? (r == C ? 1.0 : -l.x) : a[u].x;
+            a[u].y = q == Q ? -l.y : a[u].y;
         }
     }
-    if constexpr (C + 1 < 16) ldl16_step<C + 1>(a, v, dv, di, dmin, r, q);
+    if constexpr (C + 1 < 16) ldl16_step<C + 1>(m, p0, a, r, q);
 }
-__device__ __forceinline__ double ldl16(LdlLds &m, int p0, int lane) {
+__device__ __forceinline__ void ldl16(LdlLds &m, int p0, int lane) {
     const int r = lane & 15, q = lane >> 4;
-    double2 a[4], v[4], dv, di;
+    double2 a[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) a[u] = m.sp[p0 + r][4 * q + u];
-    double dmin = __builtin_inf();
-    ldl16_step<0>(a, v, dv, di, dmin, r, q);
+    ldl16_step<0>(m, p0, a, r, q);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        m.sp[p0 + r][4 * q + u] = v[u];  // column c as it stood at its own step (rows above c unused)
-        m.sx[r][4 * q + u] = a[u];
-    }
-    if (lane < 16) {
-        m.sdv[lane] = dv;
-        m.sdi[lane] = di;
-    }
-    return dmin;
+    for (int u = 0; u < 4; ++u) m.sx[r][4 * q + u] = a[u];
+    if (lane < 16) m.sdi[lane] = zinv_nr(m.sp[p0 + lane][lane]);
 }
 
 // The 16-column blocks of a 64 x 64 diagonal block that wave w holds as
@@ -509,6 +507,32 @@ __device__ __forceinline__ double ldl16(LdlLds &m, int p0, int lane) {
 // most three products and two distinct column blocks.
 __device__ inline int diag_rb(int w, int q) { return w == 3 ? 2 + q : (w == 2 ? 1 + q : q); }
 __device__ inline int diag_cb(int w, int q) { return w == 3 ? 2 + q : (w == 2 ? 1 : (w == 1 ? 3 : 0)); }
+
+// What a wave reads of Z (its diagonal entries excepted in the first
+// super-panel: sz) and of the right-hand side (lanes of its first column
+// block) for the diagonal block, loaded ahead of the sums over U: alone, behind
+// them, these loads and their address chain took 5 us per block.
+struct DiagIn {
+    double2 z[3][4], b;
+};
+template <typename T2>
+__device__ __forceinline__ void ldl_diag_load(int NP, const SysRef &sys, int ib, int js,
+                                              const T2 *__restrict__ A, const double2 *__restrict__ D,
+                                              DiagIn &in) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int g = lane >> 4, r16 = lane & 15, k0 = 64 * ib;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        if (q >= (wv < 2 ? 3 : 2)) continue;
+        const int row = k0 + 16 * diag_rb(wv, q) + g, col = k0 + 16 * diag_cb(wv, q) + r16;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            in.z[q][e] = js == 0 ? make_double2(0.0, z_off(sys, row + 4 * e, col))
+                                 : ld2(A[(size_t)(row + 4 * e) * NP + col]);
+    }
+    if (sizeof(T2) == sizeof(double2) && lane < 16)
+        in.b = rhs_base(sys, k0 + 16 * diag_cb(wv, 0) + r16, js, D + NP);
+}
 
 // Diagonal block ib: Z_ii - sum over the super-panel's rows [64 js, 64 ib) of
 // u d u^T, its L D L^T and X = L^-1, in 16-column sub-panels p:
@@ -520,17 +544,18 @@ __device__ inline int diag_cb(int w, int q) { return w == 3 ? 2 + q : (w == 2 ? 
 //      wave owns a block column j of the inverse, whose accumulators are in
 //      the layout of the B operand of both products.
 // Everything but the pivots' chain runs on FP64 matrix cores, also for
-// complex64 storage.  Bounded by the chain of 64 pivots and 16 barriers: the
-// first block of 8 systems takes 37 us with its input checks, where the whole
-// block eliminated in LDS with 80 barriers took 54.
-template <typename T2, class Src>
-__device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, int js, T2 *__restrict__ A,
+// complex64 storage.  Bounded by the chain of 64 pivots (2.4 us per 16, issue
+// and latency of one wave; 4.2 with two 32-bit DPP moves per value, selects
+// and the pivots' check inside the chain) and 16 barriers: the first block of 8
+// systems takes 31 us with its input checks, where the whole block eliminated
+// in LDS with 80 barriers took 54.
+template <typename T2>
+__device__ __forceinline__ void ldl_diag(int NP, int s, const DiagIn &in, int ib, int js, T2 *__restrict__ A,
                                          T2 *__restrict__ XT, double2 *__restrict__ D,
                                          int *__restrict__ fmt, double zmax, LdlLds &m) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane >> 4, r16 = lane & 15;
     const int k0 = 64 * ib, j0 = 64 * js;
-    const SysRef sys = src.ref(s);
     f64x4 Cr[3], Ci[3], Yr[3], Yi[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) Cr[q] = Ci[q] = Yr[q] = Yi[q] = f64x4{0, 0, 0, 0};
@@ -561,11 +586,15 @@ __device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, 
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             if (q >= nq) continue;
-            const int row = k0 + 16 * diag_rb(wv, q) + g, col = k0 + 16 * diag_cb(wv, q) + r16;
+            const int row = 16 * diag_rb(wv, q) + g, col = 16 * diag_cb(wv, q) + r16;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const double2 z = js == 0 ? z_entry(sys, row + 4 * e, col)
-                                          : ld2(A[(size_t)(row + 4 * e) * NP + col]);
+                double2 z = in.z[q][e];
+                if (js == 0 && diag_rb(wv, q) == diag_cb(wv, q)) {
+                    const double2 zd = m.sz[row + 4 * e];
+                    z.x = row + 4 * e == col ? zd.x : 0.0;
+                    z.y = row + 4 * e == col ? zd.y : z.y;
+                }
                 Cr[q][e] = z.x - Cr[q][e];
                 Ci[q][e] = z.y - Ci[q][e];
             }
@@ -578,13 +607,11 @@ __device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, 
         yacc.y += __shfl_xor(yacc.y, 32);
         if (lane < 16) {
             const int c = 16 * diag_cb(wv, 0) + r16;
-            const double2 b = rhs_base(sys, k0 + c, js, D + NP);
-            m.st[c] = make_double2(b.x - yacc.x, b.y - yacc.y);
+            m.st[c] = make_double2(in.b.x - yacc.x, in.b.y - yacc.y);
         }
     }
     T2 *X = XT + (size_t)ib * 64 * 64;
     const int yj = wv == 0 ? 0 : (wv == 2 ? 1 : (wv == 1 ? 2 : 3));  // block column of the inverse
-    double dmin = __builtin_inf();
     for (int p = 0; p < 4; ++p) {
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
@@ -599,7 +626,7 @@ __device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, 
             }
         }
         __syncthreads();
-        if (wv == 0) dmin = fmin(dmin, ldl16(m, 16 * p, lane));
+        if (wv == 0) ldl16(m, 16 * p, lane);
         __syncthreads();
         if (wv > p) {  // V of row block wv
             f64x4 vr = f64x4{0, 0, 0, 0}, vi = vr;
@@ -673,15 +700,22 @@ __device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, 
             const int c = tid >> 4;
             for (int rr = 16 * p + (tid & 15); rr < 64; rr += 16) {
                 if (rr < 16 * p + c) continue;
-                const double2 v = rr == 16 * p + c ? m.sdv[c] : m.sp[rr][c];
-                A[(size_t)(k0 + 16 * p + c) * NP + k0 + rr] = st2<T2>(v);
+                A[(size_t)(k0 + 16 * p + c) * NP + k0 + rr] = st2<T2>(m.sp[rr][c]);
             }
             if (tid < 16) D[k0 + 16 * p + tid] = m.sdi[tid];
         }
         __syncthreads();
     }
+    if (wv == 0) {  // the pivots are on the diagonal of each sub-panel
+        const double2 d = m.sp[lane][r16];
+        double dmin = fabs(d.x) + fabs(d.y);
+        dmin = dmin == dmin ? dmin : 0.0;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) dmin = fmin(dmin, __shfl_xor(dmin, off));
+        if (lane == 0 && !(dmin >= 1e-5 * zmax)) fmt[s] = kFmtNeedsPivot;
+    }
     if (kY) {  // y = X st (X^T rows just written by this workgroup)
-        double2 *red = &m.sp[0][0];
+        double2 *red = m.sd;
         const int rr = tid & 63, part = tid >> 6;
         double2 acc = make_double2(0.0, 0.0);
         if (part <= (rr >> 4))
@@ -697,7 +731,6 @@ __device__ __forceinline__ void ldl_diag(int NP, int s, const Src &src, int ib, 
             D[NP + k0 + tid] = y;
         }
     }
-    if (tid == 0 && !(dmin >= 1e-5 * zmax)) fmt[s] = kFmtNeedsPivot;
 }
 
 // Workgroups of a system consecutive on one XCD (workgroups are dealt to the
@@ -709,6 +742,20 @@ __device__ inline int xcd_system(int id, int T, int *item) {
     return 8 * (k / T) + (id & 7);
 }
 
+// The same with the items t = 0 of all systems dealt first: they are the long
+// ones (a step's diagonal block), and the short ones then fill in behind them
+// instead of the launch ending on a few long ones.
+__device__ inline int xcd_system_first(int id, int S, int T, int *item) {
+    const int S8 = (S + 7) & ~7;
+    if (id < S8) {
+        *item = 0;
+        return id;
+    }
+    const int s = xcd_system(id - S8, T - 1, item);
+    ++*item;
+    return s;
+}
+
 // The first step: input flags, the largest diagonal |Z_kk|, diagonal block 0.
 template <typename T2, class Src>
 __global__ __launch_bounds__(kTB, 2) void k_ldl_start(int NP, int S, Src src, T2 *__restrict__ Aall,
@@ -718,6 +765,8 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_start(int NP, int S, Src src, T2
     const int s = blockIdx.x, tid = threadIdx.x;
     if (s >= S) return;  // whole workgroup
     const SysRef r = src.ref(s);
+    DiagIn in;
+    ldl_diag_load(NP, r, 0, 0, Aall, Dall, in);
     if (tid == 0) m.flag = 0;
     __syncthreads();
     double zm = 0.0;
@@ -737,17 +786,21 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_start(int NP, int S, Src src, T2
         zmax[s] = zm;
     }
     if (bad) return;  // whole workgroup: left to the pivoted LU
-    ldl_diag(NP, s, src, 0, 0, Aall + (size_t)s * NP * NP, Xall + (size_t)s * 64 * NP,
+    if (tid < 64) m.sz[tid] = z_diag(r, tid);
+    __syncthreads();
+    ldl_diag(NP, s, in, 0, 0, Aall + (size_t)s * NP * NP, Xall + (size_t)s * 64 * NP,
              Dall + (size_t)s * 2 * NP, fmt, zm, m);
 }
 
 // A 64 x 64 tile of the trailing matrix as accumulators: each wave holds 64
 // rows of its 16 columns, so that block row b's product with X_b takes them
 // as the B operand where they are.  base + rows (and yacc) as in acc_utu.
-template <typename T2, bool Y>
+// DIAG: the tile may be a diagonal one.
+template <typename T2, bool DIAG, bool Y>
 __device__ __forceinline__ void ldl_tile(int NP, const SysRef &sys, int rb, int cbk, int js, int j1,
                                          const T2 *__restrict__ A, const double2 *sd,
-                                         const double2 *sy, double2 &yacc, int g, int r16, int wv, typename Acc4<typename Scal<T2>::type>::type (&Cr)[4],
+                                         const double2 *sy, double2 &yacc, int g,
+                                         int r16, int wv, typename Acc4<typename Scal<T2>::type>::type (&Cr)[4],
                                          typename Acc4<typename Scal<T2>::type>::type (&Ci)[4]) {
     typedef typename Scal<T2>::type T;
     typedef typename Acc4<T>::type V4;
@@ -760,15 +813,49 @@ __device__ __forceinline__ void ldl_tile(int NP, const SysRef &sys, int rb, int 
     }
     const int cb[1] = {col};
     acc_utu<T2, T, 4, 1, Y>(A, NP, 64 * js, j1, ca, cb, sd, sy, g, Cr, Ci, yacc);
+    // Z in batches of QB x 4 entries, the loads of a batch issued together; the
+    // trailing update, with three waves per SIMD, has registers for one row of
+    // blocks at a time (all four at two waves: 2.66 ms against 2.53, 1,024 loops).
+    constexpr int QB = DIAG ? 1 : 4;
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q0 = 0; q0 < 4; q0 += QB) {
+        if (DIAG && js == 0 && rb == cbk) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int row = 64 * rb + 16 * q + acc_row<T>(g, e);
-            const double2 z = js == 0 ? z_entry(sys, row, col) : ld2(A[(size_t)row * NP + col]);
-            Cr[q][e] = (T)z.x - Cr[q][e];
-            Ci[q][e] = (T)z.y - Ci[q][e];
+            for (int e = 0; e < 4; ++e) {
+                const double2 z = z_entry(sys, 64 * rb + 16 * q0 + acc_row<T>(g, e), col);
+                Cr[q0][e] = (T)z.x - Cr[q0][e];
+                Ci[q0][e] = (T)z.y - Ci[q0][e];
+            }
+        } else if (js == 0) {
+            double zo[QB][4];
+#pragma unroll
+            for (int q = 0; q < QB; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    zo[q][e] = z_off(sys, 64 * rb + 16 * (q0 + q) + acc_row<T>(g, e), col);
+#pragma unroll
+            for (int q = 0; q < QB; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    Cr[q0 + q][e] = (T)0 - Cr[q0 + q][e];
+                    Ci[q0 + q][e] = (T)zo[q][e] - Ci[q0 + q][e];
+                }
+        } else {
+            T2 z[QB][4];
+#pragma unroll
+            for (int q = 0; q < QB; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    z[q][e] = A[(size_t)(64 * rb + 16 * (q0 + q) + acc_row<T>(g, e)) * NP + col];
+#pragma unroll
+            for (int q = 0; q < QB; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    Cr[q0 + q][e] = z[q][e].x - Cr[q0 + q][e];
+                    Ci[q0 + q][e] = z[q][e].y - Ci[q0 + q][e];
+                }
         }
+    }
 }
 
 // Block row kb: workgroup t of a system forms U_kb,i of block column
@@ -778,7 +865,9 @@ __device__ __forceinline__ void ldl_tile(int NP, const SysRef &sys, int rb, int 
 // FP64 matrix-core issue bounds it for many systems, the chain of the t = 0
 // workgroup for few.  Factorisation of 256 systems of 1,024 loops (all steps):
 // 8.2 ms where separate assembly, diagonal, panel and update launches after
-// every 64 columns took 11.6; of 160 of 256 loops 0.30 ms, 0.43 before.
+// every 64 columns took 11.6, and 6.8 ms with the t = 0 workgroups dealt first
+// and Z loaded in batches without branches; of 160 of 256 loops 0.43, 0.30 and
+// now 0.26 ms.
 template <typename T2, class Src>
 __global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int kb, int js, int T,
                                                      T2 *__restrict__ Aall, T2 *__restrict__ Xall,
@@ -788,7 +877,7 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int
     typedef typename Acc4<Ts>::type V4;
     __shared__ LdlLds m;
     int t;
-    const int s = xcd_system(blockIdx.x, T, &t);
+    const int s = xcd_system_first(blockIdx.x, S, T, &t);
     if (s >= S) return;  // whole workgroup
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int g = lane >> 4, r16 = lane & 15;
@@ -803,12 +892,14 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int
         m.sd[j] = D[64 * js + j];
         if (t == 0) m.sy[j] = D[NP + 64 * js + j];
     }
+    const SysRef sys = src.ref(s);
+    if (t == 0 && js == 0 && tid < 64) m.sz[tid] = z_diag(sys, 64 * ib + tid);
     __syncthreads();
     {
-        const SysRef sys = src.ref(s);
         V4 Cr[4], Ci[4], Ur[4], Ui[4];
         double2 none = make_double2(0.0, 0.0);
-        ldl_tile<T2, false>(NP, sys, kb, ib, js, 64 * kb, A, m.sd, nullptr, none, g, r16, wv, Cr, Ci);
+        ldl_tile<T2, false, false>(NP, sys, kb, ib, js, 64 * kb, A, m.sd, nullptr, none, g, r16,
+                                   wv, Cr, Ci);
         const T2 *X = XT + (size_t)kb * 64 * 64;
 #pragma unroll
         for (int rb = 0; rb < 4; ++rb) {
@@ -836,7 +927,9 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int
     }
     if (t != 0) return;  // whole workgroup
     __syncthreads();     // the rows of block kb are operands of the diagonal block
-    ldl_diag(NP, s, src, ib, js, A, XT, D, fmt, zmax[s], m);
+    DiagIn in;
+    ldl_diag_load(NP, sys, ib, js, A, D, in);
+    ldl_diag(NP, s, in, ib, js, A, XT, D, fmt, zmax[s], m);
 }
 
 // After the super-panel of blocks js .. ns - 1: its rows subtracted from the
@@ -844,7 +937,7 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int
 // diagonal tile, which the last step has taken care of), and from the
 // right-hand side of the rows of the diagonal tiles.
 template <typename T2, class Src>
-__global__ __launch_bounds__(kTB, 2) void k_ldl_trail(int NP, int S, Src src, int js, int ns, int T,
+__global__ __launch_bounds__(kTB, 3) void k_ldl_trail(int NP, int S, Src src, int js, int ns, int T,
                                                       T2 *__restrict__ Aall,
                                                       double2 *__restrict__ Dall,
                                                       const int *__restrict__ fmt) {
@@ -869,11 +962,11 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_trail(int NP, int S, Src src, in
         sd[j] = D[64 * js + j];
         if (kY) sy[j] = D[NP + 64 * js + j];
     }
-    __syncthreads();
     const SysRef sys = src.ref(s);
+    __syncthreads();
     V4 Cr[4], Ci[4];
     double2 yacc = make_double2(0.0, 0.0);
-    ldl_tile<T2, kY>(NP, sys, rb, cb, js, 64 * ns, A, sd, sy, yacc, g, r16, wv, Cr, Ci);
+    ldl_tile<T2, true, kY>(NP, sys, rb, cb, js, 64 * ns, A, sd, sy, yacc, g, r16, wv, Cr, Ci);
     if (kY && rb == cb) {
         yacc.x += __shfl_xor(yacc.x, 16);
         yacc.y += __shfl_xor(yacc.y, 16);
