@@ -992,14 +992,16 @@ int cosim_solve(cosim_plan_t p, int B, int F, const double *C_d, const double *o
                           status_d, st));
     } else if (p->ldl_ok) {
         HIP_TRY(launch_ldl(p->NP, p->n, S, F, p->M_d, p->R_d, C_d, omega_d, p->phi_d, p->fac, I,
-                           status_d, st));
+                           status_d, p->rec_status, st));
     } else {
         HIP_TRY(launch_solve_forward(p->NP, p->n, S, F, p->M_d, p->R_d, p->phi_d, C_d, omega_d,
                                      I, status_d, p->fac, st));
     }
-    // the forward status travels with the record: the adjoint replay starts from it
-    HIP_TRY(hipMemcpyAsync(p->rec_status, status_d, (size_t)S * sizeof(int32_t),
-                           hipMemcpyDeviceToDevice, st));
+    // the forward status travels with the record: the adjoint replay starts from
+    // it (launch_ldl has copied it)
+    if (big_plan(p->NP) || !p->ldl_ok)
+        HIP_TRY(hipMemcpyAsync(p->rec_status, status_d, (size_t)S * sizeof(int32_t),
+                               hipMemcpyDeviceToDevice, st));
     p->rec_B = B;
     p->rec_F = F;
     p->rec_S = (size_t)S;
@@ -1062,9 +1064,9 @@ int cosim_field_backward(cosim_plan_t p, int B, int F, const double *C_d, const 
     double2 *I = (double2 *)I_d;  // read only by the adjoint solves
     if (reuse) {
         // the forward status is where the replay starts
-        HIP_TRY(hipMemcpyAsync(status_d, p->rec_status, S * sizeof(int32_t),
-                               hipMemcpyDeviceToDevice, st));
         if (big_plan(p->NP)) {
+            HIP_TRY(hipMemcpyAsync(status_d, p->rec_status, S * sizeof(int32_t),
+                                   hipMemcpyDeviceToDevice, st));
             const BigFactor bf = big_factor_args(p);
             const BigRefine rf = big_refine_args(p, COSIM_FP64);
             HIP_TRY(big_solve(bf, rf, p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d,
@@ -1073,7 +1075,7 @@ int cosim_field_backward(cosim_plan_t p, int B, int F, const double *C_d, const 
         } else {
             HIP_TRY(launch_replay_adjoint(p->NP, p->n, (int)S, F, p->fac, C_d, omega_d, I,
                                           p->rpart, sh.nchunk, 0.5, p->gsys, nullptr, status_d,
-                                          st));
+                                          st, FinalSums{}, p->rec_status));
         }
     } else if (big_plan(p->NP)) {
         const BigFactor bf = big_factor_args(p);
@@ -1238,7 +1240,7 @@ static int loss_and_grad_impl(cosim_plan_t p, int B, int F, const double *C_d, c
     }
     if (p->ldl_ok) {
         HIP_TRY(launch_ldl(p->NP, p->n, (int)S, F, p->M_d, p->R_d, C_d, omega_d, p->phi_d,
-                           w.fac, w.I, status_d, st));
+                           w.fac, w.I, status_d, nullptr, st));
     } else {
         HIP_TRY(launch_solve_forward(p->NP, p->n, (int)S, F, p->M_d, p->R_d, p->phi_d, C_d,
                                      omega_d, w.I, status_d, w.fac, st));

@@ -64,12 +64,14 @@ hipError_t launch_assemble_M(int n, int max_segs, const int32_t *seg_off_d, cons
                              const double *wire_a_d, const GLRule &gl, double *M_d,
                              hipStream_t st);
 
-// Record of a factorisation, per system s, in one of two formats (fmt[s]):
+// Record of a factorisation, per system s, in one of three formats (fmt[s]):
 //   kFmtLDL: strictly lower part of Z = L D L^T packed by columns inside the
 //            system's NP*NP slot: L_ik (i > k) at L[s*NP*NP + ldl_col(NP, k) +
 //            i - k - 1]; piv_val[s][k] = 1/d_k;
 //   kFmtGJ : L[s][k][i] = multiplier of Gauss-Jordan step k for row i,
-//            piv_row[s][k] = pivot row, piv_val[s][k] = pivot value.
+//            piv_row[s][k] = pivot row, piv_val[s][k] = pivot value;
+//   kFmtInv: (NP = 64) X^T, X = L^-1 of Z = L D L^T, row-major [64][64], only
+//            the 16 x 16 blocks of X's lower triangle; piv_val[s][k] = 1/d_k.
 struct GJFactor {
     double2 *L = nullptr;
     int *piv_row = nullptr;
@@ -80,16 +82,18 @@ constexpr int kFmtLDL = 0, kFmtGJ = 1, kFmtNeedsPivot = 2;
 // above 64 loops with refinement on: the FP32 record did not converge in the
 // forward (or only in the adjoint) solve, so the system holds a pivoted FP64 record
 constexpr int kFmtRefineFailed = 3, kFmtRefineFailedAdj = 4;
+constexpr int kFmtInv = 5;
 // first element of column k in the packed LDL^T record (columns of NP - 1 - k)
 __host__ __device__ constexpr int ldl_col(int NP, int k) { return k * (2 * NP - k - 1) / 2; }
 constexpr int kFlagPivot = 1 << 16;  // kernel-internal status bit, never returned
 
 // LDL^T fast path (all R_k > 0): factorises, records and solves,
 // I = Z^-1 (E - j w Phi) in I_d, with pivoted Gauss-Jordan (and a kFmtGJ
-// record) for the systems that need pivoting.
+// record) for the systems that need pivoting.  rec_status_d (optional, [S])
+// receives a copy of the status.
 hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const double *R_d,
                       const double *C_d, const double *omega_d, const double *phi_d, GJFactor fac,
-                      double2 *I_d, int32_t *status_d, hipStream_t st);
+                      double2 *I_d, int32_t *status_d, int32_t *rec_status_d, hipStream_t st);
 // The final sums of a call with one frequency, formed by the adjoint replay in
 // place of launch_reduce when grad is set: dL/dC [S][n] and the loss [S] from
 // the partial losses [nchunk][S].
@@ -99,12 +103,14 @@ struct FinalSums {
     double lscale = 0.0;
 };
 // Adjoint solve from the record and the per-system gradient terms.
-// mu_d (optional, [S][n]): the adjoint solution itself.
+// mu_d (optional, [S][n]): the adjoint solution itself.  status_in_d: the
+// forward status that status_d continues, when it is not status_d itself.
 hipError_t launch_replay_adjoint(int NP, int n, int S, int F, GJFactor fac, const double *C_d,
                                  const double *omega_d, double2 *I_d, const double2 *rpart_d,
                                  int nchunk, double rscale, double *gsys_d, double2 *mu_d,
                                  int32_t *status_d, hipStream_t st,
-                                 const FinalSums &fin = FinalSums{});
+                                 const FinalSums &fin = FinalSums{},
+                                 const int32_t *status_in_d = nullptr);
 
 // Forward solve by pivoted Gauss-Jordan: Z I = E - j w Phi for S = B*F systems
 // (s = b*F + f); records the elimination (kFmtGJ) in `fac` when fac.L is set.

@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "ldl_block.h"
 
 namespace cosim {
 
@@ -970,7 +971,7 @@ __device__ __forceinline__ void small32_system(
     Small32Lds &lds, int s, int n, int S, int F, const double *__restrict__ M,
     const double *__restrict__ Rv, const double *__restrict__ C, const double *__restrict__ omega,
     const double *__restrict__ phi, const GJFactor &fac, double2 *__restrict__ I,
-    int32_t *__restrict__ status) {
+    int32_t *__restrict__ status, int32_t *__restrict__ rec_status) {
     const int lane = threadIdx.x;
     double2 lrow[4][8], x;
     int flag;
@@ -980,6 +981,7 @@ __device__ __forceinline__ void small32_system(
     if (pivot) {  // uniform
         gj_system<32, false>(lds.gj, s, n, S, F, M, Rv, phi, C, omega, nullptr, nullptr, 0, 0.0, I,
                              nullptr, status, false, fac, false);
+        if (rec_status && lane == 0) rec_status[s] = status[s];
         return;
     }
     if (lane >= n) x = make_double2(0.0, 0.0);
@@ -995,7 +997,11 @@ __device__ __forceinline__ void small32_system(
         nonfinite = !(isfinite(x.x) && isfinite(x.y));
     }
     const bool any = __ballot(nonfinite) != 0;
-    if (lane == 0) status[s] = flag | (any ? COSIM_SYS_NONFINITE : 0);
+    if (lane == 0) {
+        flag |= any ? COSIM_SYS_NONFINITE : 0;
+        status[s] = flag;
+        if (rec_status) rec_status[s] = flag;
+    }
 }
 // WPE waves per SIMD: 2 while every system is resident at once (no spills on
 // the single wave's way), 3 beyond (2,100 systems of 25 loops: 33 us against 39).
@@ -1004,9 +1010,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
     const double *__restrict__ C, const double *__restrict__ omega,
     const double *__restrict__ phi, GJFactor fac, double2 *__restrict__ I,
-    int32_t *__restrict__ status) {
+    int32_t *__restrict__ status, int32_t *__restrict__ rec_status) {
     __shared__ Small32Lds lds;
-    small32_system(lds, blockIdx.x, n, S, F, M, Rv, C, omega, phi, fac, I, status);
+    small32_system(lds, blockIdx.x, n, S, F, M, Rv, C, omega, phi, fac, I, status, rec_status);
 }
 template <int WPE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void k_small32_group(
@@ -1015,7 +1021,176 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void 
     const int sg = blockIdx.x;
     const SmallInst &e = g.in[group_member(g, sg)];
     small32_system(lds, sg - e.s0, e.n, e.S, e.F, e.M, e.R, e.C, e.omega, e.phi, e.fac, e.I,
-                   e.status);
+                   e.status, nullptr);
+}
+
+// ---- 33 to 64 loops, few systems -------------------------------------------
+// A workgroup of four waves per system: L D L^T of the whole matrix on
+// accumulators (ldl_block), with X = L^-1 recorded in place of L (kFmtInv), so
+// that both triangular solves, here and in the adjoint, are products with X
+// instead of chains of 64 columns; the pivoted elimination, if it is needed,
+// runs in the same launch.  Only latency counts here: 48 systems of 64 loops
+// take 28.8 us forward and 8.8 us in the adjoint, where a wave per system, the
+// launch for the pivoted ones and the replay took 47.4 and 25.2.  The line is
+// drawn by what a plan has, not by what a launch has, so that a member of a
+// group takes the route (and gets the bits) it has alone: with more systems the
+// four waves of each cost more than they save (groups of 24 plans of 64 loops,
+// whole call: 8 systems each 238 us against 282, 32 each 285 against 296, 48
+// each 336 against 332, 64 each 363 against 344).
+constexpr int kFewSystems = 48;
+
+union Small64Lds {
+    struct {
+        BlockLds b;
+        double2 red[256], v[64];
+        int pivot;
+        bool nonfinite;
+    } x;
+    GjLds<64> gj;
+    __device__ Small64Lds() {}
+};
+
+// X^T v for the record's X: thread t returns its share, rows 16 (t % 4) ..
+// + 15 of column t / 4, loaded beforehand by block_xt_load; summed over the
+// four threads by the caller.
+__device__ __forceinline__ void block_xt_load(const double2 *X, int tid, double2 (&x)[16]) {
+    const int c = tid >> 2, part = tid & 3;
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        x[i] = part >= (c >> 4) ? X[c * 64 + 16 * part + i] : make_double2(0.0, 0.0);
+}
+__device__ __forceinline__ double2 block_xt_times(const double2 (&x)[16], const double2 *v, int tid) {
+    double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc = zfma(acc, x[i], v[16 * (tid & 3) + i]);
+#pragma unroll
+    for (int off = 1; off <= 2; off <<= 1) {
+        acc.x += __shfl_xor(acc.x, off);
+        acc.y += __shfl_xor(acc.y, off);
+    }
+    return acc;
+}
+
+__device__ __forceinline__ void small64_system(Small64Lds &lds, int s, int n, int S, int F,
+                                               const double *__restrict__ M,
+                                               const double *__restrict__ Rv,
+                                               const double *__restrict__ phi,
+                                               const double *__restrict__ C,
+                                               const double *__restrict__ omega, const GJFactor &fac,
+                                               double2 *__restrict__ I, int32_t *__restrict__ status,
+                                               int32_t *__restrict__ rec_status) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int g = lane >> 4, r16 = lane & 15;
+    const int b = s / F, f = s - b * F;
+    const double w = omega[f];
+    const double *Cb = C + (size_t)b * n;
+    auto &x = lds.x;
+    // Z off the diagonal (clamped addresses, so that all loads are in flight)
+    double zo[3][4];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int i = 16 * diag_rb(wv, q) + g + 4 * e, j = 16 * diag_cb(wv, q) + r16;
+            if (q < (wv < 2 ? 3 : 2)) {
+                const double v = w * M[(size_t)min(i, n - 1) * n + min(j, n - 1)];
+                zo[q][e] = i < n && j < n ? v : 0.0;
+            }
+        }
+    int flag = 0;       // of wave 0
+    double zmax = 0.0;  // of wave 0
+    if (wv == 0) {
+        const int k = min(lane, n - 1);
+        const double c = Cb[k], r = Rv[k], xm = w * M[(size_t)k * n + k];
+        const double2 rhs = loop_voltage(phi, n, k, w);
+        const bool real = lane < n;
+        if (__ballot(real && (isnan(c) || c == 0.0 || !isfinite(w) || w == 0.0)))
+            flag = COSIM_SYS_BAD_INPUT;
+        if (__ballot(real && c < 0.0)) flag |= COSIM_SYS_NEGATIVE_C;
+        const double xk = xm - 1.0 / (w * c);
+        x.b.sz[lane].x = real ? r : 1.0;
+        x.b.sz[lane].y = real ? xk : 0.0;
+        x.b.st[lane].x = real ? rhs.x : 0.0;
+        x.b.st[lane].y = real ? rhs.y : 0.0;
+        zmax = real ? fabs(r) + fabs(xk) : 0.0;
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) zmax = fmax(zmax, __shfl_xor(zmax, off));
+        if (lane == 0) {
+            x.pivot = (flag & COSIM_SYS_BAD_INPUT) != 0;
+            x.nonfinite = false;
+        }
+    }
+    __syncthreads();
+    double2 *X = fac.L + (size_t)s * 64 * 64;
+    if (!x.pivot) {  // uniform
+        f64x4 Cr[3], Ci[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            Cr[q] = Ci[q] = f64x4{0, 0, 0, 0};
+            if (q >= (wv < 2 ? 3 : 2)) continue;
+            const int row = 16 * diag_rb(wv, q) + g, col = 16 * diag_cb(wv, q) + r16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                Ci[q][e] = zo[q][e];
+                if (diag_rb(wv, q) == diag_cb(wv, q)) {
+                    const double2 zd = x.b.sz[row + 4 * e];
+                    Cr[q][e] = row + 4 * e == col ? zd.x : 0.0;
+                    Ci[q][e] = row + 4 * e == col ? zd.y : zo[q][e];
+                }
+            }
+        }
+        ldl_block<double2, false>(x.b, Cr, Ci, X, nullptr, 64, fac.piv_val + (size_t)s * 64);
+        if (wv == 0) {
+            const double dmin = block_min_pivot(x.b, lane, n);
+            if (lane == 0) x.pivot = !(dmin >= 1e-5 * zmax);
+        }
+        double2 xt[16];
+        block_xt_load(X, tid, xt);
+        const double2 y = block_x_times(X, x.b.st, x.red, tid);
+        if (tid < 64) {
+            x.v[tid] = zmul(y, zinv_nr(x.b.pivot(tid)));
+        }
+        __syncthreads();
+        const double2 cur = block_xt_times(xt, x.v, tid);
+        const int k = tid >> 2;
+        if ((tid & 3) == 0 && k < n) {
+            I[(size_t)s * n + k] = cur;
+            if (!(isfinite(cur.x) && isfinite(cur.y))) x.nonfinite = true;
+        }
+        __syncthreads();
+    }
+    const bool pivot = x.pivot;
+    if (tid == 0 && !pivot) {
+        flag |= x.nonfinite ? COSIM_SYS_NONFINITE : 0;
+        fac.fmt[s] = kFmtInv;
+        status[s] = flag;
+        if (rec_status) rec_status[s] = flag;
+    }
+    if (!pivot) return;  // uniform
+    __syncthreads();     // every thread has read the flag: its memory is reused
+    gj_system<64, false>(lds.gj, s, n, S, F, M, Rv, phi, C, omega, nullptr, nullptr, 0, 0.0, I,
+                         nullptr, status, false, fac, false);
+    if (rec_status && tid == 0) rec_status[s] = status[s];  // the thread that wrote it
+}
+static_assert(GJShape<64>::BLOCK == 256, "one workgroup for either elimination");
+
+__global__ __launch_bounds__(256, 2) void k_small64(
+    int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
+    const double *__restrict__ phi, const double *__restrict__ C,
+    const double *__restrict__ omega, GJFactor fac, double2 *__restrict__ I,
+    int32_t *__restrict__ status, int32_t *__restrict__ rec_status) {
+    __shared__ Small64Lds lds;
+    small64_system(lds, blockIdx.x, n, S, F, M, Rv, phi, C, omega, fac, I, status, rec_status);
+}
+// The members of a group that have few systems; as in every launch of a group,
+// a member takes the same route as alone, so the results are the same bits.
+__global__ __launch_bounds__(256, 2) void k_small64_group(SmallGroup g) {
+    __shared__ Small64Lds lds;
+    const int sg = blockIdx.x;
+    const SmallInst &e = g.in[group_member(g, sg)];
+    if (e.S > kFewSystems) return;  // whole workgroup: k_ldl_group's
+    small64_system(lds, sg - e.s0, e.n, e.S, e.F, e.M, e.R, e.phi, e.C, e.omega, e.fac, e.I, e.status,
+                   nullptr);
 }
 
 // Forward solve of a system in the LDL^T format from the z the factorisation
@@ -1091,6 +1266,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const int sg = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (sg >= S) return;
     const SmallInst &e = g.in[group_member(g, sg)];
+    if (NP == 64 && e.S <= kFewSystems) return;  // whole wave: k_small64_group's
     double2 none[1][8], z;
     int flag;
     ldl_system<NP, false>(lds[threadIdx.x >> 6], none, z, flag, sg - e.s0, e.n, e.F, e.M, e.R, e.C,
@@ -1118,6 +1294,7 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
                                               double rscale, double *__restrict__ gsys,
                                               double2 *__restrict__ mu,
                                               int32_t *__restrict__ status,
+                                              const int32_t *__restrict__ status_in,
                                               const FinalSums &fin) {
     __shared__ double2 sRed[4][NP * 9];  // per wave: the lane products of ldl_backward
     __shared__ double2 sTr[4][NP >= 64 ? 64 : 128];  // per wave: an 8x8 block of L, transposed
@@ -1204,7 +1381,7 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
         const double2 bpk = make_double2(__shfl(x.x, pk), __shfl(x.y, pk));
         x = lane < n ? cmul(bpk, cinv(fac.piv_val[(size_t)s * NP + lane])) : make_double2(0.0, 0.0);
     }
-    const int flag = status[s];
+    const int flag = status_in[s];
     const bool bad = (flag & (COSIM_SYS_BAD_INPUT | COSIM_SYS_SINGULAR)) != 0;
     bool nonfinite = false;
     if (lane < n) {
@@ -1225,7 +1402,111 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
         if (lane == 0) fin.loss[s] = fin.lscale * acc;
     }
-    if (__ballot(nonfinite) != 0 && lane == 0) status[s] = flag | COSIM_SYS_NONFINITE;
+    const bool any = __ballot(nonfinite) != 0;
+    if ((any || status_in != status) && lane == 0) status[s] = flag | (any ? COSIM_SYS_NONFINITE : 0);
+}
+
+// The adjoint of one system with a kFmtInv record (small64_system) by a
+// workgroup: mu = X^T D^-1 X b, b and the results as in replay_system, which
+// takes the other records.  Both layouts of X are on their way while the
+// partial sums are added up.
+__device__ __forceinline__ void replay64_system(
+    int s, int n, int S, int F, const GJFactor &fac, const double *__restrict__ C,
+    const double *__restrict__ omega, const double2 *__restrict__ I, const double2 *__restrict__ rpart,
+    int nchunk, double rscale, double *__restrict__ gsys, double2 *__restrict__ mu,
+    int32_t *__restrict__ status, const int32_t *__restrict__ status_in, const FinalSums &fin) {
+    __shared__ double2 red[256], v[64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (fac.fmt[s] != kFmtInv) {  // whole workgroup
+        if (wv == 0)
+            replay_system<64>(s, n, S, F, fac, C, omega, I, rpart, nchunk, rscale, gsys, mu, status,
+                              status_in, fin);
+        return;
+    }
+    const double2 *__restrict__ X = fac.L + (size_t)s * 64 * 64;
+    double2 xn[16], xt[16];
+#pragma unroll
+    for (int c = 0; c < 16; ++c)
+        xn[c] = wv <= (lane >> 4) ? X[(16 * wv + c) * 64 + lane] : make_double2(0.0, 0.0);
+    block_xt_load(X, tid, xt);
+    const int b = s / F, kk = min(lane, n - 1);
+    const double w = omega[s - b * F];
+    const double2 Ik = I[(size_t)s * n + kk];
+    const double ck = C[(size_t)b * n + kk];
+    const double2 dinv = fac.piv_val[(size_t)s * 64 + lane];
+    const int flag = status_in[s];
+    double rr = 0.0, ri = 0.0;
+#pragma unroll 8
+    for (int c = wv; c < nchunk; c += 4) {
+        const double2 r = rpart[((size_t)c * S + s) * 64 + lane];
+        rr += r.x;
+        ri += r.y;
+    }
+    red[tid] = make_double2(rr, ri);
+    __syncthreads();
+    if (wv == 0) {
+        double2 t = red[lane];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) {
+            t.x += red[64 * e + lane].x;
+            t.y += red[64 * e + lane].y;
+        }
+        v[lane].x = lane < n ? rscale * t.x : 0.0;
+        v[lane].y = lane < n ? -rscale * t.y : 0.0;
+    }
+    __syncthreads();
+    double2 acc = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int c = 0; c < 16; ++c) acc = zfma(acc, xn[c], v[16 * wv + c]);
+    red[tid] = acc;
+    __syncthreads();
+    if (wv == 0) {
+        double2 t = red[lane];
+#pragma unroll
+        for (int e = 1; e < 4; ++e) {
+            t.x += red[64 * e + lane].x;
+            t.y += red[64 * e + lane].y;
+        }
+        v[lane] = zmul(t, dinv);
+    }
+    __syncthreads();
+    const double2 m = block_xt_times(xt, v, tid);
+    if ((tid & 3) == 0) red[tid >> 2] = m;
+    __syncthreads();
+    if (wv == 1 && fin.grad) {  // the order of reduce_config
+        double sum = 0.0;
+        for (int c = lane; c < nchunk; c += 64) sum += fin.lpart[(size_t)c * S + s];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
+        if (lane == 0) fin.loss[s] = fin.lscale * sum;
+    }
+    if (wv != 0) return;
+    const double2 x = red[lane];
+    // 2 Re(mu I / (j w C^2)) = 2 Im(mu I) / (w C^2); a kFmtInv record has no
+    // invalid input and no vanishing pivot
+    const double gk = 2.0 * (x.x * Ik.y + x.y * Ik.x) / (w * ck * ck);
+    if (lane < n) {
+        (fin.grad ? fin.grad : gsys)[(size_t)s * n + lane] = gk;
+        if (mu) mu[(size_t)s * n + lane] = x;
+    }
+    const bool any = __ballot(lane < n && !isfinite(gk)) != 0;
+    if ((any || status_in != status) && lane == 0) status[s] = flag | (any ? COSIM_SYS_NONFINITE : 0);
+}
+
+__global__ __launch_bounds__(256, 2) void k_replay64(
+    int n, int S, int F, GJFactor fac, const double *__restrict__ C, const double *__restrict__ omega,
+    const double2 *__restrict__ I, const double2 *__restrict__ rpart, int nchunk, double rscale,
+    double *__restrict__ gsys, double2 *__restrict__ mu, int32_t *__restrict__ status,
+    const int32_t *__restrict__ status_in, FinalSums fin) {
+    replay64_system(blockIdx.x, n, S, F, fac, C, omega, I, rpart, nchunk, rscale, gsys, mu, status,
+                    status_in, fin);
+}
+__global__ __launch_bounds__(256, 3) void k_replay64_group(SmallGroup g) {
+    const int sg = blockIdx.x;
+    const SmallInst &e = g.in[group_member(g, sg)];
+    if (e.S > kFewSystems) return;  // whole workgroup
+    replay64_system(sg - e.s0, e.n, e.S, e.F, e.fac, e.C, e.omega, e.I, e.rpart, e.nchunk, e.rscale,
+                    e.gsys, e.mu, e.status, e.status, FinalSums{});
 }
 
 template <int NP>
@@ -1238,10 +1519,12 @@ __global__ __launch_bounds__(256) void k_replay_adjoint(int n, int S, int F, GJF
                                                         double *__restrict__ gsys,
                                                         double2 *__restrict__ mu,
                                                         int32_t *__restrict__ status,
+                                                        const int32_t *__restrict__ status_in,
                                                         FinalSums fin) {
     const int s = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (s >= S) return;  // whole wave; no block-level synchronisation below
-    replay_system<NP>(s, n, S, F, fac, C, omega, I, rpart, nchunk, rscale, gsys, mu, status, fin);
+    replay_system<NP>(s, n, S, F, fac, C, omega, I, rpart, nchunk, rscale, gsys, mu, status, status_in,
+                      fin);
 }
 
 template <int NP>
@@ -1249,8 +1532,9 @@ __global__ __launch_bounds__(256) void k_replay_adjoint_group(SmallGroup g, int 
     const int sg = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
     if (sg >= S) return;
     const SmallInst &e = g.in[group_member(g, sg)];
+    if (NP == 64 && e.S <= kFewSystems) return;  // whole wave: k_replay64_group's
     replay_system<NP>(sg - e.s0, e.n, e.S, e.F, e.fac, e.C, e.omega, e.I, e.rpart, e.nchunk,
-                      e.rscale, e.gsys, e.mu, e.status, FinalSums{});
+                      e.rscale, e.gsys, e.mu, e.status, e.status, FinalSums{});
 }
 
 // One block per configuration b: dL/dC_b summed over frequencies per loop, and
@@ -1348,18 +1632,23 @@ hipError_t launch_solve_forward(int NP, int n, int S, int F, const double *M_d,
 
 hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const double *R_d,
                       const double *C_d, const double *omega_d, const double *phi_d, GJFactor fac,
-                      double2 *I_d, int32_t *status_d, hipStream_t st) {
+                      double2 *I_d, int32_t *status_d, int32_t *rec_status_d, hipStream_t st) {
     const dim3 grid((S + 3) / 4);
     switch (NP) {
         case 32:
             if (S <= kOneRound)
                 hipLaunchKernelGGL(k_small32<2>, dim3(S), dim3(64), 0, st, n, S, F, M_d, R_d, C_d,
-                                   omega_d, phi_d, fac, I_d, status_d);
+                                   omega_d, phi_d, fac, I_d, status_d, rec_status_d);
             else
                 hipLaunchKernelGGL(k_small32<3>, dim3(S), dim3(64), 0, st, n, S, F, M_d, R_d, C_d,
-                                   omega_d, phi_d, fac, I_d, status_d);
+                                   omega_d, phi_d, fac, I_d, status_d, rec_status_d);
             return hipGetLastError();
         case 64:
+            if (S <= kFewSystems) {
+                hipLaunchKernelGGL(k_small64, dim3(S), dim3(256), 0, st, n, S, F, M_d, R_d, phi_d,
+                                   C_d, omega_d, fac, I_d, status_d, rec_status_d);
+                return hipGetLastError();
+            }
             if (S <= kOneRound) {
                 hipLaunchKernelGGL((k_ldl<64, true>), grid, dim3(256), 0, st, n, S, F, M_d, R_d,
                                    C_d, omega_d, phi_d, fac, I_d, status_d);
@@ -1375,22 +1664,36 @@ hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const doub
     hipLaunchKernelGGL(k_gj_fallback<64>, dim3((S + kFbSystems - 1) / kFbSystems),
                        dim3(GJShape<64>::BLOCK), 0, st, n, S, F, M_d, R_d, phi_d, C_d, omega_d, I_d,
                        status_d, fac);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !rec_status_d) return e;
+    return hipMemcpyAsync(rec_status_d, status_d, (size_t)S * sizeof(int32_t),
+                          hipMemcpyDeviceToDevice, st);
 }
 
 hipError_t launch_replay_adjoint(int NP, int n, int S, int F, GJFactor fac, const double *C_d,
                                  const double *omega_d, double2 *I_d, const double2 *rpart_d,
                                  int nchunk, double rscale, double *gsys_d, double2 *mu_d,
-                                 int32_t *status_d, hipStream_t st, const FinalSums &fin) {
+                                 int32_t *status_d, hipStream_t st, const FinalSums &fin,
+                                 const int32_t *status_in_d) {
+    if (!status_in_d) status_in_d = status_d;
     const dim3 grid((S + 3) / 4);
     switch (NP) {
         case 32:
             hipLaunchKernelGGL(k_replay_adjoint<32>, grid, dim3(256), 0, st, n, S, F, fac, C_d,
-                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d, fin);
+                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d,
+                               status_in_d, fin);
             break;
         case 64:
+            // a call's factorisation and its replay have the same systems
+            if (S <= kFewSystems) {
+                hipLaunchKernelGGL(k_replay64, dim3(S), dim3(256), 0, st, n, S, F, fac, C_d, omega_d,
+                                   I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d, status_in_d,
+                                   fin);
+                break;
+            }
             hipLaunchKernelGGL(k_replay_adjoint<64>, grid, dim3(256), 0, st, n, S, F, fac, C_d,
-                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d, fin);
+                               omega_d, I_d, rpart_d, nchunk, rscale, gsys_d, mu_d, status_d,
+                               status_in_d, fin);
             break;
         default:
             return hipErrorInvalidValue;
@@ -1426,6 +1729,8 @@ hipError_t launch_small_group(int NP, const SmallGroup &g, int S, SmallPhase pha
     if (S <= 0) return hipSuccess;
     const dim3 wave_grid((S + 3) / 4);
     if (NP != 32 && NP != 64) return hipErrorInvalidValue;
+    bool few = false, many = false;  // 33 to 64 loops: members on either side of kFewSystems
+    for (int i = 0; i < g.count; ++i) (g.in[i].S <= kFewSystems ? few : many) = true;
     switch (phase) {
         case SmallPhase::Factor:
             if (NP == 32) {
@@ -1435,6 +1740,8 @@ hipError_t launch_small_group(int NP, const SmallGroup &g, int S, SmallPhase pha
                     hipLaunchKernelGGL(k_small32_group<3>, dim3(S), dim3(64), 0, st, g);
                 break;
             }
+            if (few) hipLaunchKernelGGL(k_small64_group, dim3(S), dim3(256), 0, st, g);
+            if (!many) break;
             if (S <= kOneRound) {
                 hipLaunchKernelGGL((k_ldl_group<64, true>), wave_grid, dim3(256), 0, st, g, S);
             } else {
@@ -1445,9 +1752,12 @@ hipError_t launch_small_group(int NP, const SmallGroup &g, int S, SmallPhase pha
                                dim3(GJShape<64>::BLOCK), 0, st, g, S);
             break;
         case SmallPhase::Adjoint:
-            if (NP == 32)
+            if (NP == 32) {
                 hipLaunchKernelGGL(k_replay_adjoint_group<32>, wave_grid, dim3(256), 0, st, g, S);
-            else
+                break;
+            }
+            if (few) hipLaunchKernelGGL(k_replay64_group, dim3(S), dim3(256), 0, st, g);
+            if (many)
                 hipLaunchKernelGGL(k_replay_adjoint_group<64>, wave_grid, dim3(256), 0, st, g, S);
             break;
     }
