@@ -16,13 +16,17 @@
 // A workgroup (WM x WN waves) computes a BM x BN tile over K in steps of 32:
 // each step's operands are loaded from memory into registers two steps ahead
 // and stored to LDS while the step before is multiplied (two LDS buffers, two
-// register sets, one barrier per step).  Each wave multiplies a (BM / WM) x (BN / WN) block with 16x16
-// matrix-core tiles: BF16X3 (hi hi + hi lo + lo hi into FP32), FP32 or FP64,
-// the same products as the fused kernel.  BF16X3 uses 256 x 128 tiles of 8
-// waves (one workgroup per compute unit: fewer operand bytes per product),
-// FP32 128 x 128 tiles of 4 waves (two workgroups per compute unit, one's
-// barrier waits overlapping the other's products), FP64 (bound by its
-// matrix-core rate) 128 x 64 tiles of 8 waves.
+// register sets, one barrier per step).  Each wave multiplies a (BM / WM) x
+// (BN / WN) block with 16x16 matrix-core tiles: BF16X3 (hi hi + hi lo + lo hi
+// into FP32), FP32 or FP64, the same products as the fused kernel.  BF16X3
+// uses 256 x 128 tiles of 8 waves (one workgroup per compute unit, fewer
+// operand bytes per product: 1,024 loops, 256 systems, 262,144 points 1.07 +
+// 0.87 ms; 128 x 128 tiles of 4 waves, two workgroups, 1.10 + 1.01), FP32
+// 128 x 128 and FP64 64 x 64 tiles of 4 waves: two workgroups per compute unit,
+// one's barrier waits, first loads and epilogue overlapping the other's
+// products (FP64, 256 loops, 160 systems, 40,000 points: 155 + 122 us, 42 and 54
+// TFLOP/s, where 128 x 64 tiles of 8 waves with padded LDS rows and two
+// address additions per load took 189 + 138).
 #include <algorithm>
 
 #include "epilogue.h"
@@ -61,9 +65,9 @@ struct GBF3 {
         bf16x8 h, l;
     };
     __device__ static constexpr int row(int q, int m) { return 4 * q + m; }
-    __device__ static Op lds(const char *hi, const char *lo) {
-        return Op{__builtin_bit_cast(bf16x8, *(const u32x4 *)hi),
-                  __builtin_bit_cast(bf16x8, *(const u32x4 *)lo)};
+    __device__ static Op lds(const char *hi, const char *lo, const int (&o)[1]) {
+        return Op{__builtin_bit_cast(bf16x8, *(const u32x4 *)(hi + o[0])),
+                  __builtin_bit_cast(bf16x8, *(const u32x4 *)(lo + o[0]))};
     }
     __device__ static V mma(const Op &a, const Op &b, V c) {
         c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.l, b.h, c, 0, 0, 0);
@@ -74,22 +78,23 @@ struct GBF3 {
 template <typename T>
 struct GScalar {
     static constexpr int ESZ = sizeof(T), PLANES = 1;
-    static constexpr int BM = 128, BN = sizeof(T) == 4 ? 128 : 64;
-    static constexpr int WM = sizeof(T) == 4 ? 2 : 4, WN = 2;
+    static constexpr int BM = sizeof(T) == 4 ? 128 : 64, BN = sizeof(T) == 4 ? 128 : 64;
+    static constexpr int WM = 2, WN = 2;
     typedef T Acc;
     typedef T V __attribute__((ext_vector_type(4)));
     struct Op {
         T v[8];
     };
     __device__ static constexpr int row(int q, int m) { return sizeof(T) == 4 ? 4 * q + m : q + 4 * m; }
-    __device__ static Op lds(const char *p, const char *) {
+    __device__ static Op lds(const char *p, const char *, const int (&of)[sizeof(T) / 2]) {
+        constexpr int W = 16 / (int)sizeof(T);
         Op o;
 #pragma unroll
-        for (int j = 0; j < 8; j += 16 / (int)sizeof(T)) {
-            const u32x4 u = *(const u32x4 *)(p + j * sizeof(T));
+        for (int j = 0; j < 8 / W; ++j) {
+            const u32x4 u = *(const u32x4 *)(p + of[j]);
             const T *e = (const T *)&u;
 #pragma unroll
-            for (int i = 0; i < 16 / (int)sizeof(T); ++i) o.v[j + i] = e[i];
+            for (int i = 0; i < W; ++i) o.v[W * j + i] = e[i];
         }
         return o;
     }
@@ -107,10 +112,19 @@ struct GScalar {
 typedef GScalar<float> GF32;
 typedef GScalar<double> GF64;
 
-// LDS rows of one step: 32 K entries plus 16 bytes of padding
+// LDS rows of one step: 32 K entries, PR pieces of 16 bytes, piece c of row r
+// at place c ^ swz(r).  16 rows at one piece (what 16 lanes of an operand read
+// address) and consecutive pieces (what they store) then fall on disjoint
+// banks; with rows padded by 16 bytes instead, bank conflicts were a third to a
+// half of the LDS cycles.
 template <class Pol>
 constexpr int row_bytes() {
-    return kBK * Pol::ESZ + 16;
+    return kBK * Pol::ESZ;
+}
+template <class Pol>
+__device__ constexpr int swz(int r) {
+    constexpr int PR = kBK * Pol::ESZ / 16;
+    return (r / (16 / PR)) & (PR - 1);
 }
 template <class Pol>
 constexpr int stage_bytes() {
@@ -147,52 +161,59 @@ __global__ __launch_bounds__(threads<Pol>(), 2) void k_gemm(GemmArgs a) {
     // block (which share its A tile) run side by side on one XCD
     const int nbn = a.N / BN, nbm = (a.M + BM - 1) / BM;
     const int Nw = nbn * nbm * a.nkc, b = (int)blockIdx.x;
-    const int item = (Nw & 7) == 0 ? (b & 7) * (Nw >> 3) + (b >> 3) : b;
+    const int item = (b & 7) * ((Nw + 7) >> 3) + (b >> 3);
+    if (item >= Nw) return;  // whole workgroup: the last XCD's share may be short
     const int bn = item % nbn, bm = (item / nbn) % nbm, kc = item / (nbn * nbm);
     const int row0 = bm * BM, col0 = bn * BN;
     const int k0 = kc * a.kchunk, k1 = min(a.K, k0 + a.kchunk);
     const int nsteps = (k1 - k0) / kBK;
 
-    // global -> registers -> LDS staging of one step, two register sets
-    auto fetch = [&](int kb, u32x4 (&ga)[NA], u32x4 (&gb)[NB]) {
+    // global -> registers -> LDS staging of one step, two register sets.  Each
+    // piece has its pointer, moved on by a step after every load but the last
+    // (`adv`), and its place in LDS.
+    const char *pa[NA], *pb[NB];
+    int da[NA], db[NB];
+#pragma unroll
+    for (int u = 0; u < NA; ++u) {
+        const int e = tid + NT * u;
+        const int pl = e / (BM * CPR), rem = e - pl * (BM * CPR);
+        const int r = rem / CPR, c = rem - r * CPR;
+        // rows past M: the last row is read (in bounds, unconditionally, so
+        // that no merge of register values waits on the load) and zeroed when
+        // stored; M is a multiple of 64, so tiles of 64 rows have none
+        const int gr = min(row0 + r, a.M - 1);
+        pa[u] = (const char *)(pl ? a.Alo : a.A) + ((size_t)gr * a.lda + k0) * ESZ + 16 * c;
+        da[u] = (pl * BM + r) * RB + 16 * (c ^ swz<Pol>(r));
+    }
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+        const int e = tid + NT * u;
+        const int pl = e / (BN * CPR), rem = e - pl * (BN * CPR);
+        const int r = rem / CPR, c = rem - r * CPR;
+        pb[u] = (const char *)(pl ? a.Blo : a.B) + ((size_t)(col0 + r) * a.ldb + k0) * ESZ + 16 * c;
+        db[u] = BM * RB * PL + (pl * BN + r) * RB + 16 * (c ^ swz<Pol>(r));
+    }
+    auto fetch = [&](bool adv, u32x4 (&ga)[NA], u32x4 (&gb)[NB]) {
+        const size_t d = adv ? kBK * ESZ : 0;
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-            const int e = tid + NT * u;
-            const int pl = e / (BM * CPR), rem = e - pl * (BM * CPR);
-            const int r = rem / CPR, c = rem - r * CPR;
-            // rows past M: the last row is read (in bounds, unconditionally, so
-            // that no merge of register values waits on the load) and zeroed
-            // when stored
-            const int gr = min(row0 + r, a.M - 1);
-            const char *src = (const char *)(pl ? a.Alo : a.A);
-            ga[u] = *(const u32x4 *)(src + ((size_t)gr * a.lda + kb) * ESZ + 16 * c);
+            ga[u] = *(const u32x4 *)pa[u];
+            pa[u] += d;
         }
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
-            const int e = tid + NT * u;
-            const int pl = e / (BN * CPR), rem = e - pl * (BN * CPR);
-            const int r = rem / CPR, c = rem - r * CPR;
-            const char *src = (const char *)(pl ? a.Blo : a.B);
-            gb[u] = *(const u32x4 *)(src + ((size_t)(col0 + r) * a.ldb + kb) * ESZ + 16 * c);
+            gb[u] = *(const u32x4 *)pb[u];
+            pb[u] += d;
         }
     };
     auto stash = [&](char *st, const u32x4 (&ga)[NA], const u32x4 (&gb)[NB]) {
-        char *sa = st, *sb = st + BM * RB * PL;
 #pragma unroll
         for (int u = 0; u < NA; ++u) {
-            const int e = tid + NT * u;
-            const int pl = e / (BM * CPR), rem = e - pl * (BM * CPR);
-            const int r = rem / CPR, c = rem - r * CPR;
-            *(u32x4 *)(sa + (pl * BM + r) * RB + 16 * c) =
-                row0 + r < a.M ? ga[u] : u32x4{0u, 0u, 0u, 0u};
+            const int r = (tid + NT * u) % (BM * CPR) / CPR;
+            *(u32x4 *)(st + da[u]) = BM <= 64 || row0 + r < a.M ? ga[u] : u32x4{0u, 0u, 0u, 0u};
         }
 #pragma unroll
-        for (int u = 0; u < NB; ++u) {
-            const int e = tid + NT * u;
-            const int pl = e / (BN * CPR), rem = e - pl * (BN * CPR);
-            const int r = rem / CPR, c = rem - r * CPR;
-            *(u32x4 *)(sb + (pl * BN + r) * RB + 16 * c) = gb[u];
-        }
+        for (int u = 0; u < NB; ++u) *(u32x4 *)(st + db[u]) = gb[u];
     };
 
     V acc[TI][TJ];
@@ -200,18 +221,22 @@ __global__ __launch_bounds__(threads<Pol>(), 2) void k_gemm(GemmArgs a) {
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = V{};
+    // places of a lane's pieces in its rows (every row it reads is r16 mod 16)
+    int off[ESZ / 2];
+#pragma unroll
+    for (int j = 0; j < ESZ / 2; ++j) off[j] = 16 * ((ESZ / 2 * q + j) ^ swz<Pol>(r16));
     auto compute = [&](const char *sa) {
         const char *sb = sa + BM * RB * PL;
         Op bo[TJ];
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
             const int r = wn * TN + 16 * j + r16;
-            bo[j] = Pol::lds(sb + r * RB + 8 * ESZ * q, sb + (BN + r) * RB + 8 * ESZ * q);
+            bo[j] = Pol::lds(sb + r * RB, sb + (BN + r) * RB, off);
         }
 #pragma unroll
         for (int i = 0; i < TI; ++i) {
             const int r = wm * TM + 16 * i + r16;
-            const Op ao = Pol::lds(sa + r * RB + 8 * ESZ * q, sa + (BM + r) * RB + 8 * ESZ * q);
+            const Op ao = Pol::lds(sa + r * RB, sa + (BM + r) * RB, off);
 #pragma unroll
             for (int j = 0; j < TJ; ++j) acc[i][j] = Pol::mma(ao, bo[j], acc[i][j]);
         }
@@ -223,21 +248,20 @@ __global__ __launch_bounds__(threads<Pol>(), 2) void k_gemm(GemmArgs a) {
     // unconditional (the step index clamped to the last step), so that each
     // register set is filled by its loads alone and no copy waits on them.
     constexpr int SB = stage_bytes<Pol>();
-    const int last = nsteps > 0 ? nsteps - 1 : 0;
+    const int last = nsteps - 1;  // nsteps is even: K and every chunk of it are multiples of 64
     u32x4 ga0[NA], gb0[NB], ga1[NA], gb1[NB];
     if (nsteps > 0) {
-        fetch(k0, ga0, gb0);
+        fetch(true, ga0, gb0);
         stash(smem, ga0, gb0);
-        fetch(k0 + min(1, last) * kBK, ga1, gb1);
+        fetch(2 <= last, ga1, gb1);
     }
     __syncthreads();
-    // nsteps is even: K and every chunk of it are multiples of 64
     for (int s = 0; s < nsteps; s += 2) {
-        fetch(k0 + min(s + 2, last) * kBK, ga0, gb0);
+        fetch(s + 3 <= last, ga0, gb0);  // of step s + 2 (the last step's again at the end)
         compute(smem);
         stash(smem + SB, ga1, gb1);
         __syncthreads();
-        fetch(k0 + min(s + 3, last) * kBK, ga1, gb1);
+        fetch(s + 4 <= last, ga1, gb1);  // of step s + 3
         compute(smem + SB);
         if (s + 2 < nsteps) stash(smem, ga0, gb0);
         __syncthreads();
@@ -360,15 +384,16 @@ hipError_t go(const GemmArgs &a, hipStream_t st) {
     const int nbn = a.N / Pol::BN, nbm = (a.M + Pol::BM - 1) / Pol::BM;
     const unsigned blocks = (unsigned)(nbn * nbm * a.nkc);
     if (blocks == 0) return hipSuccess;
+    const unsigned grid = (blocks + 7) / 8 * 8;  // an equal share of items for each XCD
     // the kernel runs whole pairs of 32-deep steps
-    if (a.K % (2 * kBK) != 0 || a.kchunk % (2 * kBK) != 0 || a.N % Pol::BN != 0)
+    if (a.K % (2 * kBK) != 0 || a.kchunk % (2 * kBK) != 0 || a.N % Pol::BN != 0 || a.M % 64 != 0)
         return hipErrorInvalidValue;
     // more dynamic LDS than the default limit: raised once per kernel
     static const hipError_t attr = hipFuncSetAttribute(
         (const void *)k_gemm<Pol, EPI, LOSS>, hipFuncAttributeMaxDynamicSharedMemorySize,
         2 * stage_bytes<Pol>());
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k_gemm<Pol, EPI, LOSS>), dim3(blocks), dim3(threads<Pol>()), 2 * stage_bytes<Pol>(),
+    hipLaunchKernelGGL((k_gemm<Pol, EPI, LOSS>), dim3(grid), dim3(threads<Pol>()), 2 * stage_bytes<Pol>(),
                        st, a);
     return hipGetLastError();
 }
