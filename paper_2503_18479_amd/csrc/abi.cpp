@@ -135,7 +135,7 @@ void dfree(T *&p) {
 
 // Device blocks of destroyed plans' operators, kept for the next plan: a new
 // allocation of some hundred MB has to be mapped and, once the memory that
-// the driver holds cleared is used up, cleared at about 36 GB/s (15 ms for
+// the GPU driver holds cleared is used up, cleared at about 36 GB/s (15 ms for
 // the 539 MB of 256 loops at 65,536 points, where assembly takes 0.4 ms).  At most
 // kPoolBlocks blocks and kPoolBytes in all; the oldest go back first, and all
 // of a device's when an allocation there fails.  A block is handed out after

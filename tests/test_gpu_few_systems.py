@@ -59,3 +59,27 @@ def test_few_systems(nx, ny, batch, nf):
     gb, scale = x.grad.cpu().numpy()[ok], np.linalg.norm(gr, axis=1)
     k = np.sum(gb * gr) / np.sum(gr * gr)  # the two losses differ by a constant factor
     assert np.all(np.linalg.norm(gb - k * gr, axis=1) <= 1e-9 * abs(k) * scale)
+
+
+def test_group_of_few_and_many_matches_single_calls():
+    """A grouped call whose members of 33 to 64 loops lie on both sides of the
+    line gives each the bits of its own call, capacitance by capacitance."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    from paper_2503_18479_amd import Geometry, Plan, loss_and_grad_many
+    dev = torch.device("cuda:0")
+    wls = [W.small_array(nx, ny, batch=b, grid=12, n_freq=f, seed=b)
+           for nx, ny, b, f in ((8, 8, 49, 1), (8, 8, 5, 2), (7, 6, 48, 1), (7, 7, 25, 2), (11, 3, 1, 1))]
+    t = lambda a: torch.tensor(a, device=dev)
+    plans = [Plan(Geometry.from_workload(w.geom), t(w.pts), w.bext_z) for w in wls]
+    Cs, Os, Ts = [t(w.C) for w in wls], [t(w.omega) for w in wls], [t(w.target) for w in wls]
+    Cs[0][3, 1] = 0.0  # an invalid configuration on either side
+    Cs[1][2, 0] = 0.0
+    for prec in (0, 2):
+        print(f"[few and many] prec={prec}", flush=True)
+        outs = loss_and_grad_many(plans, Cs, Os, Ts, precision=prec)
+        for p, C, om, T, out in zip(plans, Cs, Os, Ts, outs):
+            for a, b in zip(out, p.loss_and_grad(C, om, T, precision=prec)):
+                assert torch.equal(torch.nan_to_num(a.double()), torch.nan_to_num(b.double()))
+                assert torch.equal(torch.isnan(a.double()), torch.isnan(b.double()))
+    assert int(outs[0][2].sum()) == 1 and int(outs[1][2].sum()) == 2
