@@ -76,8 +76,10 @@ GLRule make_gl_rule() {
 
 // Appends to `out` the vertices of the closed polygon v[0 .. n) that remain
 // when straight runs of segments are merged: field and flux of a straight
-// filament do not depend on where it is cut, and every segment costs the same
-// in assembly (a square of 32 segments: 8 times less for G, 64 times for M).
+// filament do not depend on where it is cut, nor does the accuracy they are
+// evaluated with (closed forms; neumann_skew grades its panels), and every
+// segment costs the same in assembly (a square of 32 segments: 8 times less for
+// G, 64 times for M).
 // A run ends where a vertex turns back or lies further from the chord than the
 // rounding of the coordinates, 4 units in the last place of the loop's
 // largest.  The first vertex kept is one where the polygon turns.

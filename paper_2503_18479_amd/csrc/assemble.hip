@@ -165,10 +165,8 @@ __global__ __launch_bounds__(256) void k_assemble_G(int n, int NP, int P, int P_
 //                  F(u) = u asinh(u/d) - sqrt(u^2 + d^2); for d = 0 (collinear)
 //                  F(u) = |u| ln|u| (the terms linear in |u| cancel);
 //   perpendicular: exactly zero;
-//   otherwise:     inner integral along y in closed form
-//                  asinh((L2 - t0)/r) + asinh(t0/r), outer integral along x by
-//                  composite Gauss-Legendre with panels scaled to the closest
-//                  approach of the two filaments.
+//   otherwise:     inner integral along y in closed form, outer integral along x
+//                  by composite Gauss-Legendre on graded panels (neumann_skew).
 // ----------------------------------------------------------------------------
 struct V3 {
     double x, y, z;
@@ -184,12 +182,76 @@ __device__ inline double cornerF(double u, double d) {
     return au > 0.0 ? au * log(au) : 0.0;
 }
 
-// distance from point c to the segment p0 + t*e, t in [0, L] (e unit)
-__device__ inline double point_seg_dist(V3 c, V3 p0, V3 e, double L) {
-    V3 w = sub(c, p0);
-    double t = fmin(fmax(dot3(w, e), 0.0), L);
-    V3 d = sub(w, scl(e, t));
-    return sqrt(dot3(d, d));
+__device__ inline V3 cross(V3 a, V3 b) {
+    return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
+}
+
+// Integral over x = x1 + s u, 0 <= s <= L1, of the potential of the filament
+// y1 -> y2 = y1 + L2 v (u, v unit, c = u.v, s2 = |u x v|^2 > 0):
+//   f(s) = asinh((L2 - t0)/r) + asinh(t0/r),
+// t0 the projection on the filament, r^2 = rho^2 + a^2 with rho the distance
+// from its line; far from the filament, where the two terms cancel, as
+// log(1 + 2 L2 / (R1 + R2 - L2)), R the distances to its ends.
+//   f is singular at complex s only: c_j +- i d_j for the projections of the
+// two ends (d = sqrt(distance^2 + a^2)) and, if the filament holds its point,
+// for the closest approach of the lines (d = sqrt(distance^2 + a^2) / |u x v|;
+// past an end the logarithms of r cancel).  A panel is no longer than its
+// distance from the nearest of them, so 16 nodes leave an error of 4.2^-32 of
+// the panel whatever the filaments' lengths are: panels grow geometrically
+// away from a near crossing or a shared corner (about 2 log2(L / d) of them)
+// and a filament seen from afar takes one.  Panels of one length, a quarter of
+// the ends' distances and at most 64, lost all but 2 to 8 digits where whole
+// sides cross or meet at a thin wire's radius.
+__device__ double neumann_skew(V3 x1, V3 u, double L1, V3 y1, V3 v, double L2, double c, double s2,
+                               double a, const GLRule &gl) {
+    const V3 w0 = sub(x1, y1);
+    const double p = dot3(w0, u), q = dot3(w0, v), a2 = a * a;
+    double sc[3], sd[3];
+    const double tc = (q - c * p) / s2;
+    sc[0] = (c * q - p) / s2;
+    const V3 gap = sub(add(w0, scl(u, sc[0])), scl(v, tc));
+    sd[0] = tc >= 0.0 && tc <= L2 ? sqrt((dot3(gap, gap) + a2) / s2) : 1e300;
+    const V3 e0 = sub(y1, x1), e1 = add(e0, scl(v, L2));
+    sc[1] = dot3(e0, u);
+    sc[2] = dot3(e1, u);
+    const V3 h0 = sub(e0, scl(u, sc[1])), h1 = sub(e1, scl(u, sc[2]));
+    sd[1] = sqrt(dot3(h0, h0) + a2);
+    sd[2] = sqrt(dot3(h1, h1) + a2);
+    // touching filaments (a = 0) would need panels without end: at least 2^-40 L1
+    const double hmin = L1 * 0x1p-40;
+    double acc = 0.0, s = 0.0;
+    for (int k = 0; k < 400 && s < L1; ++k) {
+        double h = L1 - s;
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const double g = sc[j] - s, d = sd[j];
+            // behind s the distance is that of s; ahead, that of the panel's end,
+            // and once the panel reaches past it, d
+            h = fmin(h, d >= h ? h : g <= 0.0 ? sqrt(g * g + d * d) : d < g ? (g * g + d * d) / (2.0 * g) : d);
+        }
+        const bool last = fmax(h, hmin) >= L1 - s;
+        h = last ? L1 - s : fmax(h, hmin);
+        double part = 0.0;
+        for (int i = 0; i < kGLOrder; ++i) {
+            const V3 w = add(w0, scl(u, s + 0.5 * h * (1.0 + gl.x[i])));
+            const double t0 = dot3(w, v), t1 = L2 - t0;
+            const V3 n = cross(w, v);  // |n| = rho, without the cancellation of |w|^2 - t0^2
+            const double r2 = dot3(n, n) + a2;
+            const double R = sqrt(fma(t0, t0, r2)) + sqrt(fma(t1, t1, r2));
+            double f;
+            if (R >= 2.0 * L2) {
+                f = log1p(2.0 * L2 / (R - L2));
+            } else {
+                double r = sqrt(r2);
+                if (r == 0.0) r = 1e-300;
+                f = asinh(t1 / r) + asinh(t0 / r);
+            }
+            part += gl.w[i] * f;
+        }
+        acc += 0.5 * h * part;
+        s = last ? L1 : s + h;
+    }
+    return acc;
 }
 
 __device__ double neumann_pair(V3 x1, V3 x2, V3 y1, V3 y2, double a, const GLRule &gl) {
@@ -197,7 +259,7 @@ __device__ double neumann_pair(V3 x1, V3 x2, V3 y1, V3 y2, double a, const GLRul
     const double L1 = sqrt(dot3(du, du)), L2 = sqrt(dot3(dv, dv));
     const V3 u = scl(du, 1.0 / L1), v = scl(dv, 1.0 / L2);
     const double c = dot3(u, v);
-    const V3 cr = {u.y * v.z - u.z * v.y, u.z * v.x - u.x * v.z, u.x * v.y - u.y * v.x};
+    const V3 cr = cross(u, v);
     const double s2 = dot3(cr, cr);
     if (s2 < 1e-24) {
         const double sgn = c > 0.0 ? 1.0 : -1.0;
@@ -213,34 +275,7 @@ __device__ double neumann_pair(V3 x1, V3 x2, V3 y1, V3 y2, double a, const GLRul
         return kMu0Over4Pi * sgn * val;
     }
     if (fabs(c) < 1e-12) return 0.0;
-    // closest approach (endpoint-to-segment distances bound it for separated
-    // filaments) sets the panel count so that each panel spans ~1/4 of it
-    double dmin = fmin(fmin(point_seg_dist(x1, y1, v, L2), point_seg_dist(x2, y1, v, L2)),
-                       fmin(point_seg_dist(y1, x1, u, L1), point_seg_dist(y2, x1, u, L1)));
-    const double reff = sqrt(dmin * dmin + a * a);
-    int npan = 4;
-    if (reff > 0.0) {
-        const double want = ceil(4.0 * L1 / reff);
-        npan = (int)fmin(fmax(want, 4.0), 64.0);
-    } else {
-        npan = 64;
-    }
-    const double h = L1 / npan;
-    double acc = 0.0;
-    for (int j = 0; j < npan; ++j) {
-        const double mid = (j + 0.5) * h;
-        for (int q = 0; q < kGLOrder; ++q) {
-            const double s = mid + 0.5 * h * gl.x[q];
-            const V3 x = add(x1, scl(u, s));
-            const V3 w = sub(x, y1);
-            const double t0 = dot3(w, v);
-            const double rho2 = fmax(dot3(w, w) - t0 * t0, 0.0);
-            double r = sqrt(rho2 + a * a);
-            if (r == 0.0) r = 1e-300;
-            acc += 0.5 * h * gl.w[q] * (asinh((L2 - t0) / r) + asinh(t0 / r));
-        }
-    }
-    return kMu0Over4Pi * c * acc;
+    return kMu0Over4Pi * c * neumann_skew(x1, u, L1, y1, v, L2, c, s2, a, gl);
 }
 
 // One group of TP threads per unordered loop pair (k <= l), striding over the
