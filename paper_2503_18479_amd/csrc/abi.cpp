@@ -958,6 +958,7 @@ int cosim_plan_set_refinement(cosim_plan_t p, int enable, int max_iter, double t
     p->refine = on;
     p->refine_iter = on ? max_iter : 0;
     p->refine_tol = on ? tol : 0.0;
+    p->rec_S = 0;  // a factor record is in the storage type of the mode it was made in
     return COSIM_OK;
 }
 
