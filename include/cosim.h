@@ -145,7 +145,13 @@ int cosim_assemble_ex(cosim_geom_t g, int P, const double *pts_d, double bext_z,
  * Errors: those of cosim_assemble_ex; COSIM_EINVAL for a component outside 0..2. */
 int cosim_assemble_component(cosim_geom_t g, int P, const double *pts_d, double bext_z,
                              int precisions, int component, void *stream, cosim_plan_t *out);
+/* The operators' memory of destroyed plans (up to 8 plans and 1 GiB per
+ * process) is kept for the plans assembled next, which save the allocation.
+ * Allocations of this library that run out of memory take it back by
+ * themselves; cosim_trim gives it back to the device, for programs whose other
+ * allocations need it (it waits for the device). */
 int cosim_plan_destroy(cosim_plan_t p);
+int cosim_trim(void);
 /* Loops n, points P of a plan. */
 int cosim_plan_size(cosim_plan_t p, int *n_loops, int *n_points);
 /* Number of batches whose impedance matrices the plan's calls have

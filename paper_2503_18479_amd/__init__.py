@@ -11,5 +11,5 @@ from .api import (  # noqa: F401
     SYS_BAD_INPUT, SYS_SINGULAR, SYS_NONFINITE, SYS_NEGATIVE_C,
     Geometry, Plan, CosimField, cosim_field, adam_step, loss_and_grad_many, ManyCall,
     capture_loss_and_grad_many,
-    SParamPlan, sp_rc, sp_rc_backward, tanh_projection, clip_,
+    SParamPlan, sp_rc, sp_rc_backward, tanh_projection, clip_, trim,
 )

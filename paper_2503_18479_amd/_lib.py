@@ -24,6 +24,7 @@ SIGNATURES = {
     "cosim_geometry_size": (c_int, [c_void_p, P(c_int), P(c_int)]),
     "cosim_assemble": (c_int, [c_void_p, c_int, c_void_p, c_double, c_void_p, P(c_void_p)]),
     "cosim_plan_destroy": (c_int, [c_void_p]),
+    "cosim_trim": (c_int, []),
     "cosim_plan_size": (c_int, [c_void_p, P(c_int), P(c_int)]),
     "cosim_plan_factorisations": (c_int, [c_void_p, P(ctypes.c_longlong)]),
     "cosim_plan_reserve": (c_int, [c_void_p, c_int, c_int]),

@@ -514,6 +514,11 @@ def cosim_field(C: torch.Tensor, plan: Plan, omega: torch.Tensor, precision=FP64
     return CosimField.apply(C, plan, omega, precision_code(precision), bool(add_incident))
 
 
+def trim() -> None:
+    """Gives the memory kept from destroyed plans back to the device (cosim_trim)."""
+    check(load_library().cosim_trim())
+
+
 # ---------------------------------------------------------------------------
 # S-parameter pipeline (include/cosim_sparam.h)
 # ---------------------------------------------------------------------------

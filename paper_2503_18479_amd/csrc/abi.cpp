@@ -13,6 +13,7 @@
 #include <new>
 #include <vector>
 
+#include "block_pool.h"
 #include "cosim_sparam.h"
 #include "internal.h"
 
@@ -135,99 +136,40 @@ void dfree(T *&p) {
     p = nullptr;
 }
 
-// Waits for all work of the current device, as hipFree does on the way.  (Not
-// hipDeviceSynchronize: it ends the graph captures of other threads, also those
-// that allow allocations beside them.  1.3 us when the device is idle.)
-hipError_t wait_for_device() {
-    void *p = nullptr;
-    hipError_t e = hipMalloc(&p, 256);
-    if (e == hipSuccess) e = hipFree(p);
-    if (e != hipSuccess) (void)hipGetLastError();
-    return e;
-}
-
-// Device blocks of destroyed plans' operators, kept for the next plan: a new
-// allocation of some hundred MB has to be mapped and, once the memory that
-// the GPU driver holds cleared is used up, cleared at about 36 GB/s (15 ms for
-// the 539 MB of 256 loops at 65,536 points, where assembly takes 0.4 ms).  At most
-// kPoolBlocks blocks and kPoolBytes in all; the oldest go back first, and all
-// of a device's when an allocation there fails.  A block is handed out after
-// the device has been waited for (whatever still ran on it when its plan was
-// destroyed, on any stream, has ended), within cosim_assemble, which waits
-// itself.
-struct BlockPool {
-    struct Block {
-        int device;
-        void *p;
-        size_t bytes;
-    };
-    static constexpr size_t kPoolBlocks = 8, kPoolBytes = (size_t)1 << 30;
-    std::mutex mu;
-    std::vector<Block> idle;  // oldest first
-    size_t total = 0;
-
-    Block remove(size_t i) {
-        const Block b = idle[i];
-        idle.erase(idle.begin() + i);
-        total -= b.bytes;
-        return b;
+// The device as the block pool sees it.
+struct HipDev {
+    static constexpr int no_memory = (int)hipErrorOutOfMemory;
+    static int alloc(void **p, size_t bytes) {
+        const hipError_t e = hipMalloc(p, bytes);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return (int)e;
     }
-    // A block of at least `bytes` on the current device; *got: its size.
-    hipError_t take(int device, size_t bytes, void **out, size_t *got) {
-        bytes = (bytes + 65535) / 65536 * 65536;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            size_t best = idle.size();
-            for (size_t i = 0; i < idle.size(); ++i)
-                if (idle[i].device == device && idle[i].bytes >= bytes &&
-                    idle[i].bytes <= bytes + bytes / 4 &&
-                    (best == idle.size() || idle[i].bytes < idle[best].bytes))
-                    best = i;
-            if (best < idle.size()) {
-                const Block b = remove(best);
-                *out = b.p;
-                *got = b.bytes;
-            } else {
-                *out = nullptr;
-            }
-        }
-        if (*out) {
-            if (wait_for_device() == hipSuccess) return hipSuccess;
-            give(device, *out, *got);  // cannot wait here: a block of its own
-        }
-        *got = bytes;
-        hipError_t e = hipMalloc(out, bytes);
-        if (e == hipSuccess) return e;
-        (void)hipGetLastError();
-        std::vector<Block> back;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            for (size_t i = idle.size(); i-- > 0;)
-                if (idle[i].device == device) back.push_back(remove(i));
-        }
-        if (back.empty()) {
-            *out = nullptr;
-            return e;
-        }
-        for (const Block &b : back) (void)hipFree(b.p);
-        if ((e = hipMalloc(out, bytes)) != hipSuccess) *out = nullptr;
-        return e;
-    }
-    void give(int device, void *p, size_t bytes) {
-        if (!p) return;
-        std::vector<Block> back;
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            idle.push_back(Block{device, p, bytes});
-            total += bytes;
-            while (idle.size() > kPoolBlocks || total > kPoolBytes) back.push_back(remove(0));
-        }
-        for (const Block &b : back) (void)hipFree(b.p);  // waits for the device
+    static void free(void *p) { (void)hipFree(p); }  // waits for the device
+    // All work of the current device, as hipFree waits for it on the way.  (Not
+    // hipDeviceSynchronize: it ends the graph captures of other threads, also
+    // those that allow allocations beside them.  1.3 us when the device is idle.)
+    static int wait() {
+        void *p = nullptr;
+        hipError_t e = hipMalloc(&p, 256);
+        if (e == hipSuccess) e = hipFree(p);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return (int)e;
     }
 };
-BlockPool &block_pool() {
-    static BlockPool *pool = new BlockPool;  // never destroyed: plans may outlive static objects
+BlockPool<HipDev> &block_pool() {
+    static auto *pool = new BlockPool<HipDev>;  // never destroyed: plans may outlive static objects
     return *pool;
+}
+// Memory of the current device (see BlockPool::alloc); *out is null on failure.
+template <typename T>
+hipError_t dev_alloc(T **out, size_t bytes) {
+    int dev = -1;
+    const hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    void *p = nullptr;
+    const int rc = block_pool().alloc(dev, &p, bytes);
+    *out = (T *)p;
+    return (hipError_t)rc;
 }
 
 void plan_free_workspace(cosim_plan *p) {
@@ -323,7 +265,7 @@ int ensure_workspace(cosim_plan *p, size_t systems, int chunks, size_t parts = 0
             // the FP32 factor slots alone, beside the workspace (nothing else
             // moves, so buffers that captured graphs use stay where they are)
             const size_t NP = (size_t)p->NP;
-            if (hipMalloc(&p->bA32, p->cap_systems * NP * NP * sizeof(float2)) != hipSuccess) {
+            if (dev_alloc(&p->bA32, p->cap_systems * NP * NP * sizeof(float2)) != hipSuccess) {
                 p->bA32 = nullptr;
                 (void)hipGetLastError();
                 return fail(COSIM_ENOMEM, "FP32 factor workspace for %zu systems failed",
@@ -340,28 +282,28 @@ int ensure_workspace(cosim_plan *p, size_t systems, int chunks, size_t parts = 0
     const size_t n = (size_t)p->n, NP = (size_t)p->NP;
     const bool big = big_plan(p->NP);
     if (big && p->ldl_ok &&
-        (hipMalloc((void **)&p->bX, ns * 64 * NP * sizeof(double2)) != hipSuccess ||
-         hipMalloc((void **)&p->bZmax, ns * sizeof(double)) != hipSuccess ||
-         hipMalloc((void **)&p->bD, ns * 2 * NP * sizeof(double2)) != hipSuccess)) {
+        (dev_alloc(&p->bX, ns * 64 * NP * sizeof(double2)) != hipSuccess ||
+         dev_alloc(&p->bZmax, ns * sizeof(double)) != hipSuccess ||
+         dev_alloc(&p->bD, ns * 2 * NP * sizeof(double2)) != hipSuccess)) {
         plan_free_workspace(p);
         (void)hipGetLastError();
         return fail(COSIM_ENOMEM, "LDL^T workspace for %zu systems failed", ns);
     }
-    if (need32 && hipMalloc(&p->bA32, ns * NP * NP * sizeof(float2)) != hipSuccess) {
+    if (need32 && dev_alloc(&p->bA32, ns * NP * NP * sizeof(float2)) != hipSuccess) {
         plan_free_workspace(p);
         (void)hipGetLastError();
         return fail(COSIM_ENOMEM, "FP32 factor workspace for %zu systems failed", ns);
     }
-    if (hipMalloc((void **)&p->I_ws, ns * n * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&p->rpart, np_parts * NP * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&p->lpart, nl_parts * sizeof(double)) != hipSuccess ||
-        (ngws > 0 && hipMalloc(&p->gws, ngws) != hipSuccess) ||
-        hipMalloc((void **)&p->gsys, ns * n * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&p->rec_status, ns * sizeof(int32_t)) != hipSuccess ||
-        hipMalloc((void **)&p->fac.L, ns * NP * NP * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&p->fac.piv_row, ns * NP * sizeof(int)) != hipSuccess ||
-        hipMalloc((void **)&p->fac.piv_val, ns * NP * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&p->fac.fmt, ns * sizeof(int)) != hipSuccess) {
+    if (dev_alloc(&p->I_ws, ns * n * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&p->rpart, np_parts * NP * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&p->lpart, nl_parts * sizeof(double)) != hipSuccess ||
+        (ngws > 0 && dev_alloc(&p->gws, ngws) != hipSuccess) ||
+        dev_alloc(&p->gsys, ns * n * sizeof(double)) != hipSuccess ||
+        dev_alloc(&p->rec_status, ns * sizeof(int32_t)) != hipSuccess ||
+        dev_alloc(&p->fac.L, ns * NP * NP * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&p->fac.piv_row, ns * NP * sizeof(int)) != hipSuccess ||
+        dev_alloc(&p->fac.piv_val, ns * NP * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&p->fac.fmt, ns * sizeof(int)) != hipSuccess) {
         plan_free_workspace(p);
         (void)hipGetLastError();
         return fail(COSIM_ENOMEM, "workspace allocation for %zu systems, %zu partial sums failed",
@@ -536,12 +478,12 @@ int pool_group_ws(StreamPool *pool, size_t nA, size_t nX, size_t nD, size_t nPiv
     dfree(pool->gFmt);
     dfree(pool->gZmax);
     pool->capA = pool->capX = pool->capD = pool->capPiv = pool->capSys = 0;
-    if (hipMalloc((void **)&pool->gA, nA * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&pool->gX, nX * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&pool->gD, nD * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&pool->gPiv, nPiv * sizeof(int)) != hipSuccess ||
-        hipMalloc((void **)&pool->gFmt, nSys * sizeof(int)) != hipSuccess ||
-        hipMalloc((void **)&pool->gZmax, nSys * sizeof(double)) != hipSuccess) {
+    if (dev_alloc(&pool->gA, nA * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&pool->gX, nX * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&pool->gD, nD * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&pool->gPiv, nPiv * sizeof(int)) != hipSuccess ||
+        dev_alloc(&pool->gFmt, nSys * sizeof(int)) != hipSuccess ||
+        dev_alloc(&pool->gZmax, nSys * sizeof(double)) != hipSuccess) {
         dfree(pool->gA);
         dfree(pool->gX);
         dfree(pool->gD);
@@ -765,7 +707,7 @@ int cosim_assemble_component(cosim_geom_t g, int P, const double *pts_d, double 
     const size_t oHost = bytes;
     const size_t oR = take(n, 8), oPhi = take(3 * n, 8), oWa = take(n, 8);
     const size_t oVerts = take(g->mverts.size(), 8), oSeg = take(n + 1, sizeof(int32_t));
-    if (block_pool().take(p->device, bytes, &p->arena, &p->arena_bytes) != hipSuccess) {
+    if (block_pool().take(p->device, bytes, &p->arena, &p->arena_bytes) != 0) {
         p->arena = nullptr;
         return cleanup(fail(COSIM_ENOMEM, "device allocation for the operators failed"));
     }
@@ -838,6 +780,11 @@ int cosim_plan_factorisations(cosim_plan_t p, long long *count) {
     if (!p) return fail(COSIM_EINVAL, "null plan");
     if (!count) return fail(COSIM_EINVAL, "count is null");
     *count = p->factorisations;
+    return COSIM_OK;
+}
+
+int cosim_trim(void) {
+    (void)block_pool().drain(-1);
     return COSIM_OK;
 }
 
@@ -1329,8 +1276,8 @@ int cosim_loss_and_grad_params(cosim_plan_t p, int B, int F, const double *C_d,
         dfree(p->mu_ws);
         dfree(p->gpar_ws);
         p->par_cap = 0;
-        if (hipMalloc((void **)&p->mu_ws, S * n * sizeof(double2)) != hipSuccess ||
-            hipMalloc((void **)&p->gpar_ws, (2 * S * n + S) * sizeof(double)) != hipSuccess) {
+        if (dev_alloc(&p->mu_ws, S * n * sizeof(double2)) != hipSuccess ||
+            dev_alloc(&p->gpar_ws, (2 * S * n + S) * sizeof(double)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(COSIM_ENOMEM, "parameter-gradient workspace for %zu systems failed", S);
         }
@@ -1891,9 +1838,9 @@ int cosim_plan_autotune(cosim_plan_t p, int B, int F, const double *C_d, const d
         if (e1) (void)hipEventDestroy(e1);
         return code;
     };
-    if (hipMalloc((void **)&loss, (size_t)B * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&grad, (size_t)B * p->n * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&status, S * sizeof(int32_t)) != hipSuccess ||
+    if (dev_alloc(&loss, (size_t)B * sizeof(double)) != hipSuccess ||
+        dev_alloc(&grad, (size_t)B * p->n * sizeof(double)) != hipSuccess ||
+        dev_alloc(&status, S * sizeof(int32_t)) != hipSuccess ||
         hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return done(fail(COSIM_ENOMEM, "autotune scratch allocation failed"));
     const int nv = plan_variants(p, (Prec)precision);
@@ -2053,14 +2000,14 @@ int sp_ensure(cosim_sp *p, int B) {
     // batches are factored in slabs
     const size_t slots = std::min<size_t>(S, (size_t)1 << 17);
     const size_t psz = f64 ? sizeof(double2) : sizeof(float2);
-    if (hipMalloc((void **)&p->w.X, S * n0 * sizeof(double2)) != hipSuccess ||
-        hipMalloc(&p->w.Xg, S * n0 * sizeof(double2)) != hipSuccess ||
-        (f32 && hipMalloc(&p->w.Y, S * (size_t)rows * sizeof(float2)) != hipSuccess) ||
-        hipMalloc(&p->w.Rp, parts * n0 * psz) != hipSuccess ||
-        hipMalloc((void **)&p->w.lpart, parts * sizeof(double)) != hipSuccess ||
-        hipMalloc((void **)&p->w.lu, slots * n0 * n0 * sizeof(double2)) != hipSuccess ||
-        hipMalloc((void **)&p->w.piv, slots * n0 * sizeof(int)) != hipSuccess ||
-        hipMalloc((void **)&p->w.dinv, slots * n0 * sizeof(double2)) != hipSuccess) {
+    if (dev_alloc(&p->w.X, S * n0 * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&p->w.Xg, S * n0 * sizeof(double2)) != hipSuccess ||
+        (f32 && dev_alloc(&p->w.Y, S * (size_t)rows * sizeof(float2)) != hipSuccess) ||
+        dev_alloc(&p->w.Rp, parts * n0 * psz) != hipSuccess ||
+        dev_alloc(&p->w.lpart, parts * sizeof(double)) != hipSuccess ||
+        dev_alloc(&p->w.lu, slots * n0 * n0 * sizeof(double2)) != hipSuccess ||
+        dev_alloc(&p->w.piv, slots * n0 * sizeof(int)) != hipSuccess ||
+        dev_alloc(&p->w.dinv, slots * n0 * sizeof(double2)) != hipSuccess) {
         (void)hipGetLastError();
         return fail(COSIM_ENOMEM, "S-parameter workspace for %d configurations failed", B);
     }
@@ -2144,18 +2091,18 @@ int cosim_sp_create(int n0, int n1, int F, int P, int ncomp, const double *S0_d,
         for (int e = 0; e < nvar; ++e)
             if (idx_x[e] < n0) rowent[at[idx_x[e]]++] = e;
     }
-    SP_TRY(hipMalloc((void **)&d.S0T, (size_t)F * n0 * n0 * sizeof(double2)));
-    SP_TRY(hipMalloc((void **)&d.KT, (size_t)F * n0 * n0 * sizeof(double2)));
-    SP_TRY(hipMalloc((void **)&d.rowptr, rowptr.size() * sizeof(int)));
-    SP_TRY(hipMalloc((void **)&d.rowent, rowent.size() * sizeof(int)));
+    SP_TRY(dev_alloc(&d.S0T, (size_t)F * n0 * n0 * sizeof(double2)));
+    SP_TRY(dev_alloc(&d.KT, (size_t)F * n0 * n0 * sizeof(double2)));
+    SP_TRY(dev_alloc(&d.rowptr, rowptr.size() * sizeof(int)));
+    SP_TRY(dev_alloc(&d.rowent, rowent.size() * sizeof(int)));
     SP_TRY(hipMemcpyAsync(d.rowptr, rowptr.data(), rowptr.size() * sizeof(int), hipMemcpyHostToDevice, st));
     SP_TRY(hipMemcpyAsync(d.rowent, rowent.data(), rowent.size() * sizeof(int), hipMemcpyHostToDevice, st));
-    SP_TRY(hipMalloc((void **)&d.r0, (size_t)F * n0 * sizeof(double2)));
-    SP_TRY(hipMalloc((void **)&d.exc, (size_t)n1 * sizeof(double2)));
-    SP_TRY(hipMalloc((void **)&d.ix, std::max(nvar, 1) * sizeof(int)));
-    SP_TRY(hipMalloc((void **)&d.iy, std::max(nvar, 1) * sizeof(int)));
-    SP_TRY(hipMalloc((void **)&d.fields64, nf * sizeof(double2)));
-    if (precisions & (1 << COSIM_FP32)) SP_TRY(hipMalloc((void **)&d.fields32, nf * sizeof(float2)));
+    SP_TRY(dev_alloc(&d.r0, (size_t)F * n0 * sizeof(double2)));
+    SP_TRY(dev_alloc(&d.exc, (size_t)n1 * sizeof(double2)));
+    SP_TRY(dev_alloc(&d.ix, std::max(nvar, 1) * sizeof(int)));
+    SP_TRY(dev_alloc(&d.iy, std::max(nvar, 1) * sizeof(int)));
+    SP_TRY(dev_alloc(&d.fields64, nf * sizeof(double2)));
+    if (precisions & (1 << COSIM_FP32)) SP_TRY(dev_alloc(&d.fields32, nf * sizeof(float2)));
     SP_TRY(hipMemcpyAsync(d.fields64, fields_d, nf * sizeof(double2), hipMemcpyDeviceToDevice, st));
     SP_TRY(hipMemcpyAsync(d.exc, exc, (size_t)n1 * sizeof(double2), hipMemcpyHostToDevice, st));
     if (nvar > 0) {
