@@ -77,8 +77,9 @@ __device__ inline int acc_row(int g, int m) {
     return sizeof(T) == 8 ? g + 4 * m : 4 * g + m;
 }
 
-// 1/a of a pivot that is checked afterwards: hardware reciprocal and two
-// Newton steps (error at the rounding of the result, no division sequence).
+// 1/a of a pivot that is checked afterwards (block_min_pivot): hardware
+// reciprocal and two Newton steps (error at the rounding of the result, no
+// division sequence).
 __device__ inline double2 zinv_nr(double2 a) {
     const double q = fma(a.x, a.x, a.y * a.y);
     double r = __builtin_amdgcn_rcp(q);
@@ -300,11 +301,12 @@ __device__ __forceinline__ void ldl_block(BlockLds &m, f64x4 (&Cr)[3], f64x4 (&C
     __syncthreads();
 }
 
-// Smallest |re| + |im| of the first n pivots, 0 if one is NaN (one wave).
+// Smallest |re| + |im| of the first n pivots, 0 if one is NaN or outside the
+// range in which zinv_nr holds (its square has to be a normal number); one wave.
 __device__ __forceinline__ double block_min_pivot(const BlockLds &m, int lane, int n) {
     const double2 d = m.pivot(lane);
     double v = fabs(d.x) + fabs(d.y);
-    v = v == v ? v : 0.0;
+    v = v > 1e-150 && v < 1e150 ? v : 0.0;
     v = lane < n ? v : __builtin_inf();
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off));
