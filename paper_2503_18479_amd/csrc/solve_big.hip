@@ -394,7 +394,7 @@ __device__ __forceinline__ void ldl_diag_load(int NP, const SysRef &sys, int ib,
 // Diagonal block ib: Z_ii - sum over the super-panel's rows [64 js, 64 ib) of
 // u d u^T, then ldl_block and y = X (E - j w Phi - L y).
 template <typename T2>
-__device__ __forceinline__ void ldl_diag(int NP, int s, const DiagIn &in, int ib, int js, T2 *__restrict__ A,
+__device__ __forceinline__ void ldl_diag(int NP, int n, int s, const DiagIn &in, int ib, int js, T2 *__restrict__ A,
                                          T2 *__restrict__ XT, double2 *__restrict__ D,
                                          int *__restrict__ fmt, double zmax, LdlLds &m) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -457,7 +457,7 @@ __device__ __forceinline__ void ldl_diag(int NP, int s, const DiagIn &in, int ib
     T2 *X = XT + (size_t)ib * 64 * 64;
     ldl_block<T2, true>(m, Cr, Ci, X, A + (size_t)k0 * NP + k0, NP, D + k0);
     if (wv == 0) {
-        const double dmin = block_min_pivot(m, lane, 64);
+        const double dmin = block_min_pivot(m, lane, n - k0);  // not the padding's pivots of 1
         if (lane == 0 && !(dmin >= 1e-5 * zmax)) fmt[s] = kFmtNeedsPivot;
     }
     if (kY) {
@@ -521,7 +521,7 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_start(int NP, int S, Src src, T2
     if (bad) return;  // whole workgroup: left to the pivoted LU
     if (tid < 64) m.sz[tid] = z_diag(r, tid);
     __syncthreads();
-    ldl_diag(NP, s, in, 0, 0, Aall + (size_t)s * NP * NP, Xall + (size_t)s * 64 * NP,
+    ldl_diag(NP, r.n, s, in, 0, 0, Aall + (size_t)s * NP * NP, Xall + (size_t)s * 64 * NP,
              Dall + (size_t)s * 2 * NP, fmt, zm, m);
 }
 
@@ -662,7 +662,7 @@ __global__ __launch_bounds__(kTB, 2) void k_ldl_step(int NP, int S, Src src, int
     __syncthreads();     // the rows of block kb are operands of the diagonal block
     DiagIn in;
     ldl_diag_load(NP, sys, ib, js, A, D, in);
-    ldl_diag(NP, s, in, ib, js, A, XT, D, fmt, zmax[s], m);
+    ldl_diag(NP, sys.n, s, in, ib, js, A, XT, D, fmt, zmax[s], m);
 }
 
 // After the super-panel of blocks js .. ns - 1: its rows subtracted from the
