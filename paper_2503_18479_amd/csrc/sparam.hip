@@ -28,6 +28,7 @@
 #include <rocblas/rocblas.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "epilogue.h"
 #include "internal.h"
@@ -55,31 +56,20 @@ template <int CTRL>
 __device__ inline int dpp_i(int x) {
     return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xF, 0xF, false);
 }
-// (magnitude, row) arg-max step with a DPP partner; ties to the lower row
-template <int CTRL>
-__device__ inline void amax_step(float &m, int &idx) {
-    const float m2 = __int_as_float(dpp_i<CTRL>(__float_as_int(m)));
-    const int i2 = dpp_i<CTRL>(idx);
-    const bool take = (m2 > m) || (m2 == m && i2 < idx);
-    m = take ? m2 : m;
-    idx = take ? i2 : idx;
-}
-// arg-max over the wave: DPP inside each row of 16 lanes, shuffles across rows
-__device__ inline int wave_amax(float m, int idx) {
-    amax_step<0xB1>(m, idx);   // quad_perm [1,0,3,2]
-    amax_step<0x4E>(m, idx);   // quad_perm [2,3,0,1]
-    amax_step<0x141>(m, idx);  // row_half_mirror
-    amax_step<0x140>(m, idx);  // row_mirror
-#pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {
-        const float om = __shfl_xor(m, off);
-        const int oi = __shfl_xor(idx, off);
-        if (om > m || (om == m && oi < idx)) {
-            m = om;
-            idx = oi;
-        }
-    }
-    return __builtin_amdgcn_readfirstlane(idx);
+// The lane with the largest m over the wave (m = -1, or >= 0 and no NaN), ties to
+// the lower lane: the bits of such floats order like integers, so that the
+// largest is a DPP maximum inside each row of 16 lanes and a scalar one of the
+// four rows, and its lane the first set bit of a comparison.
+__device__ inline int wave_amax(float m) {
+    const int own = __float_as_int(m);
+    int b = own;
+    b = max(b, dpp_i<0xB1>(b));   // quad_perm [1,0,3,2]
+    b = max(b, dpp_i<0x4E>(b));   // quad_perm [2,3,0,1]
+    b = max(b, dpp_i<0x141>(b));  // row_half_mirror
+    b = max(b, dpp_i<0x140>(b));  // row_mirror
+    const int top = max(max(__builtin_amdgcn_readlane(b, 0), __builtin_amdgcn_readlane(b, 16)),
+                        max(__builtin_amdgcn_readlane(b, 32), __builtin_amdgcn_readlane(b, 48)));
+    return (int)__builtin_ctzll(__ballot(own == top));
 }
 __device__ inline double rl(double v, int src) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), src);
@@ -168,7 +158,7 @@ __device__ __forceinline__ void sp_steps(double2 (&a)[32], SpElim &e, int kbase,
             mg = (float)(fabs(a[0].x) + fabs(a[0].y));
             if (!(mg == mg)) mg = __builtin_inff();  // a NaN wins
         }
-        const int p = wave_amax(mg, lane);
+        const int p = wave_amax(mg);
         const double2 d = rl2(a[0], p);
         if (!(d.x != 0.0 || d.y != 0.0)) e.flag |= COSIM_SYS_SINGULAR;
         const double2 inv = zinv_fast(d);
@@ -229,7 +219,12 @@ __device__ __forceinline__ void sp_load_columns(const SpDev &d, int f, const dou
 // complex128, 1: complex64), the status and the record.  Without barriers the
 // waves of a SIMD hide each other's pivot chains; the four-wave form with
 // the matrix in LDS and three barriers per column took 592 us for 2,560
-// systems of 64 ports, this one 290 (three waves per SIMD spill: 395).
+// systems of 64 ports, this one 248 (three waves per SIMD spill: 395).  For one
+// system it is the chain of pivots that counts: the pivot search is integer
+// maxima and one comparison (with the row carried beside the magnitude through
+// shuffles 64 ports took 120 us, 100 now, the four-wave form 115), and the steps
+// leave out the columns past n0 (16 ports, 3,000 x 2 systems: 113 us with all 32,
+// 68 now, the four-wave form 99).
 template <int PREC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_sp_lu(
     SpDev d, int B, int s0, const double2 *__restrict__ values, double2 *__restrict__ X, void *Xg,
@@ -243,38 +238,60 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     e.t = lane < n0 ? d.r0[(size_t)f * n0 + lane] : make_double2(0.0, 0.0);
     double2 a[32];
     sp_load_columns<true>(d, f, v, lane, 0, a, e.t);
+    // eight steps at a time, with the columns that are left (a multiple of 8)
     auto half = [&](int kbase) {
-        const int left = n0 - kbase;  // > 0
-        sp_steps<32>(a, e, kbase, min(left, 8), n0, lane, frow);
-        if (left > 8) sp_steps<24>(a, e, kbase + 8, min(left - 8, 8), n0, lane, frow);
-        if (left > 16) sp_steps<16>(a, e, kbase + 16, min(left - 16, 8), n0, lane, frow);
-        if (left > 24) sp_steps<8>(a, e, kbase + 24, min(left - 24, 8), n0, lane, frow);
+        int left = min(n0 - kbase, 32);  // > 0
+        if (left > 24) {
+            sp_steps<32>(a, e, kbase, 8, n0, lane, frow);
+            kbase += 8;
+            left -= 8;
+        }
+        if (left > 16) {
+            sp_steps<24>(a, e, kbase, 8, n0, lane, frow);
+            kbase += 8;
+            left -= 8;
+        }
+        if (left > 8) {
+            sp_steps<16>(a, e, kbase, 8, n0, lane, frow);
+            kbase += 8;
+            left -= 8;
+        }
+        sp_steps<8>(a, e, kbase, left, n0, lane, frow);
     };
     half(0);
     if (n0 > 32) {
         sp_load_columns<false>(d, f, v, lane, 32, a, e.t);
-        // the steps of the first half on these columns
-        for (int k0 = 0; k0 < 32; k0 += 8) {
-            double2 l8[8];
+        // the steps of the first half on these columns (the first `w`)
+        auto earlier = [&](auto w) {
+            for (int k0 = 0; k0 < 32; k0 += 8) {
+                double2 l8[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) l8[u] = frow[k0 + u];
+                for (int u = 0; u < 8; ++u) l8[u] = frow[k0 + u];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int k = k0 + u;
-                const int p = __builtin_amdgcn_readlane(e.pk, k);
-                const double2 l = e.step > k ? l8[u] : make_double2(0.0, 0.0);
+                for (int u = 0; u < 8; ++u) {
+                    const int k = k0 + u;
+                    const int p = __builtin_amdgcn_readlane(e.pk, k);
+                    const double2 l = e.step > k ? l8[u] : make_double2(0.0, 0.0);
 #pragma unroll
-                for (int j = 0; j < 32; ++j) a[j] = zfms(a[j], l, rl2(a[j], p));
+                    for (int j = 0; j < decltype(w)::value; ++j) a[j] = zfms(a[j], l, rl2(a[j], p));
+                }
             }
-        }
+        };
+        if (n0 > 48) earlier(std::integral_constant<int, 32>{});
+        else if (n0 > 40) earlier(std::integral_constant<int, 16>{});
+        else earlier(std::integral_constant<int, 8>{});
         half(32);
     }
     // back substitution: x_k, then its column off the rows of earlier steps
     double2 x = make_double2(0.0, 0.0);
-    for (int k1 = n0; k1 > 0; k1 -= 8) {
-        double2 u8[8];
+    double2 u8[8], next[8];  // the rows' entries of eight steps, and of the eight below
+    auto rows = [&](int k1, double2 (&u)[8]) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) u8[u] = frow[max(k1 - 1 - u, 0)];
+        for (int i = 0; i < 8; ++i) u[i] = frow[max(k1 - 1 - i, 0)];
+    };
+    rows(n0, u8);
+    for (int k1 = n0; k1 > 0; k1 -= 8) {
+        rows(k1 - 8, next);
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             const int k = k1 - 1 - u;
@@ -285,6 +302,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
             const double2 c = e.step < k ? u8[u] : make_double2(0.0, 0.0);
             e.t = zfms(e.t, c, xk);
         }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) u8[u] = next[u];
     }
     int flag = e.flag;
     const bool finite = isfinite(x.x) && isfinite(x.y);
