@@ -492,15 +492,19 @@ template <int NP>
 __global__ __launch_bounds__(GJShape<NP>::BLOCK) void k_gj_fallback(
     int n, int S, int F, const double *__restrict__ M, const double *__restrict__ Rv,
     const double *__restrict__ phi, const double *__restrict__ C,
-    const double *__restrict__ omega, double2 *__restrict__ I, int32_t *__restrict__ status,
-    GJFactor fac) {
+    const double *__restrict__ omega, double2 *__restrict__ I, int32_t *status, GJFactor fac,
+    int32_t *__restrict__ rec_status) {
     __shared__ GjLds<NP> lds;
     const int s0 = blockIdx.x * kFbSystems + threadIdx.x;
     auto run = [&](int s) {
         gj_system<NP, false>(lds, s, n, S, F, M, Rv, phi, C, omega, nullptr, nullptr, 0, 0.0, I,
                              nullptr, status, false, fac, true);
     };
-    fallback_systems<NP>(S, run, threadIdx.x < kFbSystems && s0 < S ? fac.fmt + s0 : nullptr);
+    const bool mine = threadIdx.x < kFbSystems && s0 < S;
+    fallback_systems<NP>(S, run, mine ? fac.fmt + s0 : nullptr);
+    // the record's copy of the status, final now (the marked systems' by the
+    // barrier behind each)
+    if (rec_status && mine) rec_status[s0] = status[s0];
 }
 
 // The same over the S systems of a group.
@@ -1029,15 +1033,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WPE))) void 
 // accumulators (ldl_block), with X = L^-1 recorded in place of L (kFmtInv), so
 // that both triangular solves, here and in the adjoint, are products with X
 // instead of chains of 64 columns; the pivoted elimination, if it is needed,
-// runs in the same launch.  Only latency counts here: 48 systems of 64 loops
-// take 28.8 us forward and 8.8 us in the adjoint, where a wave per system, the
-// launch for the pivoted ones and the replay took 47.4 and 25.2.  The line is
-// drawn by what a plan has, not by what a launch has, so that a member of a
-// group takes the route (and gets the bits) it has alone: with more systems the
-// four waves of each cost more than they save (groups of 24 plans of 64 loops,
-// whole call: 8 systems each 238 us against 282, 32 each 285 against 296, 48
-// each 336 against 332, 64 each 363 against 344).
-constexpr int kFewSystems = 48;
+// runs in the same launch.  This is the shorter way through one system, but
+// it takes more of the chip per system: 48 systems of 64 loops take 28.8 us
+// forward and 8.8 us in the adjoint, where a wave per system, the launch for the
+// pivoted ones and the replay take 47.4 and 25.2, while 1,152 take 98 and 30 us
+// against 76 and 37 (512 workgroups are resident at once).
+//   The line is drawn by what a plan has, not by what a launch has, so that a
+// member of a group takes the route (and gets the bits) it has alone; it lies
+// where groups of up to 256 members stop gaining.  Whole calls, 64 loops, 4,096
+// points, us by this route / by the other:
+//   systems   one plan   48 plans   128 plans   256 plans
+//       8      45 / 71   290 / 305   457 / 501    706 / 758
+//      12      45 / 72   296 / 310   502 / 523    824 / 796
+//      16      46 / 72   303 / 314   552 / 538    907 / 826
+//      24         -      344 / 328   673 / 593  1,137 / 917
+//      48      48 / 76   484 / 400   992 / 742        -
+// (12 systems, 256 plans: 838 us before there were two routes.)
+constexpr int kFewSystems = 12;
 
 union Small64Lds {
     struct {
@@ -1663,11 +1675,8 @@ hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const doub
     }
     hipLaunchKernelGGL(k_gj_fallback<64>, dim3((S + kFbSystems - 1) / kFbSystems),
                        dim3(GJShape<64>::BLOCK), 0, st, n, S, F, M_d, R_d, phi_d, C_d, omega_d, I_d,
-                       status_d, fac);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !rec_status_d) return e;
-    return hipMemcpyAsync(rec_status_d, status_d, (size_t)S * sizeof(int32_t),
-                          hipMemcpyDeviceToDevice, st);
+                       status_d, fac, rec_status_d);
+    return hipGetLastError();
 }
 
 hipError_t launch_replay_adjoint(int NP, int n, int S, int F, GJFactor fac, const double *C_d,
