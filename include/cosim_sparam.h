@@ -79,7 +79,10 @@ int cosim_sp_create(int n0, int n1, int F, int P, int ncomp, const double *S0_d,
 int cosim_sp_destroy(cosim_sp_t plan);
 
 /* Reserves the workspace for up to max_batch configurations (allocates; the
- * field and loss calls allocate on first use otherwise). */
+ * field and loss calls allocate on first use otherwise).  The larger part is
+ * the factor record, 16 n0^2 bytes per system (64 KiB at 64 ports) for up to
+ * 131,072 systems, for programs that only call cosim_sp_field too; where memory
+ * is short it is made smaller and the systems are factored in slabs. */
 int cosim_sp_reserve(cosim_sp_t plan, int max_batch);
 
 /* Forward pipeline for B >= 0 configurations.

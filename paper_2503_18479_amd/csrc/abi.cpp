@@ -1996,20 +1996,25 @@ int sp_ensure(cosim_sp *p, int B) {
         parts = std::max(parts, (size_t)sp_fused_chunks(p->d, b) * b * p->d.F);
         if (b == B) break;
     }
-    // factor records for up to 2^17 systems (8.6 GB at 64 ports); larger
-    // batches are factored in slabs
-    const size_t slots = std::min<size_t>(S, (size_t)1 << 17);
     const size_t psz = f64 ? sizeof(double2) : sizeof(float2);
+    auto failed = [&] { return fail(COSIM_ENOMEM, "S-parameter workspace for %d configurations failed", B); };
     if (dev_alloc(&p->w.X, S * n0 * sizeof(double2)) != hipSuccess ||
         dev_alloc(&p->w.Xg, S * n0 * sizeof(double2)) != hipSuccess ||
         (f32 && dev_alloc(&p->w.Y, S * (size_t)rows * sizeof(float2)) != hipSuccess) ||
         dev_alloc(&p->w.Rp, parts * n0 * psz) != hipSuccess ||
-        dev_alloc(&p->w.lpart, parts * sizeof(double)) != hipSuccess ||
-        dev_alloc(&p->w.lu, slots * n0 * n0 * sizeof(double2)) != hipSuccess ||
-        dev_alloc(&p->w.piv, slots * n0 * sizeof(int)) != hipSuccess ||
-        dev_alloc(&p->w.dinv, slots * n0 * sizeof(double2)) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(COSIM_ENOMEM, "S-parameter workspace for %d configurations failed", B);
+        dev_alloc(&p->w.lpart, parts * sizeof(double)) != hipSuccess)
+        return failed();
+    // factor records for up to 2^17 systems (8.6 GB at 64 ports), fewer if the
+    // memory is short; larger batches are factored in slabs
+    size_t slots = std::min<size_t>(S, (size_t)1 << 17);
+    while (dev_alloc(&p->w.lu, slots * n0 * n0 * sizeof(double2)) != hipSuccess ||
+           dev_alloc(&p->w.piv, slots * n0 * sizeof(int)) != hipSuccess ||
+           dev_alloc(&p->w.dinv, slots * n0 * sizeof(double2)) != hipSuccess) {
+        dfree(p->w.lu);
+        dfree(p->w.piv);
+        dfree(p->w.dinv);
+        if (slots <= 256) return failed();
+        slots /= 2;
     }
     p->w.B = B;
     p->w.rows = rows;
