@@ -1402,8 +1402,10 @@ __device__ __forceinline__ void replay_system(int s, int n, int S, int F, GJFact
         const double ck = C[(size_t)b * n + lane];
         // 2 Re(mu I / (j w C^2)) = 2 Im(mu I) / (w C^2)
         const double g = 2.0 * (x.x * Ik.y + x.y * Ik.x) / (w * ck * ck);
-        // with one frequency the system's term is the configuration's gradient
-        (fin.grad ? fin.grad : gsys)[(size_t)s * n + lane] = g;
+        // with one frequency the system's term is the configuration's gradient (a
+        // sum that starts from 0, as reduce_config's, has no negative zero)
+        if (fin.grad) fin.grad[(size_t)s * n + lane] = 0.0 + g;
+        else gsys[(size_t)s * n + lane] = g;
         if (mu) mu[(size_t)s * n + lane] = x;
         nonfinite = !bad && !isfinite(g);
     }
@@ -1498,7 +1500,8 @@ __device__ __forceinline__ void replay64_system(
     // invalid input and no vanishing pivot
     const double gk = 2.0 * (x.x * Ik.y + x.y * Ik.x) / (w * ck * ck);
     if (lane < n) {
-        (fin.grad ? fin.grad : gsys)[(size_t)s * n + lane] = gk;
+        if (fin.grad) fin.grad[(size_t)s * n + lane] = 0.0 + gk;  // see replay_system
+        else gsys[(size_t)s * n + lane] = gk;
         if (mu) mu[(size_t)s * n + lane] = x;
     }
     const bool any = __ballot(lane < n && !isfinite(gk)) != 0;
