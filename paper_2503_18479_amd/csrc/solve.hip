@@ -447,11 +447,10 @@ __global__ __launch_bounds__(GJShape<NP>::BLOCK) void k_gj(
     const double *__restrict__ phi, const double *__restrict__ C,
     const double *__restrict__ omega, const double2 *__restrict__ Iin,
     const double2 *__restrict__ rpart, int nchunk, double rscale, double2 *__restrict__ Iout,
-    double *__restrict__ gsys, int32_t *__restrict__ status, bool or_status,
-    GJFactor fac, bool fallback_only) {
+    double *__restrict__ gsys, int32_t *__restrict__ status, bool or_status, GJFactor fac) {
     __shared__ GjLds<NP> lds;
     gj_system<NP, ADJ>(lds, blockIdx.x, n, S, F, M, Rv, phi, C, omega, Iin, rpart, nchunk, rscale,
-                       Iout, gsys, status, or_status, fac, fallback_only);
+                       Iout, gsys, status, or_status, fac, false);
 }
 
 // Member of a group that holds global system sg (wave-uniform): members are
@@ -899,8 +898,9 @@ __device__ __forceinline__ bool ldl_system(
                 for (int c = 0; c < PW; ++c)
                     if (r > k0 + c && r < n) lrow[k0 / 8][c] = l[c];
             }
-            // D_c = V_cc to the lane of column c
-            if (r >= k0 && r < k0 + PW) dk = vv[r][r - k0];
+            // D_c = V_cc to the lane of column c (with KEEP the padded columns of a
+            // last panel are not formed: 1 stays)
+            if (r >= k0 && r < k0 + PW && (!KEEP || r < n)) dk = vv[r][r - k0];
             // forward substitution for the panel's columns: y_r -= L_rc y_c (r > k0 + c)
 #pragma unroll
             for (int c = 0; c < PW; ++c) {
@@ -1617,17 +1617,17 @@ hipError_t launch_gj(int NP, int n, int S, int F, const double *M, const double 
                      const double *phi, const double *C, const double *omega, const double2 *Iin,
                      const double2 *rpart, int nchunk, double rscale, double2 *Iout,
                      double *gsys, int32_t *status, bool or_status, GJFactor fac,
-                     bool fallback_only, hipStream_t st) {
+                     hipStream_t st) {
     switch (NP) {
         case 32:
             hipLaunchKernelGGL((k_gj<32, ADJ>), dim3(S), dim3(GJShape<32>::BLOCK), 0, st, n, S,
                                F, M, R, phi, C, omega, Iin, rpart, nchunk, rscale, Iout, gsys,
-                               status, or_status, fac, fallback_only);
+                               status, or_status, fac);
             break;
         case 64:
             hipLaunchKernelGGL((k_gj<64, ADJ>), dim3(S), dim3(GJShape<64>::BLOCK), 0, st, n, S,
                                F, M, R, phi, C, omega, Iin, rpart, nchunk, rscale, Iout, gsys,
-                               status, or_status, fac, fallback_only);
+                               status, or_status, fac);
             break;
         default:
             return hipErrorInvalidValue;
@@ -1642,7 +1642,7 @@ hipError_t launch_solve_forward(int NP, int n, int S, int F, const double *M_d,
                                 const double *omega_d, double2 *I_d, int32_t *status_d,
                                 GJFactor fac, hipStream_t st) {
     return launch_gj<false>(NP, n, S, F, M_d, R_d, phi_d, C_d, omega_d, nullptr, nullptr, 0, 0.0,
-                            I_d, nullptr, status_d, false, fac, false, st);
+                            I_d, nullptr, status_d, false, fac, st);
 }
 
 hipError_t launch_ldl(int NP, int n, int S, int F, const double *M_d, const double *R_d,
@@ -1719,7 +1719,7 @@ hipError_t launch_solve_adjoint(int NP, int n, int S, int F, const double *M_d,
                                 double rscale, double *gsys_d, double2 *mu_d, int32_t *status_d,
                                 bool or_status, hipStream_t st) {
     return launch_gj<true>(NP, n, S, F, M_d, R_d, nullptr, C_d, omega_d, I_d, rpart_d, nchunk,
-                           rscale, mu_d, gsys_d, status_d, or_status, GJFactor{}, false, st);
+                           rscale, mu_d, gsys_d, status_d, or_status, GJFactor{}, st);
 }
 
 hipError_t launch_reduce(int n, int B, int F, int nchunk, const double *gsys_d,

@@ -50,7 +50,6 @@ __device__ inline double2 zinv(double2 a) {
     const double d = 1.0 / (a.x * a.x + a.y * a.y);
     return make_double2(a.x * d, -a.y * d);
 }
-__device__ inline double2 zconj(double2 a) { return make_double2(a.x, -a.y); }
 
 template <int CTRL>
 __device__ inline int dpp_i(int x) {
