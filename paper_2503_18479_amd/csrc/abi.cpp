@@ -1349,8 +1349,9 @@ struct ManyCall {
     const double *const *C_d, *const *omega_d, *const *T_d;
     double *const *loss_d, *const *grad_d;
     int32_t *const *status_d;
-    int loss_mode, precision, ns;
+    int loss_mode, precision;
     StreamPool *pool;
+    const std::vector<hipStream_t> &streams;  // the side streams, or the call's own alone
     const std::vector<int> &chunks, &tpcs;
 };
 
@@ -1367,11 +1368,12 @@ static int enqueue_small_group(const ManyCall &mc, const std::vector<int> &g, in
     double *const *loss_d = mc.loss_d, *const *grad_d = mc.grad_d;
     int32_t *const *status_d = mc.status_d;
     const std::vector<int> &chunks = mc.chunks;
-    const int loss_mode = mc.loss_mode, precision = mc.precision, ns = mc.ns;
+    const int loss_mode = mc.loss_mode, precision = mc.precision;
+    const size_t ns = mc.streams.size();
     const Prec prec = (Prec)precision;
     const bool grad = grad_d != nullptr, ratio = loss_mode == COSIM_LOSS_RATIO;
     StreamPool *pool = mc.pool;
-    hipStream_t gs = pool->streams[k];
+    hipStream_t gs = mc.streams[k];
     const int NP = plans[g[0]]->NP;
     int first_rc = COSIM_OK;
     const std::vector<int> &tpcs = mc.tpcs;
@@ -1406,7 +1408,7 @@ static int enqueue_small_group(const ManyCall &mc, const std::vector<int> &g, in
     }
     hipEvent_t ev_fwd = pool->extra[group];
     if (launch_small_group(NP, sg, Sg, SmallPhase::Factor, gs) != hipSuccess ||
-        hipEventRecord(ev_fwd, gs) != hipSuccess) {
+        (ns > 1 && hipEventRecord(ev_fwd, gs) != hipSuccess)) {
         return fail(COSIM_EDEVICE, "grouped solve launch failed");
     }
     // contractions: one launch for the group when every member uses the
@@ -1441,10 +1443,10 @@ static int enqueue_small_group(const ManyCall &mc, const std::vector<int> &g, in
     for (size_t m = 0; !one && m < g.size() && first_rc == COSIM_OK; ++m) {
         const int i = g[m];
         cosim_plan *p = plans[i];
-        hipStream_t cs = pool->streams[(k + 1 + m) % ns];
+        hipStream_t cs = mc.streams[(k + 1 + m) % ns];
         hipEvent_t ev_c = pool->extra[next_ev++];
         const double *Ti = T_d[i];
-        bool ok = hipStreamWaitEvent(cs, ev_fwd, 0) == hipSuccess;
+        bool ok = cs == gs || hipStreamWaitEvent(cs, ev_fwd, 0) == hipSuccess;
         if (ok && ratio) {
             ok = launch_scale((size_t)p->P, std::fabs(p->bext_z), T_d[i], p->T_ratio, cs) ==
                  hipSuccess;
@@ -1455,8 +1457,8 @@ static int enqueue_small_group(const ManyCall &mc, const std::vector<int> &g, in
         ok = ok &&
              launch_fused(prec, NP, p->variant[precision], loss_mode, grad, a, cs) ==
                  hipSuccess &&
-             hipEventRecord(ev_c, cs) == hipSuccess &&
-             hipStreamWaitEvent(gs, ev_c, 0) == hipSuccess;
+             (cs == gs || (hipEventRecord(ev_c, cs) == hipSuccess &&
+                           hipStreamWaitEvent(gs, ev_c, 0) == hipSuccess));
         if (!ok) first_rc = fail_instance(fail(COSIM_EDEVICE, "contraction launch failed"), i);
     }
     if (first_rc != COSIM_OK) return first_rc;
@@ -1491,11 +1493,12 @@ static int enqueue_big_group(const ManyCall &mc, const std::vector<int> &g, int 
     double *const *loss_d = mc.loss_d, *const *grad_d = mc.grad_d;
     int32_t *const *status_d = mc.status_d;
     const std::vector<int> &chunks = mc.chunks;
-    const int loss_mode = mc.loss_mode, precision = mc.precision, ns = mc.ns;
+    const int loss_mode = mc.loss_mode, precision = mc.precision;
+    const size_t ns = mc.streams.size();
     const Prec prec = (Prec)precision;
     const bool grad = grad_d != nullptr, ratio = loss_mode == COSIM_LOSS_RATIO;
     StreamPool *pool = mc.pool;
-    hipStream_t gs = pool->streams[k];
+    hipStream_t gs = mc.streams[k];
     const int NP = plans[g[0]]->NP;
     int first_rc = COSIM_OK;
     GroupArgs ga{};
@@ -1578,7 +1581,7 @@ static int enqueue_big_group(const ManyCall &mc, const std::vector<int> &g, int 
             mwaves = sh.waves;  // a function of the padded loop count, shared by the group
             continue;
         }
-        hipStream_t cs = pool->streams[(k + 1 + m) % ns];
+        hipStream_t cs = mc.streams[(k + 1 + m) % ns];
         hipEvent_t ev_c = pool->extra[next_ev++];
         bool ok = hipStreamWaitEvent(cs, ev_fwd, 0) == hipSuccess;
         if (ok && ratio) {
@@ -1655,7 +1658,6 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
     if ((rc = stream_pool(plans[0]->device, &pool))) return rc;
     std::lock_guard<std::mutex> pool_lock(pool->mu);
     hipStream_t st = (hipStream_t)stream;
-    const int ns = std::min(kPoolStreams, count);
     // Instances with every R_k > 0 (no refinement, no phase timing) are
     // factored and solved together, up to kGroupMax (above 64 loops) or
     // kSmallGroupMax (64 or fewer) of one padded size per group: one launch per
@@ -1727,14 +1729,23 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
         }
     if (big_groups && (rc = pool_group_ws(pool, nA, nX, nD, nPiv, nSys))) return rc;
     if (!groups.empty() && (rc = pool_events(pool, groups.size() + count))) return rc;
-    HIP_TRY(hipEventRecord(pool->start, st));
-    for (int k = 0; k < ns; ++k) {
-        HIP_TRY(hipStreamWaitEvent(pool->streams[k], pool->start, 0));
+    // Under capture the call is one chain on `st`: a replay runs a graph's nodes
+    // one after another (the sum of the kernels' times is its span), so branches
+    // gain nothing there, and graphs with them are what the runtime has crashed
+    // on (see above and, replaying one with instances above 64 loops, once more).
+    const std::vector<hipStream_t> streams =
+        captured ? std::vector<hipStream_t>{st}
+                 : std::vector<hipStream_t>(pool->streams.begin(),
+                                            pool->streams.begin() + std::min(kPoolStreams, count));
+    const int ns = (int)streams.size();
+    if (!captured) HIP_TRY(hipEventRecord(pool->start, st));
+    for (int k = 0; k < ns && !captured; ++k) {
+        HIP_TRY(hipStreamWaitEvent(streams[k], pool->start, 0));
         // the group workspace is shared by every call on the device: wait
         // until the previous call that used it has finished (never under
         // capture, where no group uses it)
         if (big_groups && pool->ws_used)
-            HIP_TRY(hipStreamWaitEvent(pool->streams[k], pool->ws_free, 0));
+            HIP_TRY(hipStreamWaitEvent(streams[k], pool->ws_free, 0));
     }
     // largest work first, each item to the stream with the least work so far
     // (work ~ systems x (NP^3 for the solves + P NP for the contraction); a
@@ -1763,12 +1774,12 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
     int first_rc = COSIM_OK;
     int next_ev = (int)groups.size();
     const ManyCall mc{plans, B, F, C_d, omega_d, T_d, loss_d, grad_d, status_d,
-                      loss_mode, precision, ns, pool, chunks, tpcs};
+                      loss_mode, precision, pool, streams, chunks, tpcs};
     for (const Item &it : items) {
         if (first_rc != COSIM_OK) break;
         const int k = (int)(std::min_element(load.begin(), load.end()) - load.begin());
         load[k] += it.cost;
-        hipStream_t gs = pool->streams[k];
+        hipStream_t gs = streams[k];
         if (it.inst >= 0) {
             const int i = it.inst;
             if ((rc = cosim_loss_and_grad(plans[i], B[i], F[i], C_d[i], omega_d[i], T_d[i],
@@ -1783,8 +1794,8 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
         first_rc = big_plan(plans[g[0]]->NP) ? enqueue_big_group(mc, g, it.group, k, next_ev, off)
                                              : enqueue_small_group(mc, g, it.group, k, next_ev);
     }
-    for (int k = 0; k < ns; ++k) {  // join even after an error
-        HIP_TRY(hipEventRecord(pool->done[k], pool->streams[k]));
+    for (int k = 0; k < ns && !captured; ++k) {  // join even after an error
+        HIP_TRY(hipEventRecord(pool->done[k], streams[k]));
         HIP_TRY(hipStreamWaitEvent(st, pool->done[k], 0));
     }
     if (big_groups) {
