@@ -377,9 +377,9 @@ int cosim_adam_step(int count, double *C_d, const double *grad_d, double *m_d, d
  * streams (default priority; the largest instances first, each to the stream
  * with the least work so far) that wait for `stream` and that `stream` waits
  * for when the call returns, so the work is ordered on `stream` as one
- * operation and can be captured with it.  Under capture the instances follow
- * one another on `stream` itself (a replayed graph runs its nodes one after
- * another anyway).  Each plan's own workspace is used: reserve every plan
+ * operation and can be captured with it; under capture the instances follow one
+ * another on `stream` itself, so that a replay of many instances takes longer
+ * than the eager call.  Each plan's own workspace is used: reserve every plan
  * beforehand.
  * Outside stream capture, instances with every R_k > 0 (no refinement, no
  * phase timing) that share a padded loop count are factored and solved in

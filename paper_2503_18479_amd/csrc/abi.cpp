@@ -1729,10 +1729,14 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
         }
     if (big_groups && (rc = pool_group_ws(pool, nA, nX, nD, nPiv, nSys))) return rc;
     if (!groups.empty() && (rc = pool_events(pool, groups.size() + count))) return rc;
-    // Under capture the call is one chain on `st`: a replay runs a graph's nodes
-    // one after another (the sum of the kernels' times is its span), so branches
-    // gain nothing there, and graphs with them are what the runtime has crashed
-    // on (see above and, replaying one with instances above 64 loops, once more).
+    // Under capture the call is one chain on `st`.  As branches over the side
+    // streams captured calls have crashed the runtime on the host: at the end of
+    // the capture when side streams waited for each other both ways (a group's
+    // stream for its members' contractions and they for its forward solve: the
+    // grouped launches above, and members with a variant of their own), and
+    // once in a replay, of instances above 64 loops, with no cause found.  The
+    // chain costs what the branches overlapped (2,048 instances of 16 to 256
+    // loops: 229 ms per replay against 68; the eager call takes 20).
     const std::vector<hipStream_t> streams =
         captured ? std::vector<hipStream_t>{st}
                  : std::vector<hipStream_t>(pool->streams.begin(),

@@ -1,7 +1,9 @@
 """A captured call over instances of 64 loops or fewer is one chain of kernels on
 the capturing stream: groups in shared launches, members with a variant of
-their own, and one instance alone in its size; every replay equals the
-instances' own calls bit for bit, after eager work between the replays."""
+their own (as branches whose streams wait for each other both ways, these
+crashed the runtime at the end of the capture), and one instance alone in its
+size; every replay equals the instances' own calls bit for bit, after eager
+work between the replays."""
 import pytest
 
 import workloads as W
