@@ -360,7 +360,7 @@ int cosim_clip(int64_t count, double *x_d, double lo, double hi, void *stream);
  *   step_d   [1] int32, device: steps taken so far (0 before the first step);
  *            read as t - 1 and advanced by one
  * Requires 0 <= beta1, beta2 < 1, finite lr and eps >= 0 (else COSIM_EINVAL).
- * Enqueues two kernels on `stream` and nothing else; together with a reserved
+ * Enqueues one or two kernels on `stream` and nothing else; together with a reserved
  * cosim_loss_and_grad it can be captured in one HIP graph and replayed for
  * any number of steps, since t is read from device memory. */
 int cosim_adam_step(int count, double *C_d, const double *grad_d, double *m_d, double *v_d,
@@ -403,7 +403,9 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
 /* --------------------------------------------------------------------------
  * Tuning of the fused contraction (performance only; every variant computes
  * the same quantities to the precision's tolerance).  A variant fixes the
- * systems per wavefront and the field points per LDS tile.
+ * systems per wavefront and the field points per LDS tile; what a number
+ * stands for may change between builds of the library (0 is the default), so a
+ * tuning run's choice is kept with the build it was made with.
  * cosim_plan_set_variant / cosim_plan_get_variant select or read the variant
  * used for `precision` (0 is the default; n_variants receives the count).
  * cosim_plan_autotune runs cosim_loss_and_grad reps times (after one warm-up)
@@ -427,7 +429,8 @@ int cosim_plan_autotune(cosim_plan_t p, int B, int F, const double *C_d, const d
  * cosim_plan_timing_read waits for the recorded calls and writes, per call,
  * COSIM_PHASES durations in milliseconds to ms[record][phase]:
  *   0 forward solve, 1 fused contraction (B = G I, loss, G^T w),
- *   2 adjoint solve, 3 reductions.
+ *   2 adjoint solve, 3 reductions (up to 64 loops with one frequency the adjoint
+ *     solve forms the sums and phase 3 is empty).
  * *n_records receives the number of calls recorded; recording restarts at 0.
  * -------------------------------------------------------------------------- */
 enum { COSIM_PHASES = 4 };

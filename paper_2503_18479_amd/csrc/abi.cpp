@@ -1669,9 +1669,8 @@ int cosim_loss_and_grad_many(int count, const cosim_plan_t *plans, const int *B,
     // been run again.  Their groups would also keep factor records in the
     // pool's shared workspace, whose reuse across calls is ordered by the event
     // ws_free of the previous grouping call, recorded outside any capture.
-    // Groups of 64 loops or fewer use only their plans' workspaces and events
-    // recorded inside the call (and capture correctly), so they are grouped
-    // under capture too.
+    // Groups of 64 loops or fewer use only their plans' workspaces, so they are
+    // grouped under capture too.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(st, &cap));
     const bool captured = cap != hipStreamCaptureStatusNone;
